@@ -340,7 +340,7 @@ def main():
     # FP32 peak.  The render stage also holds the 4-5 us one-block sum of the loss partials.
     def kernel_roofline(stage):
         if stage == "render":
-            flop, instr, kname = FLOP_FWD, FWD_VALU_INSTR + EXP_SLOTS, "k_render"
+            flop, instr, kname = FLOP_FWD, FWD_VALU_INSTR + EXP_SLOTS, "k_render<4>"
         else:
             flop, instr, kname = FLOP_BWD, 2 * FWD_VALU_INSTR + EXP_SLOTS, "k_partials<false>"
         sec = stage_ms[stage] / 1e3

@@ -66,7 +66,7 @@ def _compile(src: str) -> str:
 # kernels with counter summaries (profiles/<kernel>_traffic_*.md): source file and the
 # kernel's symbol as it appears mangled (the instantiation the benchmark runs)
 DIGESTED = {"k_partials": ("backward.hip", "10k_partialsILb0E"),
-            "k_render": ("render.hip", "8k_renderE")}
+            "k_render": ("render.hip", "8k_renderILi4EE")}
 DIGESTS = os.path.join(HERE, "kernel_digests.json")
 
 

@@ -2,15 +2,28 @@
 // Gaussian is pre-convolved with the slice profile, so the same formula applies with the
 // record's amplitude and conic).
 //
-// One wavefront owns one GM_TX x GM_TY x GM_TZ tile and accumulates it in LDS.  It walks
-// the tile's Gaussian list (ascending id) in batches of 32: a lane loads one record and
-// prepares that Gaussian's piece (box intersect tile) in LDS.  Then the pieces are taken in
-// list order.  A lane holds one (x, y) column of a piece's footprint and walks the piece's
-// z-range, so the in-plane part of the exponent is formed once per column and each voxel
-// costs two FMAs, one exp2 and one accumulate.  Two consecutive pieces whose footprints sum to
-// at most 64 columns share the wave (the first piece's columns on the low lanes); the first
-// piece's lanes add into the tile before the second's, so every voxel's sum is still formed
-// in ascending Gaussian order and the result is the same on every run.
+// A block owns one GM_TX x GM_TY x GM_TZ tile.  The tile's Gaussian list (ascending id) is cut
+// into 2 to 16 parts (parts_of), one wavefront each, and every wavefront sums its part into its
+// own LDS copy of the tile; the copies are added in a fixed order at the end.  (With one
+// wavefront per tile the 192 tiles of three 64x64x16 stacks left most of the chip idle, each
+// wavefront walking some 750 entries one dependent pass after the other: k_render 182 us, 33 us
+// with 16 parts; at three 128x128x32 stacks 258 against 105 us.)
+//
+// A wavefront walks its part in batches of 32: a lane loads one record and prepares that
+// Gaussian's piece (box intersect tile) in LDS.  Then the pieces are taken in list order.  A
+// lane holds one (x, y) column of a piece's footprint and evaluates it on the tile's four
+// planes, so the in-plane part of the exponent is formed once per column.  The tile keeps a
+// column's four voxels side by side: a lane adds its column with one 16-byte read and one
+// 16-byte write whatever planes the piece reaches (a plane outside the box gets exactly 0).
+// What bounds it at the 256^3 workload is vector issue: about 50 instructions per pass, four of
+// them exponentials.  Evaluating only the planes a pass reaches (ten straight-line variants
+// behind one branch) issued fewer but ran 4% slower, fetching the next pass's pieces one pass
+// ahead 2-5% slower, and padding the tile's rows to 17, 20 or 21 columns changed nothing (the
+// 16-byte accesses do not conflict).
+// Two consecutive pieces whose footprints sum to at most 64 columns share the wave (the first
+// piece's columns on the low lanes); the first piece's lanes add into the tile before the
+// second's, so every voxel's sum is formed in a fixed order and the result is the same on every
+// run.
 //
 // With the paper's block query on a rotated grid (k_render_block, and k_render_field's MASK
 // form) a Gaussian's voxels are not its box: each evaluated voxel of the box is also tested
@@ -23,57 +36,60 @@ namespace {
 
 __device__ __forceinline__ int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// The tile in LDS: column (x, y) of the tile holds its GM_TZ voxels side by side, so that a
+// lane adds a whole column with one 16-byte read and one 16-byte write; rows of the tile are
+// ACC_P columns apart.
+static_assert(GM_TX == 16 && GM_TY == 16 && GM_TZ == 4, "16 x 16 columns of one float4 each");
+constexpr int ACC_P = 16;
+constexpr int ACC_COLS = GM_TY * ACC_P;
+
 // Per (Gaussian, tile) piece, prepared lane-parallel for a batch of list entries, in the
 // frame of the piece's intersection origin (the box clipped to the tile): the centre's x offset
-// plus 1/2 and its y offset, the base-2 conic (off-diagonals doubled), the z-walk constants of
-// the column formula below (F0, E, g1 = d0 kxz, g2 = d0 kyz), the footprint width (as a float
-// and its reciprocal) and area, and the LDS index of the origin minus 1/2.
-struct Piece {
-    float uxh, uy, F0, E;
-    float kxx, kyy, kzz, kxy;
-    float kxz, kyz, g1, g2;
-    float inv_wx, wxf, Ff, basef;
+// plus 1/2 and its y offset, log2 of the amplitude, the base-2 conic (off-diagonals doubled),
+// the footprint width (as a float and its reciprocal), the LDS column of the origin minus 1/2,
+// and the z offset from the centre of each of the tile's planes (DZ_OUT on planes outside the
+// box, where the value is then 2^-huge = 0).
+struct alignas(16) Piece {
+    float uxh, uy, lamp, kxx;
+    float kyy, kzz, kxy, kxz;
+    float kyz, inv_wx, wxf, basef;
+    float dz0, dz1, dz2, dz3;
 };
+// kzz <= -KZZ_MIN (see accumulate_tile), so kzz dz^2 of a plane outside the box is at most
+// -1e20 and the exponential exactly 0
+constexpr float DZ_OUT = 1e25f, KZZ_MIN = 1e-30f;
 
 // Keeps the compiler from moving or merging LDS accesses across this point.  The two groups of
 // lanes of a wave that hold two different Gaussians may touch the same voxel; their
 // read-add-writes must stay two separate, ordered sequences.
 __device__ __forceinline__ void lds_order() { __asm__ __volatile__("" ::: "memory"); }
 
-// Column f of piece p, passed as fh = f + 1/2: its voxel values w[k] = amp 2^Q_k for the
-// z-steps k < KM, and the LDS index of its voxel at k = 0.  The column is (x, y) = (f mod wx,
-// f div wx), found as y = floor(fh / wx) (the fraction (x + 1/2) / wx stays at least 1/(2 wx)
-// from an integer, far beyond the reciprocal's error) and x + 1/2 = fh - y wx, all exact in
-// float.  With dz = k + d0 (d0 = minus the centre's z offset), Q_k = qxy + dz (bz + kzz dz),
-// qxy = dx (kxx dx + kxy dy) + kyy dy^2 and bz = kxz dx + kyz dy, is expanded in k as
-// A + k (B + k kzz) with A = dx (kxx dx + kxy dy + d0 kxz) + dy (kyy dy + d0 kyz) + F0 and
-// B = bz + E: the per-piece parts (F0 = log2 amp + kzz d0^2, E = 2 kzz d0, d0 kxz, d0 kyz) are
-// formed once, and amp enters as log2 amp in the exponent.
-template <int KM>
-__device__ __forceinline__ void eval_column(const Piece& p, float fh, float (&w)[KM], int& idx)
+// Column f of piece p, passed as fh = f + 1/2: its values w = amp 2^Q on the tile's four planes,
+// and its LDS column.  The column is (x, y) = (f mod wx, f div wx), found as
+// y = floor(fh / wx) (the fraction (x + 1/2) / wx stays at least 1/(2 wx) from an integer, far
+// beyond the reciprocal's error) and x + 1/2 = fh - y wx, all exact in float.
+// Q = qxy + dz (bz + kzz dz) with qxy = dx (kxx dx + kxy dy) + kyy dy^2 + log2 amp and
+// bz = kxz dx + kyz dy: centred in every axis, so no large terms cancel.
+__device__ __forceinline__ void eval_column(const Piece& p, float fh, float4& w, int& col)
 {
     const float yf = floorf(fh * p.inv_wx);
     const float xh = fmaf(-yf, p.wxf, fh);
     const float dx = xh - p.uxh;
     const float dy = yf - p.uy;
-    const float A = fmaf(dx, fmaf(p.kxx, dx, fmaf(p.kxy, dy, p.g1)),
-                         fmaf(dy, fmaf(p.kyy, dy, p.g2), p.F0));
-    static_assert(GM_TX == 16 && GM_TY == 16, "index arithmetic assumes 16x16 tiles");
-    idx = (int)fmaf(yf, (float)GM_TX, xh + p.basef);     // an exact small integer
-    w[0] = __builtin_amdgcn_exp2f(A);
-    if (KM > 1) {
-        const float B = fmaf(p.kxz, dx, fmaf(p.kyz, dy, p.E));
-#pragma unroll
-        for (int k = 1; k < KM; ++k)
-            w[k] = __builtin_amdgcn_exp2f(fmaf((float)k, fmaf((float)k, p.kzz, B), A));
-    }
+    col = (int)fmaf(yf, (float)ACC_P, xh + p.basef);     // an exact small integer
+    const float qxy = fmaf(dx, fmaf(p.kxy, dy, p.kxx * dx), fmaf(p.kyy * dy, dy, p.lamp));
+    const float bz = fmaf(p.kxz, dx, p.kyz * dy);
+    w.x = __builtin_amdgcn_exp2f(fmaf(p.dz0, fmaf(p.kzz, p.dz0, bz), qxy));
+    w.y = __builtin_amdgcn_exp2f(fmaf(p.dz1, fmaf(p.kzz, p.dz1, bz), qxy));
+    w.z = __builtin_amdgcn_exp2f(fmaf(p.dz2, fmaf(p.kzz, p.dz2, bz), qxy));
+    w.w = __builtin_amdgcn_exp2f(fmaf(p.dz3, fmaf(p.kzz, p.dz3, bz), qxy));
 }
 
 // The block query on a masked grid (Sec. 3.3.1, Eqs. 4-6): per piece of the batch, its first
-// voxel in grid coordinates and its Gaussian's cell; per tile, the grid's index -> world affine
-// and the query's resolution and radius.
+// voxel in the plane, in grid coordinates, and its Gaussian's cell; per tile, the grid's
+// index -> world affine and the query's resolution and radius.
 struct PieceCell {
-    int ix0, iy0, iz0, pad;
+    int ix0, iy0, pad0, pad1;
     int4 cm;
 };
 struct MaskCtx {
@@ -82,127 +98,73 @@ struct MaskCtx {
     const double* m;
     double res;
     int radius;
+    int t0z;                // the tile's first plane
     const int* vc;          // the tile's voxel cells [3][GM_TILE_VOX] (x, y, z planes), or NULL
 };
 
-// w[k] = 0 for the voxels of column fh of piece p (as eval_column maps it, LDS index idx at
-// k = 0) outside the block: from the tile's voxel cells when they are staged, else formed here
-template <int KM>
+// w = 0 on the planes of column fh of piece p (LDS column col, as eval_column maps it) whose
+// voxel lies outside the block: from the tile's voxel cells when they are staged, else formed
+// here
 __device__ __forceinline__ void mask_column(const Piece& p, const PieceCell& q, const MaskCtx& mc,
-                                            float fh, int idx, float (&w)[KM])
+                                            float fh, int col, float4& w)
 {
+    bool in[GM_TZ];
     if (mc.vc) {
         const long long r = mc.radius;
+        // a lane past its piece reads some voxel's cells and stores nothing
+        const int cc = min(max(col, 0), ACC_COLS - 1);
+        const int v0 = min((cc / ACC_P) * GM_TX + cc % ACC_P, GM_TX * GM_TY - 1);
 #pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            // a lane past its piece (or a z step past the tile) reads some voxel's cells and
-            // stores nothing
-            const int vi = min(max(idx + k * GM_TX * GM_TY, 0), GM_TILE_VOX - 1);
+        for (int k = 0; k < GM_TZ; ++k) {
+            const int vi = v0 + k * GM_TX * GM_TY;
             const long long dx = (long long)mc.vc[vi] - q.cm.x;
             const long long dy = (long long)mc.vc[GM_TILE_VOX + vi] - q.cm.y;
             const long long dz = (long long)mc.vc[2 * GM_TILE_VOX + vi] - q.cm.z;
-            const bool in = dx >= -r && dx <= r && dy >= -r && dy <= r && dz >= -r && dz <= r;
-            if (!in) w[k] = 0.0f;
+            in[k] = dx >= -r && dx <= r && dy >= -r && dy <= r && dz >= -r && dz <= r;
         }
-        return;
-    }
-    const float yf = floorf(fh * p.inv_wx);
-    const float xh = fmaf(-yf, p.wxf, fh);        // x + 1/2 within the piece
-    const int x = q.ix0 + (int)xh, y = q.iy0 + (int)yf;
+    } else {
+        const float yf = floorf(fh * p.inv_wx);
+        const float xh = fmaf(-yf, p.wxf, fh);        // x + 1/2 within the piece
+        const int x = q.ix0 + (int)xh, y = q.iy0 + (int)yf;
 #pragma unroll
-    for (int k = 0; k < KM; ++k)
-        if (!voxel_in_block(mc.m, mc.res, mc.radius, x, y, q.iz0 + k, q.cm)) w[k] = 0.0f;
-}
-
-// acc[column voxel at z-step k] += w[k] for k < KZ (the piece's exact z extent; KZ <= the
-// length of w).  The z-steps are distinct voxels, so all reads are issued before the writes.
-template <int KZ, int KM>
-__device__ __forceinline__ void add_column(float* acc, int idx, const float (&w)[KM])
-{
-    static_assert(KZ <= KM, "z extent within the evaluated steps");
-    float old[KZ];
-#pragma unroll
-    for (int k = 0; k < KZ; ++k) old[k] = acc[idx + k * GM_TX * GM_TY];
-#pragma unroll
-    for (int k = 0; k < KZ; ++k) acc[idx + k * GM_TX * GM_TY] = old[k] + w[k];
-}
-
-// One piece on the whole wave: columns f0 + lane, KM z-steps each (lane_fh = lane + 1/2).
-// MASK: mc (mc.on on a masked grid) and the piece's batch slot jq.
-template <int KM, bool MASK>
-__device__ __forceinline__ void single_piece(const Piece& p, float* acc, int F, float lane_fh,
-                                             const MaskCtx& mc, int jq)
-{
-    float fh = lane_fh;
-#pragma unroll 1
-    for (int f0 = 0; f0 < F; f0 += 64) {
-        float w[KM];
-        int idx;
-        eval_column<KM>(p, fh, w, idx);
-        if (MASK && mc.on) mask_column<KM>(p, mc.pcc[jq], mc, fh, idx, w);
-        if (fh < p.Ff) add_column<KM, KM>(acc, idx, w);
-        fh += 64.0f;
+        for (int k = 0; k < GM_TZ; ++k)
+            in[k] = voxel_in_block(mc.m, mc.res, mc.radius, x, y, mc.t0z + k, q.cm);
     }
+    if (!in[0]) w.x = 0.0f;
+    if (!in[1]) w.y = 0.0f;
+    if (!in[2]) w.z = 0.0f;
+    if (!in[3]) w.w = 0.0f;
 }
 
-// Two pieces side by side in the wave (lane's piece p, column fh - 1/2) with z extents ZA
-// and ZB, evaluated over the larger of the two.  The first piece's read-add-writes complete
-// before the second piece's are issued.  Both extents are template parameters, so a pass
-// dispatches once on the pair and its two add phases carry no branches of their own.
-template <int ZA, int ZB, bool MASK>
-__device__ __forceinline__ void paired_pieces(const Piece& p, float* acc, bool act, bool first,
-                                              float fh, const MaskCtx& mc, int jq)
+__device__ __forceinline__ void add_column(float4* acc, int col, const float4& w)
 {
-    constexpr int KM = ZA > ZB ? ZA : ZB;
-    // every lane evaluates (a lane past its piece's footprint computes values it never
-    // stores), so no lane mask is needed around the evaluation
-    float w[KM];
-    int idx;
-    eval_column<KM>(p, fh, w, idx);
-    if (MASK && mc.on) mask_column<KM>(p, mc.pcc[jq], mc, fh, idx, w);
-    lds_order();
-    if (act && first) add_column<ZA, KM>(acc, idx, w);
-    lds_order();
-    if (act && !first) add_column<ZB, KM>(acc, idx, w);
-    lds_order();
+    float4 o = acc[col];
+    o.x += w.x;
+    o.y += w.y;
+    o.z += w.z;
+    o.w += w.w;
+    acc[col] = o;
 }
 
-// paired_pieces for uniform z extents wza, wzb in [1, GM_TZ]
-template <bool MASK>
-__device__ __forceinline__ void paired_pieces_kz(const Piece& p, float* acc, bool act,
-                                                 bool first, float fh, int wza, int wzb,
-                                                 const MaskCtx& mc, int jq)
-{
-    static_assert(GM_TZ == 4, "z extents 1..4 are dispatched below");
-#define GM_PAIR_CASE(A, B) \
-    case (A - 1) * 4 + (B - 1): paired_pieces<A, B, MASK>(p, acc, act, first, fh, mc, jq); break;
-    switch ((wza - 1) * 4 + (wzb - 1)) {
-    GM_PAIR_CASE(1, 1) GM_PAIR_CASE(1, 2) GM_PAIR_CASE(1, 3) GM_PAIR_CASE(1, 4)
-    GM_PAIR_CASE(2, 1) GM_PAIR_CASE(2, 2) GM_PAIR_CASE(2, 3) GM_PAIR_CASE(2, 4)
-    GM_PAIR_CASE(3, 1) GM_PAIR_CASE(3, 2) GM_PAIR_CASE(3, 3) GM_PAIR_CASE(3, 4)
-    GM_PAIR_CASE(4, 1) GM_PAIR_CASE(4, 2) GM_PAIR_CASE(4, 3)
-    default: paired_pieces<4, 4, MASK>(p, acc, act, first, fh, mc, jq); break;
-    }
-#undef GM_PAIR_CASE
-}
-
-// List entries prepared per batch; 32 keeps the LDS of a wavefront at 6 KB so that six
-// wavefronts fit per SIMD.
+// List entries prepared per batch.
 constexpr int RB = 32;
 
-// Barrier before LDS written by some lanes is read by others.  BLOCK: the workgroup is this
-// one wavefront (a block barrier); otherwise the other wavefronts of the block run their own
-// tiles, so only this wavefront's LDS accesses are ordered (a workgroup-scope fence waits for
-// them; the wavefront's lanes run in lockstep).
-template <bool BLOCK>
-__device__ __forceinline__ void tile_sync()
+// LDS of NW wavefronts: their pieces, then their copies of the tile.  (In a pass of the last of
+// RB pieces, the lanes past its footprint read the 64 bytes after it and store nothing; the
+// copies follow so that those bytes are the block's own.)
+template <int NW>
+struct TileLds {
+    Piece pcs[NW][RB];
+    float4 accs[NW * ACC_COLS];
+};
+
+// Barrier before LDS written by some lanes of a wavefront is read by others of the same
+// wavefront, which owns that LDS: a wavefront's LDS accesses execute in order, so only the
+// compiler has to keep them in order.
+__device__ __forceinline__ void wave_sync()
 {
-    if constexpr (BLOCK) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-    }
+    lds_order();
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Origin and grid of flattened tile t of a launch (t < a.total_blocks).
@@ -228,46 +190,104 @@ __device__ __forceinline__ TilePos tile_pos(const RenderArgs& a, int t)
     return p;
 }
 
-constexpr int VPL = GM_TILE_VOX / 64;   // tile voxels per lane in the epilogues
+// Columns per thread in the epilogues of a tile finished by T threads (at least one).
+template <int T>
+constexpr int cols_per_thread() { return GM_TX * GM_TY / T > 0 ? GM_TX * GM_TY / T : 1; }
 
 // loss mode: the tile's data values, loaded before the Gaussian list is walked so that their
-// latency is hidden behind the accumulation
-__device__ __forceinline__ void load_targets(const TilePos& P, int lane, float (&tv)[VPL])
+// latency is hidden behind the accumulation (thread t of T: columns t, t + T, ...)
+template <int T>
+__device__ __forceinline__ void load_targets(const TilePos& P, int t,
+                                             float (&tv)[cols_per_thread<T>()][GM_TZ])
 {
     const RenderGrid& G = *P.G;
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) {
-        const int i = j * 64 + lane;
-        const int x = i % GM_TX, y = (i / GM_TX) % GM_TY, z = i / (GM_TX * GM_TY);
-        const int gx = P.t0x + x, gy = P.t0y + y, gz = P.t0z + z;
-        // outside the grid: a valid address (voxel 0) whose value goes unused
-        const bool in = (gx < G.nx) & (gy < G.ny) & (gz < G.nz);
-        const size_t v = in ? ((size_t)gz * G.ny + gy) * G.nx + gx : 0;
-        tv[j] = __builtin_nontemporal_load(G.target + v);
+    for (int j = 0; j < cols_per_thread<T>(); ++j) {
+        const int c = (j * T + t) % (GM_TX * GM_TY);
+        const int gx = P.t0x + c % GM_TX, gy = P.t0y + c / GM_TX;
+#pragma unroll
+        for (int z = 0; z < GM_TZ; ++z) {
+            const int gz = P.t0z + z;
+            // outside the grid: a valid address (voxel 0) whose value goes unused
+            const bool in = (gx < G.nx) & (gy < G.ny) & (gz < G.nz);
+            const size_t v = in ? ((size_t)gz * G.ny + gy) * G.nx + gx : 0;
+            tv[j][z] = __builtin_nontemporal_load(G.target + v);
+        }
     }
 }
 
-// acc (the tile's voxels, LDS) = the sum over the tile's list of Gaussians, in list order.
-// Ends with a tile_sync, so every lane may read any voxel afterwards.  MASK: on a masked grid
-// every voxel is also tested against its Gaussian's cell block (pcc: the batch's PieceCells;
-// vcell, when given: LDS for the tile's voxel cells, formed once per tile).
-template <bool BLOCK, bool MASK>
-__device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TilePos& P, float* acc,
-                                                Piece* pc, int lane, PieceCell* pcc,
-                                                int* vcell = nullptr)
+// The lane's piece and column of one pass: lanes [0, Fa) take columns of piece j, the others
+// of piece j + 1.
+struct Pass {
+    Piece p;
+    float fh;
+};
+__device__ __forceinline__ Pass load_pass(const Piece* pc, int j, int Fa, int lane,
+                                          float lane_fh)
 {
+    Pass q;
+    const bool first = lane < Fa;
+    q.p = *reinterpret_cast<const Piece*>(reinterpret_cast<const char*>(pc + j) +
+                                          (first ? 0 : (int)sizeof(Piece)));
+    q.fh = lane_fh - (first ? 0.0f : (float)Fa);
+    return q;
+}
+
+// A tile's list [s, e) is cut into 2^a.parts_log2 parts (2 to 16), whole batches each: part k
+// starts at entry part_start(k), and part_start(2^parts_log2) >= e.
+struct TileList {
+    int s, e, nbatch, log2p;
+    __device__ __forceinline__ int part_start(int k) const
+    {
+        return s + ((nbatch * k) >> log2p) * RB;     // at most 2^31 / RB batches, 16 parts
+    }
+};
+__device__ __forceinline__ TileList tile_list(const RenderArgs& a, const TilePos& P)
+{
+    const int64_t bt = P.G->bin_tile_base + P.lt;
+    TileList l;
+    l.s = sgpr(a.tile_start[bt]);
+    l.e = sgpr(a.tile_start[bt + 1]);
+    l.nbatch = (l.e - l.s + RB - 1) / RB;
+    l.log2p = a.parts_log2;
+    return l;
+}
+
+__device__ __forceinline__ float4 add4(const float4& a, const float4& b)
+{
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
+// acc (the tile's columns, LDS, owned by this wavefront) = the sum of parts [k0, k0 + np) of the
+// tile's list, each part summed in list order and the parts one after the other (np > 1 only with
+// PARTS).  Ends with a wave_sync.  MASK: on a masked grid every voxel is also tested against its
+// Gaussian's cell block (pcc: the batch's PieceCells; vcell, when given: the tile's voxel cells).
+template <bool MASK, bool PARTS>
+__device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TilePos& P, float4* acc,
+                                                Piece* pc, int lane, int k0, int np,
+                                                PieceCell* pcc, const int* vcell)
+{
+    const TileList L = tile_list(a, P);
+    const int s = L.part_start(k0), e = min(L.e, L.part_start(k0 + np));
+    // PARTS: the sum of the finished parts, lane's columns lane + 64 j, and the next part's start
+    float4 tot[4] = {};
+    int k = k0 + 1, next = PARTS ? L.part_start(k0 + 1) : 0;
+    auto flush = [&]() {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            tot[j] = add4(tot[j], acc[j * 64 + lane]);     // 0 + v = v: no value is negative
+            acc[j * 64 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        ++k;
+        next = L.part_start(k);
+    };
     const RenderGrid& G = *P.G;
     const int t0x = P.t0x, t0y = P.t0y, t0z = P.t0z;
     const float* __restrict__ recbase = a.records + (size_t)G.grid_index * a.n_gauss * 16;
     const int* __restrict__ pg = a.pair_gauss;
     const float lane_fh = (float)lane + 0.5f;
 
-#pragma unroll
-    for (int j = 0; j < GM_TILE_VOX / 64; ++j) acc[j * 64 + lane] = 0.0f;
-
-    const int64_t bt = G.bin_tile_base + P.lt;
-    const int s = sgpr(a.tile_start[bt]);
-    const int e = sgpr(a.tile_start[bt + 1]);
+    for (int j = lane; j < ACC_COLS; j += 64) acc[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 
     // Software pipeline over batches: while a batch's pieces are evaluated, the next batch's
     // records and the list entries of the batch after it are in flight (lane i of a batch
@@ -291,28 +311,14 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
     int id_rec = load_id(s);     // the entry whose record is in n0..n3
     load_rec(id_rec);
     int id_next = load_id(s + RB);
-    MaskCtx mcv;
-    mcv.pcc = pcc;
-    mcv.m = G.index_to_world;
-    mcv.res = a.bq.res;
-    mcv.radius = a.bq.radius;
-    mcv.vc = vcell;
-    mcv.on = MASK && G.masked;
-    const MaskCtx& mc = mcv;
-    if (MASK && mc.on && vcell) {
-        // the cells of the tile's voxels (the tile_sync at the first batch orders these
-        // stores before their reads), clamped to [-2^30, 2^30] as the means' cells are
-#pragma unroll 1
-        for (int j = 0; j < GM_TILE_VOX / 64; ++j) {
-            const int i = j * 64 + lane;
-            double c[3];
-            voxel_cells(G.index_to_world, a.bq.res, t0x + i % GM_TX, t0y + (i / GM_TX) % GM_TY,
-                        t0z + i / (GM_TX * GM_TY), c);
-#pragma unroll
-            for (int u = 0; u < 3; ++u)
-                vcell[u * GM_TILE_VOX + i] = (int)fmin(fmax(c[u], -1073741824.0), 1073741824.0);
-        }
-    }
+    MaskCtx mc;
+    mc.pcc = pcc;
+    mc.m = G.index_to_world;
+    mc.res = a.bq.res;
+    mc.radius = a.bq.radius;
+    mc.t0z = t0z;
+    mc.vc = vcell;
+    mc.on = MASK && G.masked;
 
 #pragma unroll 1
     for (int b0 = s; b0 < e; b0 += RB) {
@@ -322,190 +328,276 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
         load_rec(id_next);
         id_rec = id_next;
         id_next = load_id(b0 + 2 * RB);
-        tile_sync<BLOCK>();
-        int myF = 0, myWz = 0;  // this lane's piece: footprint area and z extent
+        wave_sync();
+        if (PARTS)
+            while (b0 >= next && k < k0 + np) flush();
+        int myF = 0;            // this lane's piece: footprint area
         if (lane < nb) {
             const int lox = __float_as_int(r2.z), loy = __float_as_int(r2.w);
             const int loz = __float_as_int(r3.x), hix = __float_as_int(r3.y);
             const int hiy = __float_as_int(r3.z), hiz = __float_as_int(r3.w);
-            const int ix0 = max(lox, t0x), iy0 = max(loy, t0y), iz0 = max(loz, t0z);
+            const int ix0 = max(lox, t0x), iy0 = max(loy, t0y);
             const int wx = min(hix, t0x + GM_TX - 1) - ix0 + 1;
             const int wy = min(hiy, t0y + GM_TY - 1) - iy0 + 1;
-            const int wz = min(hiz, t0z + GM_TZ - 1) - iz0 + 1;
-            const bool ok = wx > 0 && wy > 0 && wz > 0;  // always true for a listed tile
-            const float d0 = (float)(iz0 - loz) - r0.z;
+            // a listed box overlaps the tile
+            const bool ok = wx > 0 && wy > 0;
             const int wxe = ok ? wx : 1;
             Piece p;
             p.uxh = (r0.x - (float)(ix0 - lox)) + 0.5f;
             p.uy = r0.y - (float)(iy0 - loy);
-            p.kxx = r1.x; p.kyy = r1.y; p.kzz = r1.z; p.kxy = r1.w;
+            p.kxx = r1.x; p.kyy = r1.y; p.kxy = r1.w;
             p.kxz = r2.x; p.kyz = r2.y;
+            // far below any visible curvature; keeps the planes outside the box at zero
+            p.kzz = fminf(r1.z, -KZZ_MIN);
             // amp >= 0 (0 for an empty box, never listed): log2 0 = -inf gives zeros
-            p.F0 = log2f(r0.w) + p.kzz * d0 * d0;
-            p.E = 2.0f * p.kzz * d0;
-            p.g1 = d0 * p.kxz;
-            p.g2 = d0 * p.kyz;
+            p.lamp = log2f(r0.w);
             p.wxf = (float)wxe;
             p.inv_wx = __builtin_amdgcn_rcpf(p.wxf);
+            p.basef = (float)((iy0 - t0y) * ACC_P + (ix0 - t0x)) - 0.5f;
+            const int zl = loz - t0z, zh = hiz - t0z;    // the box's planes in the tile's frame
+            const float d0 = (float)(-zl);
+            p.dz0 = zl <= 0 && zh >= 0 ? d0 - r0.z : DZ_OUT;
+            p.dz1 = zl <= 1 && zh >= 1 ? (d0 + 1.0f) - r0.z : DZ_OUT;
+            p.dz2 = zl <= 2 && zh >= 2 ? (d0 + 2.0f) - r0.z : DZ_OUT;
+            p.dz3 = zl <= 3 && zh >= 3 ? (d0 + 3.0f) - r0.z : DZ_OUT;
             myF = ok ? wx * wy : 0;
-            myWz = ok ? wz : 0;
-            p.Ff = (float)myF;
-            p.basef = (float)(((iz0 - t0z) * GM_TY + (iy0 - t0y)) * GM_TX + (ix0 - t0x)) - 0.5f;
             pc[lane] = p;
             if (MASK && mc.on) {
                 PieceCell q;
                 q.ix0 = ix0;
                 q.iy0 = iy0;
-                q.iz0 = iz0;
-                q.pad = 0;
+                q.pad0 = q.pad1 = 0;
                 q.cm = a.bq.cells[(uint32_t)my_entry & GM_ID_MASK];
                 pcc[lane] = q;
             }
         }
-        // bit j: pieces j and j + 1 fit side by side in the wave (footprints summing to <= 64)
+        // pieces j and j + 1 share a pass when their footprints sum to <= 64.  Lane j holds
+        // that pass as one word: (columns of both << 16) | footprint of piece j, the upper half
+        // equal to the lower where piece j goes alone
         const int nextF = __shfl_down(myF, 1, 64);
-        const uint64_t pm = __ballot(lane + 1 < nb && myF + nextF <= 64);
-        // lane j: (F_j << 6) | (wz_{j+1} << 3) | wz_j, so that one read gives a pass its
-        // footprint and both z extents (F <= 256, wz <= 4)
-        const int pk = (myF << 6) | (__shfl_down(myWz, 1, 64) << 3) | myWz;
-        tile_sync<BLOCK>();
+        const bool pair = lane + 1 < nb && myF + nextF <= 64;
+        const int pk = myF | ((pair ? myF + nextF : myF) << 16);
+        wave_sync();
         int j = 0;
+        int k = __builtin_amdgcn_readlane(pk, 0);
+        Pass q = load_pass(pc, 0, k & 0xffff, lane, lane_fh);
 #pragma unroll 1
-        while (j < nb) {
-            const int k = __builtin_amdgcn_readlane(pk, j);
-            if ((pm >> j) & 1u) {
-                // pieces j and j+1 side by side: lanes [0, Fa) take piece j, the next Fb piece j+1
-                const int Fa = k >> 6, wza = k & 7, wzb = (k >> 3) & 7;
-                const bool first = lane < Fa;
-                const Piece p = *reinterpret_cast<const Piece*>(
-                    reinterpret_cast<const char*>(pc + j) + (first ? 0 : (int)sizeof(Piece)));
-                const float fh = lane_fh - (first ? 0.0f : (float)Fa);
-                const bool act = fh < p.Ff;
-                paired_pieces_kz<MASK>(p, acc, act, first, fh, wza, wzb, mc, first ? j : j + 1);
-                j += 2;
-            } else {
-                const Piece p = pc[j];
-                const int F = k >> 6, wz = k & 7;
-                switch (wz) {
-                case 0: break;
-                case 1: single_piece<1, MASK>(p, acc, F, lane_fh, mc, j); break;
-                case 2: single_piece<2, MASK>(p, acc, F, lane_fh, mc, j); break;
-                case 3: single_piece<3, MASK>(p, acc, F, lane_fh, mc, j); break;
-                default: single_piece<GM_TZ, MASK>(p, acc, F, lane_fh, mc, j); break;
-                }
-                j += 1;
+        for (;;) {
+            const int Fa = k & 0xffff, Ft = k >> 16;
+            const int jn = j + (Ft > Fa ? 2 : 1);
+            const bool more = jn < nb;
+            k = __builtin_amdgcn_readlane(pk, more ? jn : j);
+            float4 w;
+            int col;
+            eval_column(q.p, q.fh, w, col);
+            if (MASK && mc.on)
+                mask_column(q.p, mc.pcc[lane < Fa || Ft == Fa ? j : j + 1], mc, q.fh, col, w);
+            // every lane evaluates (a lane past its piece's footprint computes values it
+            // never stores), so no lane mask is needed around the evaluation
+            lds_order();
+            if (lane < Fa) add_column(acc, col, w);
+            lds_order();
+            if (lane >= Fa && lane < Ft) add_column(acc, col, w);
+            lds_order();
+#pragma unroll 1
+            for (int f = 64; f < Fa; f += 64) {
+                eval_column(q.p, q.fh + (float)f, w, col);
+                if (MASK && mc.on) mask_column(q.p, mc.pcc[j], mc, q.fh + (float)f, col, w);
+                lds_order();
+                if (lane + f < Fa) add_column(acc, col, w);
+                lds_order();
             }
+            if (!more) break;
+            j = jn;
+            q = load_pass(pc, j, k & 0xffff, lane, lane_fh);
         }
     }
-    tile_sync<BLOCK>();
+    wave_sync();
+    if (PARTS) {
+        while (k <= k0 + np) flush();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j * 64 + lane] = tot[j];
+        wave_sync();
+    }
+}
+
+// Every kernel sums a tile's parts in the same association, whichever wavefronts took them: with
+// up to 8 parts one after the other, with 16 in consecutive pairs first.
+constexpr int GROUPS = 8;
+
+// Column col of the tile from the NP parts' copies of it
+template <int NP>
+__device__ __forceinline__ float4 sum_parts(const float4* accs, int col)
+{
+    constexpr int M = NP > GROUPS ? NP / GROUPS : 1;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int g = 0; g < NP / M; ++g) {
+        float4 u = accs[g * M * ACC_COLS + col];
+#pragma unroll
+        for (int i = 1; i < M; ++i) u = add4(u, accs[(g * M + i) * ACC_COLS + col]);
+        v = g == 0 ? u : add4(v, u);
+    }
+    return v;
 }
 
 // Writes the finished tile (plain mode), or (loss mode) the smooth-L1 data term on it (Eq. 11,
 // beta = 1): dL/dI = clamp(I - y, -1, 1) / N, the rendering when G.out is set, and the tile's
-// FP64 sum of smoothL1(I - y) to a.loss_part[part].
+// FP64 sum of smoothL1(I - y) to a.loss_part[part].  The tile is the sum of its NP parts' copies
+// accs, finished by T threads (thread t: columns t, t + T, ...); red: LDS, one double per
+// wavefront of them (unused for one wavefront).
+template <int NP, int T>
 __device__ __forceinline__ void finish_tile(const RenderArgs& a, const TilePos& P,
-                                            const float* acc, const float (&tv)[VPL], int lane,
-                                            int part)
+                                            const float4* accs,
+                                            const float (&tv)[cols_per_thread<T>()][GM_TZ], int t,
+                                            int part, double* red)
 {
     const RenderGrid& G = *P.G;
     float* out = G.out;
-    if (!a.loss_part) {
-#pragma unroll
-        for (int j = 0; j < GM_TILE_VOX / 64; ++j) {
-            const int i = j * 64 + lane;
-            const int x = i % GM_TX, y = (i / GM_TX) % GM_TY, z = i / (GM_TX * GM_TY);
-            const int gx = P.t0x + x, gy = P.t0y + y, gz = P.t0z + z;
-            if ((gx < G.nx) & (gy < G.ny) & (gz < G.nz))
-                out[((size_t)gz * G.ny + gy) * G.nx + gx] = acc[i];
-        }
-        return;
-    }
     const float g_scale = (float)a.inv_n;
     double lsum = 0.0;
 #pragma unroll
-    for (int j = 0; j < GM_TILE_VOX / 64; ++j) {
-        const int i = j * 64 + lane;
-        const int x = i % GM_TX, y = (i / GM_TX) % GM_TY, z = i / (GM_TX * GM_TY);
-        const int gx = P.t0x + x, gy = P.t0y + y, gz = P.t0z + z;
-        if ((gx < G.nx) & (gy < G.ny) & (gz < G.nz)) {
-            const size_t v = ((size_t)gz * G.ny + gy) * G.nx + gx;
-            const float val = acc[i];
-            if (out) out[v] = val;
-            const float d = val - tv[j];
+    for (int j = 0; j < cols_per_thread<T>(); ++j) {
+        const int c = j * T + t;
+        const int x = c % GM_TX, y = c / GM_TX;
+        const int gx = P.t0x + x, gy = P.t0y + y;
+        if (c >= GM_TX * GM_TY || gx >= G.nx || gy >= G.ny) continue;
+        const float4 v = sum_parts<NP>(accs, y * ACC_P + x);
+        const float val[GM_TZ] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int z = 0; z < GM_TZ; ++z) {
+            const int gz = P.t0z + z;
+            if (gz >= G.nz) continue;
+            const size_t o = ((size_t)gz * G.ny + gy) * G.nx + gx;
+            if (out) out[o] = val[z];
+            if (!a.loss_part) continue;
+            const float d = val[z] - tv[j][z];
             const float ad = fabsf(d);
             lsum += ad < 1.0f ? 0.5 * (double)d * (double)d : (double)ad - 0.5;
-            G.dl[v] = fminf(fmaxf(d, -1.0f), 1.0f) * g_scale;
+            G.dl[o] = fminf(fmaxf(d, -1.0f), 1.0f) * g_scale;
         }
     }
+    if (!a.loss_part) return;
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
-    if (lane == 0) a.loss_part[part] = lsum;
+    if (T == 64) {
+        if ((t & 63) == 0) a.loss_part[part] = lsum;
+        return;
+    }
+    if ((t & 63) == 0) red[t >> 6] = lsum;
+    __syncthreads();
+    if (t == 0) {
+        double v = red[0];
+#pragma unroll
+        for (int w = 1; w < T / 64; ++w) v += red[w];
+        a.loss_part[part] = v;
+    }
 }
 
-__global__ __launch_bounds__(64) void k_render(const RenderArgs a)
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_render(const RenderArgs a)
 {
-    __shared__ float acc[GM_TILE_VOX];
-    __shared__ Piece pc[RB];
-    const int lane = threadIdx.x;
+    __shared__ TileLds<NW> sh;
+    __shared__ double red[NW];
+    const int lane = threadIdx.x & 63, w = sgpr(threadIdx.x >> 6);
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const TilePos P = tile_pos(a, blk);
-    float tv[VPL];
-    if (a.loss_part) load_targets(P, lane, tv);
-    accumulate_tile<true, false>(a, P, acc, pc, lane, nullptr);
-    finish_tile(a, P, acc, tv, lane, blk);
+    float tv[cols_per_thread<64 * NW>()][GM_TZ];
+    if (a.loss_part) load_targets<64 * NW>(P, threadIdx.x, tv);
+    accumulate_tile<false, false>(a, P, sh.accs + w * ACC_COLS, sh.pcs[w], lane, w, 1, nullptr,
+                                  nullptr);
+    __syncthreads();
+    finish_tile<NW, 64 * NW>(a, P, sh.accs, tv, threadIdx.x, a.part0 + blk, red);
 }
 
 // k_render for launches that hold a masked grid (the block query on a rotated grid)
-__global__ __launch_bounds__(64) void k_render_block(const RenderArgs a)
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_render_block(const RenderArgs a)
 {
-    __shared__ float acc[GM_TILE_VOX];
-    __shared__ Piece pc[RB];
-    __shared__ PieceCell pcc[RB];
+    __shared__ TileLds<NW> sh;
+    __shared__ PieceCell pccs[NW][RB];
     __shared__ int vcell[3 * GM_TILE_VOX];
-    const int lane = threadIdx.x;
+    __shared__ double red[NW];
+    const int lane = threadIdx.x & 63, w = sgpr(threadIdx.x >> 6);
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const TilePos P = tile_pos(a, blk);
-    float tv[VPL];
-    if (a.loss_part) load_targets(P, lane, tv);
-    accumulate_tile<true, true>(a, P, acc, pc, lane, pcc, vcell);
-    finish_tile(a, P, acc, tv, lane, blk);
+    float tv[cols_per_thread<64 * NW>()][GM_TZ];
+    if (a.loss_part) load_targets<64 * NW>(P, threadIdx.x, tv);
+    if (P.G->masked) {
+        // the cells of the tile's voxels, clamped to [-2^30, 2^30] as the means' cells are
+#pragma unroll 1
+        for (int i = threadIdx.x; i < GM_TILE_VOX; i += 64 * NW) {
+            double c[3];
+            voxel_cells(P.G->index_to_world, a.bq.res, P.t0x + i % GM_TX,
+                        P.t0y + (i / GM_TX) % GM_TY, P.t0z + i / (GM_TX * GM_TY), c);
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+                vcell[u * GM_TILE_VOX + i] = (int)fmin(fmax(c[u], -1073741824.0), 1073741824.0);
+        }
+        __syncthreads();
+    }
+    accumulate_tile<true, false>(a, P, sh.accs + w * ACC_COLS, sh.pcs[w], lane, w, 1, pccs[w],
+                                 vcell);
+    __syncthreads();
+    finish_tile<NW, 64 * NW>(a, P, sh.accs, tv, threadIdx.x, a.part0 + blk, red);
 }
 
 // Render + residual field (Sec. 3.4, Eq. 8: I_final = I + r) in one pass.  Blocks of FW
-// wavefronts share the field's weights, staged once in LDS; each wavefront takes whole tiles
-// (the tiles of the launch are split into eight contiguous ranges, one per XCD, whose blocks
-// deal them to their wavefronts), renders a tile into its LDS accumulator exactly as k_render
-// does, then evaluates the field on the tile's voxels in 64 groups of 16 (one x row each) and
-// adds out_scale tanh(z_out) to each voxel before the store or loss epilogue.  Each point's
+// wavefronts share the field's weights, staged once in LDS, and stay resident; the tiles of the
+// launch are split into eight contiguous ranges, one per XCD, dealt to that XCD's blocks.  A
+// tile is taken by one wavefront (TW = 1) or, on small grids whose tiles would leave wavefronts
+// idle, by the whole block (TW = FW).  The tile's parts are rendered exactly as k_render does,
+// then the field is evaluated on the tile's voxels in 64 groups of 16 (one x row each) and
+// out_scale tanh(z_out) added to each voxel before the store or loss epilogue.  Each point's
 // field value is the same arithmetic as the field's own forward kernel, so the result is bit
 // for bit the render followed by gm_nrf_forward (and the loss the same terms).
 constexpr int FW = 8;
+static_assert(FW == GROUPS, "a block's wavefronts take one group of parts each");
 
-template <int KT, int DEPTH, bool MASK>
-__global__ __launch_bounds__(64 * FW) void k_render_field(const RenderArgs a, const NrfArgs f)
+// Two blocks fit a CU's LDS up to four layers of 64 inputs or three of 128: four wavefronts per
+// SIMD, at most 128 registers each.
+template <int KT, int DEPTH>
+constexpr int field_waves(bool masked)
+{
+    const bool two = 2 * (sizeof(nrfcore::Lds<KT, DEPTH>) + sizeof(TileLds<FW>)) <= 160 * 1024;
+    return two && !masked ? 4 : 2;
+}
+
+template <int KT, int DEPTH, bool MASK, int TW>
+__global__ __launch_bounds__(64 * FW, (field_waves<KT, DEPTH>(MASK))) void k_render_field(const RenderArgs a, const NrfArgs f)
 {
     __shared__ nrfcore::Lds<KT, DEPTH> sw;
-    __shared__ float accs[FW][GM_TILE_VOX];
-    __shared__ Piece pcs[FW][RB];
+    __shared__ TileLds<FW> sh;
     __shared__ PieceCell pccs[MASK ? FW : 1][RB];
     nrfcore::load_weights<KT, DEPTH>(f, sw);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, row = lane & 15;
+    const int lane = threadIdx.x & 63, w = sgpr(threadIdx.x >> 6), g = lane >> 4, row = lane & 15;
     nrfcore::v4s wo[4];
     nrfcore::load_wout(f, wo);
-    float* acc = accs[w];
-    Piece* pc = pcs[w];
+    float4* own = sh.accs + w * ACC_COLS;           // this wavefront's copy
+    float4* acc = TW == 1 ? own : sh.accs;          // the tile
     const int xcd = blockIdx.x & 7;
     const int nbx = (int)(gridDim.x >> 3);     // the launch has a multiple of 8 blocks
     const int T = a.total_blocks;
     const int lo = (int)((int64_t)T * xcd / 8), hi = (int)((int64_t)T * (xcd + 1) / 8);
+    constexpr int TPB = FW / TW;               // tiles a block holds at a time
+    const int np = (1 << a.parts_log2) / TW;            // parts per wavefront
+    const int k0 = TW == 1 ? 0 : w * np;
 #pragma unroll 1
-    for (int t = lo + (int)(blockIdx.x >> 3) * FW + w; t < hi; t += nbx * FW) {
+    for (int t = lo + (int)(blockIdx.x >> 3) * TPB + w / TW; t < hi; t += nbx * TPB) {
         const TilePos P = tile_pos(a, t);
         const RenderGrid& G = *P.G;
-        float tv[VPL];
-        if (a.loss_part) load_targets(P, lane, tv);
-        accumulate_tile<false, MASK>(a, P, acc, pc, lane, pccs[MASK ? w : 0]);
+        accumulate_tile<MASK, true>(a, P, own, sh.pcs[w], lane, k0, np, pccs[MASK ? w : 0], nullptr);
+        if constexpr (TW > 1) {
+            __syncthreads();
+            for (int c = threadIdx.x; c < ACC_COLS; c += 64 * FW) {
+                float4 v = sh.accs[c];
+#pragma unroll
+                for (int u = 1; u < FW; ++u) v = add4(v, sh.accs[u * ACC_COLS + c]);
+                sh.accs[c] = v;
+            }
+            __syncthreads();
+        }
 #pragma unroll 1
-        for (int q = 0; q < GM_TILE_VOX / 16; ++q) {
+        for (int q = w % TW; q < GM_TILE_VOX / 16; q += TW) {
             const int vy = P.t0y + (q % GM_TY), vz = P.t0z + q / GM_TY, vx = P.t0x + row;
             if (vy >= G.ny || vz >= G.nz) continue;     // uniform over the wavefront
             const float x[3] = {nrfcore::world_coord(G.index_to_world, vx, vy, vz),
@@ -514,11 +606,26 @@ __global__ __launch_bounds__(64 * FW) void k_render_field(const RenderArgs a, co
             nrfcore::Tile<KT, DEPTH> Tl;
             nrfcore::tile_forward<KT, DEPTH>(f, sw, x, Tl);
             const float zo = nrfcore::tile_output<KT, DEPTH>(f, Tl, wo);   // lane group 0
-            if (g == 0 && vx < G.nx) acc[q * 16 + row] += f.out_scale * tanhf(zo);
+            if (g == 0 && vx < G.nx)
+                reinterpret_cast<float*>(acc + (q % GM_TY) * ACC_P + row)[q / GM_TY] +=
+                    f.out_scale * tanhf(zo);
         }
-        tile_sync<false>();
-        finish_tile(a, P, acc, tv, lane, t);
-        tile_sync<false>();
+        if constexpr (TW == 1) {
+            wave_sync();
+            float tv[cols_per_thread<64>()][GM_TZ];
+            if (a.loss_part) load_targets<64>(P, lane, tv);
+            finish_tile<1, 64>(a, P, acc, tv, lane, a.part0 + t, nullptr);
+            wave_sync();
+        } else {
+            // the loss sums go where the pieces were: no wavefront prepares pieces before the
+            // next barrier
+            __syncthreads();
+            float tv[cols_per_thread<64 * FW>()][GM_TZ];
+            if (a.loss_part) load_targets<64 * FW>(P, threadIdx.x, tv);
+            finish_tile<1, 64 * FW>(a, P, acc, tv, threadIdx.x, a.part0 + t,
+                                    reinterpret_cast<double*>(sh.pcs));
+            __syncthreads();
+        }
     }
 }
 
@@ -550,54 +657,87 @@ __global__ __launch_bounds__(FIN_THREADS) void k_render_loss_finish(const double
     if (t == 0) *loss = (float)(sh[0] * inv_n);
 }
 
-}  // namespace
-
-hipError_t launch_render(const RenderArgs& a, hipStream_t s)
+// Parts a tile's list is cut into, by the tiles of its grid (a property of the grid alone, so
+// that every kernel and every listing of grids sums a tile the same way).  A small grid has too
+// few tiles to fill the chip with a wavefront each.  Measured training iterations (us) at 2 / 4 /
+// 8 / 16 wavefronts per tile: 64 tiles per grid 200 / 165 / 149 / 137; 216: 239 / 209 / 197 /
+// 207; 512: 429 / 394 / 383 / 420; 1728: 582 / 561 / 569 / 709; 4096: 1172 / 1148 / 1179 / 1537
+// (one: 277, 307, 515, 633, 1239); rendering one grid of 32000 tiles 804 / 816 / 911 / 1623.
+int parts_of(const RenderGrid& g)
 {
-    if (a.total_blocks == 0) return hipSuccess;
-    bool masked = false;
-    for (int k = 0; k < a.n_render; ++k) masked = masked || a.rg[k].masked;
-    if (masked)
-        hipLaunchKernelGGL(k_render_block, dim3((unsigned)a.total_blocks), dim3(64), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_render, dim3((unsigned)a.total_blocks), dim3(64), 0, s, a);
-    if (a.loss_part)
-        hipLaunchKernelGGL(k_render_loss_finish, dim3(1), dim3(FIN_THREADS), 0, s, a.loss_part,
-                           a.total_blocks, a.inv_n, a.loss);
-    return hipGetLastError();
+    const int64_t tiles = (int64_t)g.ntx * g.nty * g.ntz;
+    return tiles <= 128 ? 16 : tiles <= 1024 ? 8 : tiles <= 16384 ? 4 : 2;
 }
 
-template <int KT, int DEPTH, bool MASK>
-static void launch_field_mt(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
+// The grids of a that take np parts, as a launch of their own (no blocks: none)
+RenderArgs with_parts(const RenderArgs& a, int np)
+{
+    RenderArgs r = a;
+    r.parts_log2 = __builtin_ctz((unsigned)np);
+    r.n_render = 0;
+    r.total_blocks = 0;
+    for (int k = 0; k < a.n_render; ++k) {
+        if (parts_of(a.rg[k]) != np) continue;
+        RenderGrid& g = r.rg[r.n_render++];
+        g = a.rg[k];
+        g.first_block = r.total_blocks;
+        r.total_blocks += g.ntx * g.nty * g.ntz;
+    }
+    return r;
+}
+
+bool any_masked(const RenderArgs& a)
+{
+    bool masked = false;
+    for (int k = 0; k < a.n_render; ++k) masked = masked || a.rg[k].masked;
+    return masked;
+}
+
+template <int NW>
+void launch_render_t(const RenderArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)a.total_blocks), block(64 * NW);
+    if (any_masked(a))
+        hipLaunchKernelGGL(k_render_block<NW>, grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL(k_render<NW>, grid, block, 0, s, a);
+}
+
+template <int KT, int DEPTH, bool MASK, int TW>
+void launch_field_mt(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
 {
     // every block resident at once, a multiple of 8 (one share per XCD), capped by the tiles
     int dev = 0, cus = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_render_field<KT, DEPTH, MASK>,
-                                                       64 * FW, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, k_render_field<KT, DEPTH, MASK, TW>, 64 * FW, 0);
     int64_t full = (int64_t)(cus > 0 ? cus : 256) * (per_cu > 0 ? per_cu : 1);
-    int64_t need = ((int64_t)a.total_blocks + FW - 1) / FW;
+    int64_t need = ((int64_t)a.total_blocks * TW + FW - 1) / FW;
     int64_t nb = need < full ? need : full;
     nb = (nb + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_render_field<KT, DEPTH, MASK>), dim3((unsigned)nb), dim3(64 * FW), 0, s,
-                       a, f);
+    hipLaunchKernelGGL((k_render_field<KT, DEPTH, MASK, TW>), dim3((unsigned)nb), dim3(64 * FW), 0,
+                       s, a, f);
 }
 
 template <int KT, int DEPTH>
-static void launch_field_t(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
+void launch_field_t(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
 {
-    bool masked = false;
-    for (int k = 0; k < a.n_render; ++k) masked = masked || a.rg[k].masked;
-    if (masked)
-        launch_field_mt<KT, DEPTH, true>(a, f, s);
-    else
-        launch_field_mt<KT, DEPTH, false>(a, f, s);
+    if (any_masked(a)) {
+        if ((1 << a.parts_log2) >= FW)
+            launch_field_mt<KT, DEPTH, true, FW>(a, f, s);
+        else
+            launch_field_mt<KT, DEPTH, true, 1>(a, f, s);
+    } else {
+        if ((1 << a.parts_log2) >= FW)
+            launch_field_mt<KT, DEPTH, false, FW>(a, f, s);
+        else
+            launch_field_mt<KT, DEPTH, false, 1>(a, f, s);
+    }
 }
 
-hipError_t launch_render_field(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
+hipError_t launch_field(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
 {
-    if (a.total_blocks == 0) return hipSuccess;
     switch ((f.in_pad >> 4) * 8 + f.depth) {
     case 4 * 8 + 1: launch_field_t<4, 1>(a, f, s); break;
     case 4 * 8 + 2: launch_field_t<4, 2>(a, f, s); break;
@@ -609,8 +749,43 @@ hipError_t launch_render_field(const RenderArgs& a, const NrfArgs& f, hipStream_
     case 8 * 8 + 4: launch_field_t<8, 4>(a, f, s); break;
     default: return hipErrorInvalidValue;
     }
+    return hipSuccess;
+}
+
+// f: with the residual field (NULL: without)
+hipError_t launch_all(const RenderArgs& a, const NrfArgs* f, hipStream_t s)
+{
+    if (a.total_blocks == 0) return hipSuccess;
+    int32_t part0 = 0;
+    for (int np = 2; np <= 16; np *= 2) {
+        RenderArgs r = with_parts(a, np);
+        if (r.total_blocks == 0) continue;
+        r.part0 = part0;
+        part0 += r.total_blocks;
+        if (f) {
+            const hipError_t e = launch_field(r, *f, s);
+            if (e != hipSuccess) return e;
+        } else if (np == 2) {
+            launch_render_t<2>(r, s);
+        } else if (np == 4) {
+            launch_render_t<4>(r, s);
+        } else if (np == 8) {
+            launch_render_t<8>(r, s);
+        } else {
+            launch_render_t<16>(r, s);
+        }
+    }
     if (a.loss_part)
         hipLaunchKernelGGL(k_render_loss_finish, dim3(1), dim3(FIN_THREADS), 0, s, a.loss_part,
                            a.total_blocks, a.inv_n, a.loss);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_render(const RenderArgs& a, hipStream_t s) { return launch_all(a, nullptr, s); }
+
+hipError_t launch_render_field(const RenderArgs& a, const NrfArgs& f, hipStream_t s)
+{
+    return launch_all(a, &f, s);
 }
