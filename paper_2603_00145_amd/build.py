@@ -25,7 +25,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgm.so")
 
 SOURCES = ["gm_api.hip", "preprocess.hip", "binning.hip", "render.hip", "backward.hip",
-           "optim.hip", "init.hip", "nrf.hip", "nrf_fwd.hip", "warm.hip", "ssim.hip"]
+           "optim.hip", "init.hip", "nrf.hip", "nrf_fwd.hip", "warm.hip", "warm_fwd.hip",
+           "ssim.hip"]
 NO_CONTRACT = {"preprocess.hip"}
 # MFMA results in ordinary VGPRs rather than AGPRs: the field's forward reads every accumulator
 # back for the activation, which AGPRs would cost one v_accvgpr_read each (the field's chain

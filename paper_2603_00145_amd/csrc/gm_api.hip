@@ -1415,8 +1415,6 @@ gm_status gm_ws_forward(const gm_ws_net* net, const uint16_t* patches, int64_t n
     REQ_PTR(logit_out, "logit_out");
     char* base = reinterpret_cast<char*>(workspace);
     WsActs w = ws_acts(base, L);
-    // inference: only the last layer's pre-activation (read by the head) is stored
-    for (int l = 0; l < 3; ++l) w.z[l] = nullptr;
     WsHeadArgs h;
     memset(&h, 0, sizeof h);
     h.n = n;
@@ -1428,8 +1426,9 @@ gm_status gm_ws_forward(const gm_ws_net* net, const uint16_t* patches, int64_t n
     h.s_out = log_scale_out;
     h.q_out = quat_out;
     h.logit_out = logit_out;
-    GM_HIP(launch_ws_forward(ws_net(net), patches, n, w, h, reinterpret_cast<hipStream_t>(stream)),
-           "ws forward");
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    GM_HIP(launch_ws_infer(ws_net(net), patches, n, w.a[1], w.z[3], s), "ws forward");
+    GM_HIP(launch_ws_head(h, s), "ws head");
     return GM_OK;
 }
 

@@ -386,6 +386,10 @@ size_t ws_part_floats(int64_t B);
 hipError_t launch_ws_gather(const WsGatherArgs& a, hipStream_t s);
 hipError_t launch_ws_targets(const float* ls, const float* quat, int64_t n, float* sig6,
                              hipStream_t s);
+// inference: the layers' pre-activation z4 [B][32] (a2: [B][64][32] BF16 between the kernels)
+hipError_t launch_ws_infer(const WsNet& net, const uint16_t* X0, int64_t B, uint16_t* a2, float* z4,
+                           hipStream_t s);
+hipError_t launch_ws_head(const WsHeadArgs& head, hipStream_t s);
 hipError_t launch_ws_forward(const WsNet& net, const uint16_t* X0, int64_t B, const WsActs& w,
                              const WsHeadArgs& head, hipStream_t s);
 hipError_t launch_ws_backward(const WsNet& net, const uint16_t* X0, int64_t B, const WsActs& w,
