@@ -278,28 +278,25 @@ NrfLayout nrf_layout(const gm_nrf* n, int64_t npts)
     return L;
 }
 
-struct WsLayout {
-    size_t bytes, off_z[4], off_a[4], off_dz[4], off_part, off_loss, off_dout, off_a4;
-};
-
-WsLayout ws_layout(int64_t B)
+// workspace of a warm-start batch; with base NULL only the size
+WsWork ws_work(char* base, int64_t B, size_t* bytes)
 {
-    static const int PO[4] = {512, 64, 8, 1};
-    WsLayout L;
-    memset(&L, 0, sizeof L);
+    WsWork w;
     size_t o = 0;
-    auto take = [&](size_t b) { const size_t r = o; o += align256(b); return r; };
-    for (int l = 0; l < 4; ++l) {
-        L.off_z[l] = take((size_t)B * 32 * PO[l] * 4);
-        L.off_a[l] = take((size_t)B * 32 * PO[l] * 2);
-        L.off_dz[l] = take((size_t)B * 32 * PO[l] * 2);
-    }
-    L.off_part = take(ws_part_floats(B) * 4);
-    L.off_loss = take((size_t)B * 4);
-    L.off_dout = take((size_t)B * 8 * 4);
-    L.off_a4 = take((size_t)B * 32 * 4);
-    L.bytes = o;
-    return L;
+    auto take = [&](size_t b) { char* p = base ? base + o : nullptr; o += align256(b); return p; };
+    auto floats = [&](size_t n) { return reinterpret_cast<float*>(take(n * 4)); };
+    auto halves = [&](size_t n) { return reinterpret_cast<uint16_t*>(take(n * 2)); };
+    const size_t n = (size_t)B;
+    w.a2 = halves(n * 64 * 32);
+    w.z4 = floats(n * 32);
+    w.z2 = floats(n * 64 * 32);
+    w.dz2 = halves(n * 64 * 32);
+    w.wt = halves(ws_wt_elems());
+    w.part34 = floats(ws_part_floats(B));
+    w.part12 = w.part34 ? ws_part12(w.part34, B) : nullptr;
+    w.loss_part = reinterpret_cast<double*>(take(ws_loss_parts(B) * 8));
+    *bytes = o;
+    return w;
 }
 
 gm_status check_ws_net(const gm_ws_net* n)
@@ -322,18 +319,6 @@ WsNet ws_net(const gm_ws_net* n)
     }
     w.wl = n->wl;
     w.bl = n->bl;
-    return w;
-}
-
-WsActs ws_acts(char* base, const WsLayout& L)
-{
-    WsActs w;
-    for (int l = 0; l < 4; ++l) {
-        w.z[l] = reinterpret_cast<float*>(base + L.off_z[l]);
-        w.a[l] = reinterpret_cast<uint16_t*>(base + L.off_a[l]);
-        w.dz[l] = reinterpret_cast<uint16_t*>(base + L.off_dz[l]);
-    }
-    w.part = reinterpret_cast<float*>(base + L.off_part);
     return w;
 }
 
@@ -1380,13 +1365,13 @@ gm_status gm_ws_workspace(int64_t n, size_t* bytes)
     g_err.clear();
     if (n < 0 || n % 16 != 0 || !bytes)
         return fail(GM_ERR_INVALID_ARGUMENT, "n must be a non-negative multiple of 16");
-    *bytes = ws_layout(n).bytes;
+    (void)ws_work(nullptr, n, bytes);
     return GM_OK;
 }
 
 static gm_status ws_common(const gm_ws_net* net, const uint16_t* patches, int64_t n,
                            const float* s0, const float* logit0, void* ws, size_t ws_bytes,
-                           WsLayout* L)
+                           WsWork* w)
 {
     gm_status st = check_ws_net(net);
     if (st != GM_OK) return st;
@@ -1395,9 +1380,10 @@ static gm_status ws_common(const gm_ws_net* net, const uint16_t* patches, int64_
     REQ_PTR(s0, "s0");
     REQ_PTR(logit0, "logit0");
     REQ_PTR(ws, "workspace");
-    *L = ws_layout(n);
-    if (ws_bytes < L->bytes)
-        return fail(GM_ERR_INVALID_ARGUMENT, "workspace %zu bytes < required %zu", ws_bytes, L->bytes);
+    size_t need = 0;
+    *w = ws_work(reinterpret_cast<char*>(ws), n, &need);
+    if (ws_bytes < need)
+        return fail(GM_ERR_INVALID_ARGUMENT, "workspace %zu bytes < required %zu", ws_bytes, need);
     return GM_OK;
 }
 
@@ -1407,18 +1393,16 @@ gm_status gm_ws_forward(const gm_ws_net* net, const uint16_t* patches, int64_t n
                         size_t workspace_bytes, gm_stream stream)
 {
     g_err.clear();
-    WsLayout L;
-    gm_status st = ws_common(net, patches, n, s0, logit0, workspace, workspace_bytes, &L);
+    WsWork w;
+    gm_status st = ws_common(net, patches, n, s0, logit0, workspace, workspace_bytes, &w);
     if (st != GM_OK) return st;
     REQ_PTR(log_scale_out, "log_scale_out");
     REQ_PTR(quat_out, "quat_out");
     REQ_PTR(logit_out, "logit_out");
-    char* base = reinterpret_cast<char*>(workspace);
-    WsActs w = ws_acts(base, L);
     WsHeadArgs h;
     memset(&h, 0, sizeof h);
     h.n = n;
-    h.z4 = w.z[3];
+    h.z4 = w.z4;
     h.wl = net->wl;
     h.bl = net->bl;
     h.s0 = s0;
@@ -1427,7 +1411,7 @@ gm_status gm_ws_forward(const gm_ws_net* net, const uint16_t* patches, int64_t n
     h.q_out = quat_out;
     h.logit_out = logit_out;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    GM_HIP(launch_ws_infer(ws_net(net), patches, n, w.a[1], w.z[3], s), "ws forward");
+    GM_HIP(launch_ws_infer(ws_net(net), patches, n, w, s), "ws forward");
     GM_HIP(launch_ws_head(h, s), "ws head");
     return GM_OK;
 }
@@ -1438,8 +1422,8 @@ gm_status gm_ws_backward(const gm_ws_net* net, const uint16_t* patches, int64_t 
                          void* workspace, size_t workspace_bytes, gm_stream stream)
 {
     g_err.clear();
-    WsLayout L;
-    gm_status st = ws_common(net, patches, n, s0, logit0, workspace, workspace_bytes, &L);
+    WsWork w;
+    gm_status st = ws_common(net, patches, n, s0, logit0, workspace, workspace_bytes, &w);
     if (st != GM_OK) return st;
     REQ_PTR(sigma_target, "sigma_target");
     REQ_PTR(logit_target, "logit_target");
@@ -1456,25 +1440,17 @@ gm_status gm_ws_backward(const gm_ws_net* net, const uint16_t* patches, int64_t 
     REQ_PTR(grads->bl, "grads->bl");
     g.wl = grads->wl;
     g.bl = grads->bl;
-    char* base = reinterpret_cast<char*>(workspace);
-    WsActs w = ws_acts(base, L);
     WsHeadArgs h;
     memset(&h, 0, sizeof h);
     h.n = n;
-    h.z4 = w.z[3];
     h.wl = net->wl;
     h.bl = net->bl;
     h.s0 = s0;
     h.logit0 = logit0;
     h.sig_t = sigma_target;
     h.logit_t = logit_target;
-    h.loss_each = reinterpret_cast<float*>(base + L.off_loss);
-    h.dout = reinterpret_cast<float*>(base + L.off_dout);
-    h.a4 = reinterpret_cast<float*>(base + L.off_a4);
-    h.dz4 = w.dz[3];
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    GM_HIP(launch_ws_forward(ws_net(net), patches, n, w, h, s), "ws forward");
-    GM_HIP(launch_ws_backward(ws_net(net), patches, n, w, h, g, loss, s), "ws backward");
+    GM_HIP(launch_ws_train(ws_net(net), patches, n, w, h, g, loss,
+                           reinterpret_cast<hipStream_t>(stream)), "ws backward");
     return GM_OK;
 }
 

@@ -352,11 +352,16 @@ struct WsNet {
     const float* wl;
     const float* bl;
 };
-struct WsActs {
-    float* z[4];
-    uint16_t* a[4];
-    uint16_t* dz[4];
-    float* part;
+// Buffers of a batch of B samples: inference uses a2 and z4, a training step all but z4
+struct WsWork {
+    uint16_t* a2;            // [B][64][32] BF16 activations of layer 2
+    float* z4;               // [B][32] pre-activations of layer 4
+    float* z2;               // [B][64][32] pre-activations of layer 2
+    uint16_t* dz2;           // [B][32][64] BF16 gradients through them
+    uint16_t* wt;            // layers 2 and 3's weights, laid out for the backward
+    float* part34;           // per-block sums of the weight gradients
+    float* part12;
+    double* loss_part;
 };
 struct WsHeadArgs {
     int64_t n;
@@ -370,10 +375,6 @@ struct WsHeadArgs {
     float* logit_out;
     const float* sig_t;      // NULL: inference only
     const float* logit_t;
-    float* loss_each;
-    float* dout;
-    float* a4;
-    uint16_t* dz4;
 };
 struct WsGrads {
     float* w[4];
@@ -381,19 +382,21 @@ struct WsGrads {
     float* wl;
     float* bl;
 };
-int ws_kpad(int layer);
+// sizes of WsWork's part34 and part12 together, loss_part and wt
 size_t ws_part_floats(int64_t B);
+size_t ws_loss_parts(int64_t B);
+size_t ws_wt_elems();
+float* ws_part12(float* part34, int64_t B);   // part12's place after part34
 hipError_t launch_ws_gather(const WsGatherArgs& a, hipStream_t s);
 hipError_t launch_ws_targets(const float* ls, const float* quat, int64_t n, float* sig6,
                              hipStream_t s);
-// inference: the layers' pre-activation z4 [B][32] (a2: [B][64][32] BF16 between the kernels)
-hipError_t launch_ws_infer(const WsNet& net, const uint16_t* X0, int64_t B, uint16_t* a2, float* z4,
+// inference: z4 of B samples, then the head
+hipError_t launch_ws_infer(const WsNet& net, const uint16_t* X0, int64_t B, const WsWork& w,
                            hipStream_t s);
 hipError_t launch_ws_head(const WsHeadArgs& head, hipStream_t s);
-hipError_t launch_ws_forward(const WsNet& net, const uint16_t* X0, int64_t B, const WsActs& w,
-                             const WsHeadArgs& head, hipStream_t s);
-hipError_t launch_ws_backward(const WsNet& net, const uint16_t* X0, int64_t B, const WsActs& w,
-                              const WsHeadArgs& head, const WsGrads& g, float* loss, hipStream_t s);
+// a training step's loss and weight gradients (B a multiple of 4)
+hipError_t launch_ws_train(const WsNet& net, const uint16_t* X0, int64_t B, const WsWork& w,
+                           const WsHeadArgs& head, const WsGrads& g, float* loss, hipStream_t s);
 
 // ---- device helpers ---------------------------------------------------------------------
 #ifdef __HIPCC__

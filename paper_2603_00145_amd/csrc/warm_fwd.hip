@@ -1,4 +1,4 @@
-// K12 inference: the warm-start network's forward in two kernels whose activations stay on chip
+// K12 inference: the warm-start network's convolutions in two kernels whose activations stay on chip
 // (see warm.hip for the layers).  k_ws_conv12 takes a sample's patch through the first two
 // convolutions, the 8^3 x 32 activations between them in LDS; k_ws_conv34 takes 16 samples
 // through the last two.  Only the 4^3 x 32 activations (4 KB a sample) go through memory.
@@ -20,32 +20,12 @@
 // 3%; enforcing that interleaving instruction by instruction: slower.)  k_ws_conv34 takes 2.3 ms
 // for them, bound by the latency of its input reads.  A kernel per layer with the operands
 // gathered element by element took 80 ms.
-#include "nrf_core.h"
+#include "warm_core.h"
 
 namespace {
 
-using nrfcore::mfma2;
-using nrfcore::pack4;
-using nrfcore::silu;
-using nrfcore::v4f;
-using nrfcore::v4s;
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef short v8s __attribute__((ext_vector_type(8)));
+using namespace warmcore;
 
-__device__ __forceinline__ int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ v4f mfma8(v8s a, v8s b, v4f c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a),
-                                                   __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-}
-__device__ __forceinline__ v4s silu4(v4f z) { return pack4(silu(z.x), silu(z.y), silu(z.z), silu(z.w)); }
-
-constexpr int CO = 32, KP1 = 96, KP2 = 864, KP4 = 256;   // channels, padded K of the weights
-
-// The patch in LDS: two copies of [channel][z + 1][y + 1] rows of 12 BF16 (6 words), x from -1 in
-// the first, from 0 in the second; the copies 12 (mod 32) words apart so that the rows two
-// lane groups read sit in different banks.
-constexpr int IN_ROW = 6, IN_Z = 10 * IN_ROW, IN_C = 10 * IN_Z, IN_COPY = 3 * IN_C + 4;
 // The first layer's activations: position (z, y, x), x, y, z >= -1, at 40 elements (80 bytes) per
 // x with even and odd x apart (a stride-2 read then walks neighbouring slots); rows of 46 16-byte
 // slots.  The 8 positions (4 x, 2 y) that share a read cycle fall in 8 different 16-byte slots of
@@ -70,22 +50,8 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv12(const uint16_t* __restrict
 {
     __shared__ Lds12 s;
     const int lane = threadIdx.x & 63, w = sgpr(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
-    // the first layer's weights, both channel tiles: K group q = (channel, kz, ky) of 8 st + 4 h + g
-    v4s w1[2][4][2];
-    int off1[4][2];        // the group's row in the patch
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int q = 8 * st + 4 * h + g, qq = q < 27 ? q : 0;
-            off1[st][h] = (qq / 9) * IN_C + (qq / 3 % 3) * IN_Z + (qq % 3) * IN_ROW;
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const uint16_t* src = W1 + (16 * m + col) * KP1 + 3 * qq;
-                w1[m][st][h] = q < 27 ? v4s{(short)src[0], (short)src[1], (short)src[2], 0}
-                                      : v4s{0, 0, 0, 0};
-            }
-        }
+    Layer1 l1;
+    l1.load(W1, lane);
     // the second layer's weights of channel tile w & 1, tap by tap, through LDS
     const int m2 = 16 * (w & 1), n2 = (w >> 1) * 2;      // ... for output planes n2, n2 + 1
     for (int i = threadIdx.x; i < CO * KP2 / 4; i += 256)     // (weights are 8-byte aligned)
@@ -110,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv12(const uint16_t* __restrict
     // thread t < 192 stages row t of the patch (channel, z, y): 8 values
     const int sr = threadIdx.x;
     const bool stager = sr < 192;
-    const int srow = (sr >> 6) * IN_C + ((sr >> 3 & 7) + 1) * IN_Z + ((sr & 7) + 1) * IN_ROW;
+    const int srow = patch_row(sr);
     uint4 nx = make_uint4(0u, 0u, 0u, 0u);
     if (stager && blockIdx.x < B) nx = reinterpret_cast<const uint4*>(X + (int64_t)blockIdx.x * 1536)[sr];
     // the lane's position within a column tile of the first layer (x, and y of two) and of the
@@ -122,19 +88,7 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv12(const uint16_t* __restrict
 #pragma unroll 1
     for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
         // every wavefront has read the last sample's patch (the barrier after the first layer)
-        if (stager) {
-            uint32_t* r0 = s.in + srow;
-            uint32_t* r1 = r0 + IN_COPY;
-            r0[0] = nx.x << 16;
-            r0[1] = (nx.x >> 16) | (nx.y << 16);
-            r0[2] = (nx.y >> 16) | (nx.z << 16);
-            r0[3] = (nx.z >> 16) | (nx.w << 16);
-            r0[4] = nx.w >> 16;
-            r1[0] = nx.x;
-            r1[1] = nx.y;
-            r1[2] = nx.z;
-            r1[3] = nx.w;
-        }
+        if (stager) stage_patch_row(s.in, srow, nx);
         __syncthreads();    // ... and every wavefront is done with the last sample's activations
         if (stager && b + gridDim.x < B)
             nx = reinterpret_cast<const uint4*>(X + (b + gridDim.x) * 1536)[sr];
@@ -148,13 +102,9 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv12(const uint16_t* __restrict
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 v4s bv[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t* r = src + off1[st][h];
-                    bv[h] = __builtin_bit_cast(v4s, make_uint2(r[0], r[1]));
-                }
-                d0 = mfma2(w1[0][st][0], w1[0][st][1], bv[0], bv[1], d0);
-                d1 = mfma2(w1[1][st][0], w1[1][st][1], bv[0], bv[1], d1);
+                l1.patch(src, st, bv);
+                d0 = mfma2(l1.w[0][st][0], l1.w[0][st][1], bv[0], bv[1], d0);
+                d1 = mfma2(l1.w[1][st][0], l1.w[1][st][1], bv[0], bv[1], d1);
             }
         };
         conv1(0, c0, c1);
@@ -275,15 +225,15 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv34(const uint16_t* __restrict
 
 }  // namespace
 
-hipError_t launch_ws_infer(const WsNet& net, const uint16_t* X0, int64_t B, uint16_t* a2, float* z4,
+hipError_t launch_ws_infer(const WsNet& net, const uint16_t* X0, int64_t B, const WsWork& w,
                            hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
     // two resident blocks per CU, each walking its share of the samples
     const int64_t n12 = B < 512 ? B : 512, n34 = B / 16 < 512 ? B / 16 : 512;
     hipLaunchKernelGGL(k_ws_conv12, dim3((unsigned)n12), dim3(256), 0, s, net.w[0], net.b[0],
-                       net.w[1], net.b[1], X0, B, a2);
+                       net.w[1], net.b[1], X0, B, w.a2);
     hipLaunchKernelGGL(k_ws_conv34, dim3((unsigned)n34), dim3(256), 0, s, net.w[2], net.b[2],
-                       net.w[3], net.b[3], a2, B, z4);
+                       net.w[3], net.b[3], w.a2, B, w.z4);
     return hipGetLastError();
 }

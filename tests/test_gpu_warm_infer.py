@@ -37,3 +37,40 @@ def test_inference_matches_oracle(n):
         err = np.max(np.abs((a - b0) - (r - b0))) / np.max(np.abs(r - b0))
         assert err < TOL, err
     assert all(torch.equal(a, b) for a, b in zip(got, net.forward(Xb, s0, l0)))
+
+
+@pytest.mark.parametrize("n", [16, 1040])
+def test_gradients_match_oracle(n):
+    """One quad of samples per block (four blocks), and more quads than blocks; gradients add to
+    what the buffers hold."""
+    rng = np.random.default_rng(n)
+    net = warmstart.WarmStartNet(seed=n % 5, zero_head=False)
+    X = torch.rand((n, 3, 512), device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    X[::5] = 0.0
+    Xb = X.to(torch.bfloat16).view(torch.int16)
+    s0, l0 = rng.normal(-3.5, 0.1, (n, 3)), rng.normal(0, 0.5, n)
+    q_t = rng.normal(size=(n, 4))
+    S = owarm.covariance(rng.normal(-3.5, 0.3, (n, 3)), q_t)
+    sig6 = np.stack([S[:, 0, 0], S[:, 1, 1], S[:, 2, 2], S[:, 0, 1], S[:, 0, 2], S[:, 1, 2]], 1)
+    lt = rng.normal(size=n)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+    a = tuple(T(v) for v in (s0, l0, sig6, lt))
+    loss = net.backward(Xb, *a)
+    once = {k: v.clone() for k, v in net.g.items()}
+    loss2 = net.backward(Xb, *a)
+    assert float(loss) == float(loss2)
+    assert all(torch.equal(net.g[k], once[k] * 2) for k in once)
+    W = net.weights_host()
+    out, _, _ = owarm.forward(W, X.to(torch.bfloat16).double().cpu().numpy().reshape(n, 3, 8, 8, 8))
+    f32 = lambda v: np.asarray(v, np.float32).astype(np.float64)
+    L, dout = owarm.loss_grad(out, f32(s0), f32(l0), S, f32(lt))
+    assert float(loss) == pytest.approx(L, rel=TOL)
+    ref = owarm.backward(W, X.to(torch.bfloat16).double().cpu().numpy().reshape(n, 3, 8, 8, 8), dout)
+    got = {f"W{l + 1}": once[f"w{l}"].cpu().numpy()[:, :k] for l, k in enumerate(warmstart.KREAL)}
+    got |= {f"b{l + 1}": once[f"b{l}"].cpu().numpy() for l in range(4)}
+    got |= {"Wl": once["wl"].cpu().numpy(), "bl": once["bl"].cpu().numpy()}
+    for k, v in got.items():
+        r = np.asarray(ref[k]).reshape(v.shape)
+        err = np.max(np.abs(v - r)) / np.max(np.abs(r))
+        assert err < 2e-2, (k, err)      # as for every BF16 gradient of the network
+    assert not bool(once["w0"][:, warmstart.KREAL[0]:].any())      # padded columns stay untouched
