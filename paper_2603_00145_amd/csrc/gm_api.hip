@@ -1190,7 +1190,8 @@ gm_status gm_loss_ssim(int32_t n_stacks, const float* const* preds, const float*
     SsimArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.n_stacks = n_stacks;
-    int64_t tiles = 0, vox = 0;
+    int64_t vox = 0;
+    int32_t slices[GM_MAX_GRIDS];
     for (int k = 0; k < n_stacks; ++k) {
         const int32_t nx = dims[3 * k], ny = dims[3 * k + 1], nz = dims[3 * k + 2];
         if (nx < 0 || ny < 0 || nz < 0) return fail(GM_ERR_INVALID_ARGUMENT, "negative dims");
@@ -1202,15 +1203,12 @@ gm_status gm_loss_ssim(int32_t n_stacks, const float* const* preds, const float*
         }
         sa.nx[k] = nx;
         sa.ny[k] = ny;
-        ssim_tiles(nx, ny, &sa.tiles_x[k], &sa.tiles_y[k]);
-        sa.tile_begin[k] = tiles;
-        if (n > 0) tiles += (int64_t)nz * sa.tiles_x[k] * sa.tiles_y[k];
+        slices[k] = n > 0 ? nz : 0;
         sa.pred[k] = preds[k];
         sa.target[k] = targets[k];
         sa.dl[k] = dl_di[k];
         vox += n;
     }
-    sa.tile_begin[n_stacks] = tiles;
     // 1D Gaussian taps, sigma 1.5, normalised
     double gs = 0.0;
     for (int i = 0; i < 11; ++i) {
@@ -1220,7 +1218,7 @@ gm_status gm_loss_ssim(int32_t n_stacks, const float* const* preds, const float*
     }
     for (int i = 0; i < 11; ++i) sa.g[i] /= gs;
     sa.grad_scale = vox > 0 ? -(double)lambda / (double)vox : 0.0;
-    GM_HIP(launch_ssim(sa, vox, loss, workspace, reinterpret_cast<hipStream_t>(stream)), "SSIM");
+    GM_HIP(launch_ssim(sa, slices, vox, loss, workspace, reinterpret_cast<hipStream_t>(stream)), "SSIM");
     return GM_OK;
 }
 
