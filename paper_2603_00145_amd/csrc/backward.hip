@@ -1,46 +1,53 @@
 // K7 + K8: gradients of L = sum_k sum_v dL/dI_k[v] I_k[v] (+ lambda_aniso * L_aniso,
 // Eq. 12-13) with respect to every Gaussian parameter, boxes held fixed.
 //
-// K7 (grid-frame partials): eight lanes per Gaussian gather g = dL/dI over the voxels of the
-// Gaussian's box on each listed grid, recomputing E = 2^Q (no per-voxel contributions are
+// K7 (grid-frame partials): a group of lanes per Gaussian gathers g = dL/dI over the voxels of
+// the Gaussian's box on each listed grid, recomputing E = 2^Q (no per-voxel contributions are
 // stored).  With delta = v - c, Q = delta^T K delta (K the record's base-2 conic as a
 // symmetric matrix) and w = amp E, the ten grid-frame partials are
 //     d amp = sum g E,   d c = -2 amp ln2 K m,   d K_ab = amp ln2 m_ab
 // with the weighted moments m = sum g E delta and m_ab = sum g E delta_a delta_b.  A lane
-// owns one (x, z) column of the box at a time and walks it along y, summing g E, g E dy and
-// g E dy^2; the column's share of the ten moments follows from those three sums and its
-// (dx, dz).  The moments are reduced across the eight lanes with DPP and turned into the
-// partials once per (grid, Gaussian).  No global atomics are needed.  With the paper's block
-// query on a rotated grid (k_partials<true>) every Gaussian of that grid takes the global-memory
-// path and each voxel of its box is also tested against its cell block (Eqs. 4-6): the sums
-// run over the voxels that pass.
+// walks columns of the box along y, summing g E, g E dy and g E dy^2; the column's share of the
+// ten moments follows from those three sums and its (dx, dz).  The moments are reduced across
+// the group with DPP and turned into the partials once per (grid, Gaussian).  No global atomics
+// are needed.  With the paper's block query on a rotated grid (k_partials<true>) every Gaussian of
+// that grid takes the global-memory path and each voxel of its box is also tested against its
+// cell block (Eqs. 4-6): the sums run over the voxels that pass.
 //
 // K8 (chain rule, FP64): thread per Gaussian.  The partials of every grid are pulled back
 // through c = L mu + t, C = Sigma_g^-1, amp = alpha sqrt(det Sigma_idx / det Sigma_g),
 // Sigma_idx = L Sigma L^T, Sigma = R diag(e^{2s}) R^T (Eq. 3), R(q/|q|) and
 // alpha = sigmoid(logit), summed over grids, and added (+=) to the gradient buffers.
 #include "gm_internal.h"
+#include <type_traits>
 
 namespace {
 
 __device__ __forceinline__ int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Sum of v over each aligned group of G lanes (G = 8 or 16; every lane of the group ends with
-// it): DPP adds across lane xor 1, xor 2, the half-row mirror and, for 16, the row mirror.
+// Sum of v over each aligned group of G lanes (every lane of the group ends with it): DPP adds
+// across lane xor 1, xor 2, the half-row mirror and the row mirror, then the wavefront's rows.
 template <int G>
 __device__ __forceinline__ float group_sum(float v)
 {
-    static_assert(G == 8 || G == 16, "groups of 8 or 16 lanes");
+    static_assert(G == 4 || G == 8 || G == 64, "groups of 4, 8 or 64 lanes");
     int xi;
     xi = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false);  // xor 1
     v += __int_as_float(xi);
     xi = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false);  // xor 2
     v += __int_as_float(xi);
-    xi = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false); // half mirror
-    v += __int_as_float(xi);
-    if (G == 16) {
+    if (G > 4) {
+        xi = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false); // half mirror
+        v += __int_as_float(xi);
+    }
+    if (G == 64) {
         xi = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false); // mirror
         v += __int_as_float(xi);
+        const int b = __float_as_int(v);
+        v = (__int_as_float(__builtin_amdgcn_readlane(b, 0)) +
+             __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+            (__int_as_float(__builtin_amdgcn_readlane(b, 32)) +
+             __int_as_float(__builtin_amdgcn_readlane(b, 48)));
     }
     return v;
 }
@@ -69,58 +76,111 @@ __device__ __forceinline__ int group_min(int v)
 // row reads at one step sit in different LDS banks.
 constexpr int RX = GM_TX + 8, RY = GM_TY + 8, RZ = GM_TZ + 6;
 constexpr int RZS = RX * RY + 8;
-constexpr int BWD_G = 8;   // lanes per Gaussian in the backward
+// lanes per Gaussian in the rounds from LDS: setting a Gaussian up and reducing its moments costs
+// about as much as walking its box, and is shared by as many Gaussians as a wavefront holds; with
+// 2 lanes the rounds are too few and too uneven (256^3 workload: 399 us with 8 lanes, 378 with 4,
+// 416 with 2)
+constexpr int BWD_G = 4;
+constexpr int PER_ROUND = 64 / BWD_G;
 constexpr int WINB = 1024; // list entries a block sorts at a time
 constexpr int EPT = WINB / 256;  // ... per thread
-// sort keys of home entries: boxes inside the staged region by (column chunks, y length), both
-// capped, 8 x 16 keys; then one key for boxes reaching past the region
-constexpr int NKEY = 8 * 16 + 1;
+// longest column of lds_column: it reads that many rows whatever the box's length, so at most
+// NK_MAX - 8 rows past the last plane's end (masked where they are used)
+constexpr int NK_MAX = 12;
+constexpr int REGION = RZ * RZS + (NK_MAX - 8) * RX;
+// sort keys of home entries: boxes inside the staged region by (lane passes in x, z planes, y
+// length), each capped; then one key for boxes reaching past the region
+constexpr int KEY_X = 4, KEY_Z = 5, KEY_Y = 12;
+constexpr int NKEY = KEY_X * KEY_Z * KEY_Y + 1;
 static_assert(RZS % 32 == 8, "z-plane stride must be 8 mod 32 banks");
 
 // Column sums s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge (ge = g 2^Q_k) over the first NK
-// rows of a column whose rows are RX floats apart in the staged region.  Rows 0..7 of a home
-// box lie inside the region (the box starts in the tile, the region reaches 8 rows past it),
-// so all NK reads are issued at immediate offsets before the first use; rows past the column
-// (k >= ncol) are masked where they are used.  NK is the wavefront's longest column (up to 8),
-// a compile-time constant, so the steps carry no branches.
+// rows of a column whose rows are RX floats apart in the staged region, all NK reads issued at
+// immediate offsets before the first use; rows past the column (k >= ncol) are masked where they
+// are used.  NK is the wavefront's longest column (up to NK_MAX), a compile-time constant, so
+// the steps carry no branches.  (No contraction: a Gaussian's sums must not depend on the NK its
+// wavefront takes.)
 template <int NK, bool MASK>
 __device__ __forceinline__ void lds_column(const float* __restrict__ region, uint32_t off,
                                            int ncol, float A, float B, float kyy, float& s0,
                                            float& s1, float& s2)
 {
+#pragma clang fp contract(off)
     float gv[NK];
 #pragma unroll
     for (int k = 0; k < NK; ++k) gv[k] = region[off + k * RX];
+    s1 = s2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         const float Q = k == 0 ? A : fmaf((float)k, fmaf((float)k, kyy, B), A);
         // without MASK every active column of the wavefront is at least NK long
         const float gk = (k == 0 || !MASK) ? gv[k] : (k < ncol ? gv[k] : 0.0f);
         const float ge = gk * __builtin_amdgcn_exp2f(Q);
-        s0 += ge;
-        if (k > 0) {
+        s0 = k == 0 ? ge : s0 + ge;
+        if (k == 1) s1 = s2 = ge;
+        if (k > 1) {
             s1 = fmaf((float)k, ge, s1);
             s2 = fmaf((float)(k * k), ge, s2);
         }
     }
 }
 
-// 64/G Gaussians of one grid at a time, one per group of G lanes: the ten moments of each,
-// turned into the grid-frame partials and stored.  A group maps its lanes onto chunks of G
-// (x, z) columns of its Gaussian's box and walks each column along y (for thick-slice stacks the box
-// is longest in-plane, so this gives the fewest chunks and the longest walks).  With FROM_LDS
-// every box lies inside the block's staged region and dL/dI is read from LDS; otherwise from
-// global memory.  All of a column's values are read first; step k then costs
-// Q_k = A + k (B + k kyy) (two FMAs), one exp2, one multiply and three adds for the column sums
-// of g E, k g E and k^2 g E (k a compile-time constant in the unrolled loop).  Past a shorter
-// box, a row's reads are clamped and zeroed.
+// Sums over the planes of a lane's (y, z) sheet: S = sum gE, k (the row index) and dz moments.
+struct Sheet {
+    float s, k, kk, z, zz, kz;
+};
+
+// A lane's sheet of its Gaussian's box: planes 0 .. wz - 1 (none for an inactive lane), whose
+// first voxel is region[off].  max_wz, max_wy: the wavefront's.  Q along a plane's column is
+// A + k (B + k kyy) with A = Ab + dz (hz + kzz dz) and B = Bx + kyz dz.
+template <int NK, bool MASK>
+__device__ __forceinline__ void lds_sheet(const float* __restrict__ region, uint32_t off, int wz,
+                                          int max_wz, int ncol, int max_wy, float cz, float Ab,
+                                          float hz, float kzz, float Bx, float kyz, float kyy,
+                                          Sheet& S)
+{
+#pragma clang fp contract(off)
+    float zf = 0.0f;
+#pragma unroll 1
+    for (int z = 0; z < max_wz; ++z, zf += 1.0f, off += RZS) {
+        const float dz = zf - cz;
+        // a lane past its planes reads the region's first column and gets A = -inf, so its
+        // every term is exactly zero
+        const bool in = z < wz;
+        const uint32_t o = in ? off : 0u;
+        const float A = in ? fmaf(dz, fmaf(kzz, dz, hz), Ab) : -__builtin_inff();
+        const float B = fmaf(kyz, dz, Bx);
+        float s0, s1, s2;
+        lds_column<NK, MASK>(region, o, ncol, A, B, kyy, s0, s1, s2);
+        if (NK == NK_MAX) {
+#pragma unroll 1
+            for (int k = NK_MAX; k < max_wy; ++k) {
+                const float t = region[o + min(k, ncol - 1) * RX];
+                const float gk = k < ncol ? t : 0.0f;
+                const float fk = (float)k;
+                const float ge = gk * __builtin_amdgcn_exp2f(fmaf(fk, fmaf(fk, kyy, B), A));
+                s0 += ge;
+                s1 = fmaf(fk, ge, s1);
+                s2 = fmaf(fk * fk, ge, s2);
+            }
+        }
+        const float az = s0 * dz;
+        S.s += s0;
+        S.k += s1;
+        S.kk += s2;
+        S.z += az;
+        S.zz = fmaf(az, dz, S.zz);
+        S.kz = fmaf(s1, dz, S.kz);
+    }
+}
+
 // A Gaussian's 64-byte render record on one grid, as the group loads it (zeros when invalid).
 struct Rec {
     float4 r0, r1, r2, r3;
 };
 
 // (an invalid lane group passes mine = 0 and gets Gaussian 0's record: finite values whose
-// box group_of_gaussians never walks)
+// box is never walked)
 __device__ __forceinline__ Rec load_record(const BackwardArgs& a, int gi, uint32_t mine)
 {
     const int64_t gid = min((int64_t)(mine & GM_ID_MASK), a.n - 1);
@@ -133,21 +193,136 @@ __device__ __forceinline__ Rec load_record(const BackwardArgs& a, int gi, uint32
     return r;
 }
 
-template <int G, bool FROM_LDS, bool MASK = false>
-__device__ __forceinline__ void group_of_gaussians(const BackwardArgs& a, int kk, uint32_t mine,
-                                                   bool gvalid, const Rec& rec,
-                                                   const float* __restrict__ region,
-                                                   int t0x, int t0y, int t0z, bool mk = false)
+// Lane sums of the weighted moments m = sum gE, m_a = sum gE delta_a, m_ab = sum gE delta_a
+// delta_b over a lane's share of a box
+struct Moments {
+    float m, x, y, z, xx, yy, zz, xy, xz, yz;
+};
+
+// The moments added over each group of G lanes, turned into the ten grid-frame partials and
+// stored by the group's first lane.
+template <int G>
+__device__ __forceinline__ void store_partials(const BackwardArgs& a, int gi, uint32_t mine,
+                                               bool gvalid, const Rec& rec, Moments v)
 {
-    static_assert(!(MASK && FROM_LDS), "masked grids read dL/dI from global memory");
+    v.m = group_sum<G>(v.m);
+    v.x = group_sum<G>(v.x);
+    v.y = group_sum<G>(v.y);
+    v.z = group_sum<G>(v.z);
+    v.xx = group_sum<G>(v.xx);
+    v.yy = group_sum<G>(v.yy);
+    v.zz = group_sum<G>(v.zz);
+    v.xy = group_sum<G>(v.xy);
+    v.xz = group_sum<G>(v.xz);
+    v.yz = group_sum<G>(v.yz);
+    if ((threadIdx.x & (G - 1)) == 0 && gvalid) {
+        const int64_t gid = min((int64_t)(mine & GM_ID_MASK), a.n - 1);
+        // K as a full symmetric matrix has off-diagonal entries kxy/2, kxz/2, kyz/2
+        const float Al = rec.r0.w * GM_LN2F;   // amp ln2
+        const float hxy = 0.5f * rec.r1.w, hxz = 0.5f * rec.r2.x, hyz = 0.5f * rec.r2.y;
+        const float tx = rec.r1.x * v.x + hxy * v.y + hxz * v.z;
+        const float ty = hxy * v.x + rec.r1.y * v.y + hyz * v.z;
+        const float tz = hxz * v.x + hyz * v.y + rec.r1.z * v.z;
+        float2* o = reinterpret_cast<float2*>(a.grid_grads + ((size_t)gi * a.n + gid) * 10);
+        o[0] = make_float2(v.m, -2.0f * Al * tx);
+        o[1] = make_float2(-2.0f * Al * ty, -2.0f * Al * tz);
+        o[2] = make_float2(Al * v.xx, Al * v.yy);
+        o[3] = make_float2(Al * v.zz, Al * v.xy);
+        o[4] = make_float2(Al * v.xz, Al * v.yz);
+    }
+}
+
+// A round of Gaussians whose boxes lie inside the staged region, one per group of BWD_G lanes.
+// A lane takes every BWD_G-th x of its box and walks the (y, z) sheet there, plane by plane, so
+// everything that depends on x alone is formed once, a plane costs three FMAs to set up, and
+// the x moments follow from the sheet's sums at the end.  rb: the round's keys, from bit 0 a bit
+// per y length, then per plane count, then per number of x passes.
+__device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_t mine, bool gvalid,
+                                          const Rec& rec, const float* __restrict__ region,
+                                          int t0x, int t0y, int t0z, uint32_t rb)
+{
+    const int ql = threadIdx.x & (BWD_G - 1);
+    const float4 r0 = rec.r0, r1 = rec.r1, r2 = rec.r2, r3 = rec.r3;
+    const int lox = __float_as_int(r2.z), loy = __float_as_int(r2.w), loz = __float_as_int(r3.x);
+    const int wx = gvalid ? __float_as_int(r3.y) - lox + 1 : 0;
+    const int wy = __float_as_int(r3.z) - loy + 1, wz = __float_as_int(r3.w) - loz + 1;
+    const float cx = r0.x, cz = r0.z;
+    const float kxx = r1.x, kyy = r1.y, kzz = r1.z, kxy = r1.w;
+    const float kxz = r2.x, kyz = r2.y;
+    const int ncol = gvalid ? wy : 64;
+    int max_wy = 32 - __clz(rb & ((1 << KEY_Y) - 1));
+    const int min_wy = __ffs(rb & ((1 << KEY_Y) - 1));
+    int max_wz = 32 - __clz((rb >> KEY_Y) & ((1 << KEY_Z) - 1));
+    int max_wx = (32 - __clz(rb >> (KEY_Y + KEY_Z))) * BWD_G;
+    if (max_wy == KEY_Y) max_wy = group_max<BWD_G>(gvalid ? wy : 0);
+    if (max_wz == KEY_Z) max_wz = group_max<BWD_G>(gvalid ? wz : 0);
+    if (max_wx == KEY_X * BWD_G) max_wx = group_max<BWD_G>(wx);
+    const float dy0 = -r0.y;                      // dy = dy0 + k at step k of a column
+    const float g1 = dy0 * kxy, g2 = dy0 * kyz, A0 = kyy * dy0 * dy0, B0 = 2.0f * kyy * dy0;
+    const uint32_t base = (uint32_t)((loz - t0z) * RZS + (loy - t0y) * RX + (lox - t0x));
+    Moments v = {};
+    float k1 = 0.0f, k2 = 0.0f, k1x = 0.0f, k1z = 0.0f;
+    const int nk = min(max_wy, NK_MAX);
+    const bool whole = min_wy >= nk;
+#pragma unroll 1
+    for (int x = ql; x - ql < max_wx; x += BWD_G) {
+        const float dx = (float)x - cx;
+        const int nz = x < wx ? wz : 0;
+        const uint32_t off = base + x;
+        const float Ab = fmaf(dx, fmaf(kxx, dx, g1), A0);
+        const float hz = fmaf(kxz, dx, g2);
+        const float Bx = fmaf(kxy, dx, B0);
+        Sheet S = {};
+#define SHEET(K, M) \
+        lds_sheet<K, M>(region, off, nz, max_wz, ncol, max_wy, cz, Ab, hz, kzz, Bx, kyz, kyy, S)
+#define SHEETS(K) case K: if (whole) SHEET(K, false); else SHEET(K, true); break
+        switch (nk) {
+        SHEETS(1); SHEETS(2); SHEETS(3); SHEETS(4); SHEETS(5); SHEETS(6); SHEETS(7); SHEETS(8);
+        SHEETS(9); SHEETS(10); SHEETS(11);
+        default: SHEET(NK_MAX, true); break;
+        }
+#undef SHEETS
+#undef SHEET
+        const float ax = S.s * dx;
+        v.m += S.s;
+        v.x += ax;
+        v.xx = fmaf(ax, dx, v.xx);
+        v.z += S.z;
+        v.zz += S.zz;
+        v.xz = fmaf(S.z, dx, v.xz);
+        k1 += S.k;
+        k2 += S.kk;
+        k1x = fmaf(S.k, dx, k1x);
+        k1z += S.kz;
+    }
+    // from sums over the step index k to moments in dy = dy0 + k (dy0 is the Gaussian's):
+    // sum (dy0 + k) gE = k1 + dy0 m, sum (dy0 + k)^2 gE = k2 + dy0 (2 k1 + dy0 m), and the
+    // products with dx and dz likewise
+    v.y = fmaf(dy0, v.m, k1);
+    v.yy = fmaf(dy0, fmaf(2.0f, k1, dy0 * v.m), k2);
+    v.xy = fmaf(dy0, v.x, k1x);
+    v.yz = fmaf(dy0, v.z, k1z);
+    store_partials<BWD_G>(a, gi, mine, gvalid, rec, v);
+}
+
+// A round of Gaussians whose dL/dI is read from global memory: boxes reaching past the staged
+// region, the block query's wide ones, and masked grids.  A group maps its lanes onto chunks of
+// BWD_G (x, z) columns of its Gaussian's box and walks each column along y, eight rows' reads at
+// a time.  The walk is centred in y: Q = qxz + dy (by + kyy dy) with dy = dy0 + k, and the column
+// sums are in dy itself, so that a box much wider than its Gaussian (the block query) adds no
+// large terms that cancel.
+template <bool MASK, int G>
+__device__ __forceinline__ void global_round(const BackwardArgs& a, int kk, uint32_t mine,
+                                             bool gvalid, const Rec& rec, bool mk)
+{
+#pragma clang fp contract(off)
     const int ql = threadIdx.x & (G - 1);
-    const int gi = a.grid_index[kk];
     const int nx = a.nx[kk], ny = a.ny[kk];
     const float* __restrict__ g = a.dl_di[kk];
-    const int64_t gid = min((int64_t)(mine & GM_ID_MASK), a.n - 1);
     const float4 r0 = rec.r0, r1 = rec.r1, r2 = rec.r2, r3 = rec.r3;
     // masked grid: the Gaussian's cell and the grid's index -> world affine
-    const int4 cm = (MASK && mk) ? a.bq.cells[gid] : make_int4(0, 0, 0, 0);
+    const int4 cm = (MASK && mk) ? a.bq.cells[min((int64_t)(mine & GM_ID_MASK), a.n - 1)]
+                                 : make_int4(0, 0, 0, 0);
     const double* mw = a.m[kk];
     const int lox = __float_as_int(r2.z), loy = __float_as_int(r2.w), loz = __float_as_int(r3.x);
     const int hix = __float_as_int(r3.y), hiy = __float_as_int(r3.z), hiz = __float_as_int(r3.w);
@@ -157,12 +332,11 @@ __device__ __forceinline__ void group_of_gaussians(const BackwardArgs& a, int kk
     const int wx = nonempty ? hix - lox + 1 : 1;
     const int wy = nonempty ? hiy - loy + 1 : 0;
     const int wz = nonempty ? hiz - loz + 1 : 0;
-    const float cx = r0.x, cy = r0.y, cz = r0.z;
+    const float cx = r0.x, cz = r0.z;
     const float kxx = r1.x, kyy = r1.y, kzz = r1.z, kxy = r1.w;
     const float kxz = r2.x, kyz = r2.y;
     const int fp = wx * wz;                       // (x, z) footprint of the box
-    const int chunks = (fp + G - 1) / G;
-    const int max_chunks = group_max<G>(chunks);
+    const int max_chunks = group_max<G>((fp + G - 1) / G);
     const int max_wy = group_max<G>(wy);
     // y steps every active column of the wavefront takes (no mask needed below it)
     const int min_wy = group_min<G>(nonempty ? wy : 64);
@@ -171,22 +345,10 @@ __device__ __forceinline__ void group_of_gaussians(const BackwardArgs& a, int kk
     // reciprocal's error for any f < 2^20) and x + 1/2 = fh - z wx, exact in float
     const float wxf = (float)wx;
     const float inv_wx = __builtin_amdgcn_rcpf(wxf);
-    const float dy0 = -cy;                        // dy = dy0 + k at step k of a column
-    const float B0 = 2.0f * kyy * dy0;
-    // Q along a column at (dx, dz): A = qxz + dy0 (kxy dx + kyz dz + kyy dy0) regrouped as
-    // dx (kxx dx + kxz dz + dy0 kxy) + dz (kzz dz + dy0 kyz) + kyy dy0^2
-    const float g1 = dy0 * kxy, g2 = dy0 * kyz, A0 = kyy * dy0 * dy0;
+    const float dy0 = -r0.y;
     const float cxh = cx + 0.5f;
-    // staged-region index of the box's voxel (x, 0, z) minus 1/2, as a float: zf RZS + (x + 1/2)
-    // + obase, exact (the region holds fewer than 2^13 floats); in the grid, integer arithmetic
-    const int ystride = FROM_LDS ? RX : nx;       // between consecutive y steps
-    const float obase = (float)((loz - t0z) * RZS + (loy - t0y) * RX + (lox - t0x)) - 0.5f;
     const float qlh = (float)ql + 0.5f;
-    // weighted moments: m0 = sum gE, m1 = sum gE delta, m2 = sum gE delta delta^T
-    float m0 = 0.0f, mx = 0.0f, mz = 0.0f, mxx = 0.0f, mzz = 0.0f, mxz = 0.0f;
-    // ... and in the column step index k: k1 = sum k gE, k2 = sum k^2 gE, k1x = sum k gE dx,
-    // k1z = sum k gE dz
-    float k1 = 0.0f, k2 = 0.0f, k1x = 0.0f, k1z = 0.0f;
+    Moments v = {};
 #pragma unroll 1
     for (int c = 0; c < max_chunks; ++c) {
         const float fh = fmaf((float)c, (float)G, qlh);
@@ -194,166 +356,74 @@ __device__ __forceinline__ void group_of_gaussians(const BackwardArgs& a, int kk
         const float zf = floorf(fh * inv_wx);
         const float xh = fmaf(-zf, wxf, fh);
         const float dx = xh - cxh, dz = zf - cz;
-        // Q along the column: Q_k = A + k (B + k kyy).  A lane outside the footprint reads
-        // the first voxel of the region (or grid) at every step and gets A = -inf, so its
-        // every term is exactly zero.
-        const float Aq = fmaf(dx, fmaf(kxx, dx, fmaf(kxz, dz, g1)), fmaf(dz, fmaf(kzz, dz, g2), A0));
-        const float A = act ? Aq : -__builtin_inff();
-        const float B = fmaf(kxy, dx, fmaf(kyz, dz, B0));
-        // the global-memory path's centred form: Q = qxz + dy (by + kyy dy)
+        // a lane outside the footprint reads the grid's first column and gets Q = -inf, so
+        // its every term is exactly zero
         const float by = fmaf(kxy, dx, kyz * dz);
         const float qxz = act ? fmaf(dx, fmaf(kxx, dx, kxz * dz), kzz * dz * dz)
                               : -__builtin_inff();
-        uint32_t off = 0u;
-        if (act) {
-            off = FROM_LDS ? (uint32_t)fmaf(zf, (float)RZS, xh + obase)
-                           : (uint32_t)(((loz + (int)zf) * ny + loy) * nx + (lox + (int)xh));
-        }
+        const int vx = lox + (int)xh, vz = loz + (int)zf;
+        const uint32_t off = act ? (uint32_t)((vz * ny + loy) * nx + vx) : 0u;
         const int ncol = act ? wy : 1;             // steps whose voxel lies in the box
-        // s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge over the column (ge = g 2^Q)
         float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-        if (FROM_LDS) {
-            const int nk = max_wy < 8 ? max_wy : 8;
-            if (min_wy >= nk) {
-                switch (nk) {
-                case 1: lds_column<1, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 2: lds_column<2, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 3: lds_column<3, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 4: lds_column<4, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 5: lds_column<5, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 6: lds_column<6, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 7: lds_column<7, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                default: lds_column<8, false>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                }
-            } else {
-                switch (nk) {
-                case 1: lds_column<1, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 2: lds_column<2, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 3: lds_column<3, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 4: lds_column<4, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 5: lds_column<5, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 6: lds_column<6, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                case 7: lds_column<7, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                default: lds_column<8, true>(region, off, ncol, A, B, kyy, s0, s1, s2); break;
-                }
-            }
-        } else {
-            // masked grid: the column's voxel (vx, loy + k, vz)
-            const int vx = lox + (int)xh, vz = loz + (int)zf;
+#pragma unroll 1
+        for (int kb = 0; kb < max_wy; kb += 8) {
             float gv[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int j = 0; j < 8; ++j) {
+                const int k = kb + j;
                 if (k < max_wy) {
                     if (k < min_wy) {
-                        gv[k] = (g + (size_t)k * nx)[off];
+                        gv[j] = (g + (size_t)k * nx)[off];
                     } else {
                         const int kc = min(k, ncol - 1);
                         const float t = (g + (size_t)kc * nx)[off];
-                        gv[k] = k < ncol ? t : 0.0f;
+                        gv[j] = k < ncol ? t : 0.0f;
                     }
                 }
             }
             if (MASK && mk) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (k < max_wy &&
-                        !voxel_in_block(mw, a.bq.res, a.bq.radius, vx, loy + k, vz, cm))
-                        gv[k] = 0.0f;
+                for (int j = 0; j < 8; ++j)
+                    if (kb + j < max_wy &&
+                        !voxel_in_block(mw, a.bq.res, a.bq.radius, vx, loy + kb + j, vz, cm))
+                        gv[j] = 0.0f;
             }
-            // centred in y: Q = qxz + dy (by + kyy dy) with dy = dy0 + k, and the column sums
-            // in dy itself (s1 = sum dy gE, s2 = sum dy^2 gE), so that a box much wider than
-            // its Gaussian (the block query) adds no large terms that cancel
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (k < max_wy) {
-                    const float dy = dy0 + (float)k;
+            for (int j = 0; j < 8; ++j) {
+                if (kb + j < max_wy) {
+                    const float dy = dy0 + (float)(kb + j);
                     const float Q = fmaf(dy, fmaf(kyy, dy, by), qxz);
-                    const float ge = gv[k] * __builtin_amdgcn_exp2f(Q);
+                    const float ge = gv[j] * __builtin_amdgcn_exp2f(Q);
                     s0 += ge;
                     s1 = fmaf(dy, ge, s1);
                     s2 = fmaf(dy * dy, ge, s2);
                 }
             }
         }
-#pragma unroll 1
-        for (int k = 8; k < max_wy; ++k) {  // boxes longer than 8 voxels in y
-            const int kc = min(k, ncol - 1);
-            const float t = FROM_LDS ? region[off + kc * RX] : g[(size_t)kc * ystride + off];
-            float gk = k < ncol ? t : 0.0f;
-            if (MASK && mk &&
-                !voxel_in_block(mw, a.bq.res, a.bq.radius, lox + (int)xh, loy + k, loz + (int)zf,
-                                cm))
-                gk = 0.0f;
-            const float fk = (float)k;
-            if (FROM_LDS) {
-                const float ge = gk * __builtin_amdgcn_exp2f(A + fk * (B + fk * kyy));
-                s0 += ge;
-                s1 += fk * ge;
-                s2 += fk * fk * ge;
-            } else {
-                const float dy = dy0 + fk;
-                const float ge = gk * __builtin_amdgcn_exp2f(fmaf(dy, fmaf(kyy, dy, by), qxz));
-                s0 += ge;
-                s1 = fmaf(dy, ge, s1);
-                s2 = fmaf(dy * dy, ge, s2);
-            }
-        }
-        // the column's share in the step index k (moments in dy = dy0 + k follow below)
         const float ax = s0 * dx, az = s0 * dz;
-        m0 += s0;
-        mx += ax;
-        mz += az;
-        mxx = fmaf(ax, dx, mxx);
-        mzz = fmaf(az, dz, mzz);
-        mxz = fmaf(ax, dz, mxz);
-        k1 += s1;
-        k2 += s2;
-        k1x = fmaf(s1, dx, k1x);
-        k1z = fmaf(s1, dz, k1z);
+        v.m += s0;
+        v.x += ax;
+        v.z += az;
+        v.xx = fmaf(ax, dx, v.xx);
+        v.zz = fmaf(az, dz, v.zz);
+        v.xz = fmaf(ax, dz, v.xz);
+        v.y += s1;
+        v.yy += s2;
+        v.xy = fmaf(s1, dx, v.xy);
+        v.yz = fmaf(s1, dz, v.yz);
     }
-    // from sums over the step index k to moments in dy = dy0 + k (dy0 is the Gaussian's):
-    // sum (dy0 + k) gE = k1 + dy0 m0, sum (dy0 + k)^2 gE = k2 + dy0 (2 k1 + dy0 m0), and
-    // the products with dx and dz likewise
-    // (the global-memory path summed in dy already: k1, k2, k1x, k1z are the moments)
-    float my = FROM_LDS ? fmaf(dy0, m0, k1) : k1;
-    float myy = FROM_LDS ? fmaf(dy0, fmaf(2.0f, k1, dy0 * m0), k2) : k2;
-    float mxy = FROM_LDS ? fmaf(dy0, mx, k1x) : k1x;
-    float myz = FROM_LDS ? fmaf(dy0, mz, k1z) : k1z;
-    m0 = group_sum<G>(m0);
-    mx = group_sum<G>(mx);
-    my = group_sum<G>(my);
-    mz = group_sum<G>(mz);
-    mxx = group_sum<G>(mxx);
-    myy = group_sum<G>(myy);
-    mzz = group_sum<G>(mzz);
-    mxy = group_sum<G>(mxy);
-    mxz = group_sum<G>(mxz);
-    myz = group_sum<G>(myz);
-    if (ql == 0 && gvalid) {
-        // K as a full symmetric matrix has off-diagonal entries kxy/2, kxz/2, kyz/2
-        const float Al = r0.w * GM_LN2F;   // amp ln2
-        const float hxy = 0.5f * kxy, hxz = 0.5f * kxz, hyz = 0.5f * kyz;
-        const float tx = kxx * mx + hxy * my + hxz * mz;
-        const float ty = hxy * mx + kyy * my + hyz * mz;
-        const float tz = hxz * mx + hyz * my + kzz * mz;
-        float2* o = reinterpret_cast<float2*>(a.grid_grads + ((size_t)gi * a.n + gid) * 10);
-        o[0] = make_float2(m0, -2.0f * Al * tx);
-        o[1] = make_float2(-2.0f * Al * ty, -2.0f * Al * tz);
-        o[2] = make_float2(Al * mxx, Al * myy);
-        o[3] = make_float2(Al * mzz, Al * mxy);
-        o[4] = make_float2(Al * mxz, Al * myz);
-    }
+    store_partials<G>(a, a.grid_index[kk], mine, gvalid, rec, v);
 }
 
 // Exclusive prefix sums of hist[0..NKEY) in place and the total in hist[NKEY], by one
-// wavefront (three keys per lane).
+// wavefront (a run of keys per lane).
 __device__ __forceinline__ void scan_keys(int* hist, int lane)
 {
-    static_assert(NKEY <= 3 * 64, "three keys per lane");
-    int c[3], sum = 0;
+    constexpr int PER = (NKEY + 63) / 64;
+    int c[PER], sum = 0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int k = 3 * lane + i;
+    for (int i = 0; i < PER; ++i) {
+        const int k = PER * lane + i;
         c[i] = k < NKEY ? hist[k] : 0;
         sum += c[i];
     }
@@ -365,33 +435,44 @@ __device__ __forceinline__ void scan_keys(int* hist, int lane)
     }
     int off = incl - sum;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int k = 3 * lane + i;
+    for (int i = 0; i < PER; ++i) {
+        const int k = PER * lane + i;
         if (k < NKEY) hist[k] = off;
         off += c[i];
     }
     if (lane == 63) hist[NKEY] = incl;
 }
 
-// One block (four wavefronts) per tile of a listed grid.  The block stages the tile's dL/dI
-// region in LDS (coalesced rows), then sorts the home Gaussians of the tile's list (the tile
-// holding the box's lower corner: every Gaussian of the grid exactly once), WINB list entries
-// at a time, by the loop trips of their boxes: a counting sort over (column chunks, y length)
-// with LDS atomics.  The sorted Gaussians are taken eight at a time (a round), rounds dealt to
-// the wavefronts in turn, so that the eight Gaussians of a wavefront have similar loop trips
-// and the wavefronts of the block similar work.  Each Gaussian is read from LDS when its box
-// lies inside the region (the common case) and from global memory otherwise.  A Gaussian's
-// partials come from its own eight lanes only and do not depend on which others share its
-// round, so the order the atomics give within a key does not change any result bit.
-// Gaussians with an empty box are in no list; gm_bin wrote their zeros.
+// One block (four wavefronts) per part of a tile's list (1 << parts_log2 parts per tile, by
+// partial_parts below).  The block sorts the part's home Gaussians (home: the tile holds the box's
+// lower corner, so every Gaussian of the grid is home exactly once), WINB list entries at a time,
+// by the loop trips of their boxes: a counting sort over (x passes, planes, y length) with LDS
+// atomics.  It stages the dL/dI region they need in LDS (coalesced rows).  The sorted Gaussians are
+// taken PER_ROUND at a time, rounds dealt to the wavefronts in turn, so that the Gaussians of a
+// round have similar loop trips and the wavefronts similar work.  Each Gaussian is read from LDS
+// when its box lies inside the region (the common case) and from global memory otherwise.  A
+// Gaussian's partials come from its own lanes only and do not depend on which others share its
+// round, so the order the atomics give within a key does not change any result bit.  Gaussians
+// with an empty box are in no list; gm_bin wrote their zeros.
+//
+// Bound by vector issue (166 M VALU instructions at the 256^3 workload, half of them walking
+// boxes) and by latency: list, records, region and sort precede a block's first round, and five
+// blocks a CU (29 KB of LDS, 96 VGPRs) have to cover that.  1M Gaussians on three 256x256x64
+// stacks 378 us, 200k on 128x128x32 90, 20k on 64x64x16 38 (29 with the list in four parts); with
+// eight lanes per Gaussian walking dense chunks of (x, z) columns, a column's place found anew for
+// each, 425, 104 and 44.  Staging the records in LDS as well (four blocks a CU) took 460, the next
+// round's records in flight while one is walked 443 (the registers cost a block, and the wait for
+// them is also one for the stores in between).
 template <bool MASK>
-__global__ __launch_bounds__(256) void k_partials(const BackwardArgs a)
+__global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardArgs a)
 {
-    __shared__ float region[RZ * RZS];
+    __shared__ float region[REGION];
     __shared__ uint32_t order[WINB];
     __shared__ int hist[NKEY + 1];
+    __shared__ uint32_t round_box[WINB / PER_ROUND];
     __shared__ int zext;
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int lin = blk >> a.parts_log2;
     int kk = 0;                                            // listed grid of this block
 #pragma unroll 1
     while (kk + 1 < a.n_ids && lin >= a.block_start[kk + 1]) ++kk;
@@ -399,8 +480,13 @@ __global__ __launch_bounds__(256) void k_partials(const BackwardArgs a)
     const int ntx = a.ntx[kk], nty = a.nty[kk];
     const int t0x = (t % ntx) * GM_TX, t0y = ((t / ntx) % nty) * GM_TY, t0z = (t / (ntx * nty)) * GM_TZ;
     const int64_t T = a.tile_base[kk] + t;
-    const int e0 = __builtin_amdgcn_readfirstlane(a.tile_start[T]);
-    const int e1 = __builtin_amdgcn_readfirstlane(a.tile_start[T + 1]);
+    int e0 = __builtin_amdgcn_readfirstlane(a.tile_start[T]);
+    int e1 = __builtin_amdgcn_readfirstlane(a.tile_start[T + 1]);
+    {   // this block's part of the tile's list
+        const int per = (int)(((int64_t)(e1 - e0) + (1 << a.parts_log2) - 1) >> a.parts_log2);
+        e0 = min(e0 + (blk & ((1 << a.parts_log2) - 1)) * per, e1);
+        e1 = min(e0 + per, e1);
+    }
     if (e0 == e1) return;  // block-uniform
     const int nx = a.nx[kk], ny = a.ny[kk], nz = a.nz[kk];
     const float* __restrict__ g = a.dl_di[kk];
@@ -429,8 +515,8 @@ __global__ __launch_bounds__(256) void k_partials(const BackwardArgs a)
             if (fabsf(kyy) * wyf * wyf > 64.0f) return NKEY - 1;
         }
         zreach = hz - t0z + 1;
-        const int chunks = ((hx - lx + 1) * (hz - lz + 1) + BWD_G - 1) / BWD_G;
-        return (min(chunks, 8) - 1) * 16 + (min(hy - ly + 1, 16) - 1);
+        return (min((hx - lx) / BWD_G, KEY_X - 1) * KEY_Z + min(hz - lz, KEY_Z - 1)) * KEY_Y +
+               min(hy - ly, KEY_Y - 1);
     };
     uint32_t v[EPT];
     int key[EPT], rank[EPT];
@@ -448,93 +534,95 @@ __global__ __launch_bounds__(256) void k_partials(const BackwardArgs a)
     auto scatter = [&]() {
 #pragma unroll
         for (int h = 0; h < EPT; ++h)
-            if (key[h] >= 0) order[hist[key[h]] + rank[h]] = v[h];
+            if (key[h] >= 0) {
+                const int pos = hist[key[h]] + rank[h];
+                order[pos] = v[h];
+                if (key[h] < NKEY - 1) {
+                    const int zx = key[h] / KEY_Y;
+                    atomicOr(&round_box[pos / PER_ROUND], (1u << (key[h] - zx * KEY_Y)) |
+                             (1u << (KEY_Y + zx % KEY_Z)) | (1u << (KEY_Y + KEY_Z + zx / KEY_Z)));
+                }
+            }
     };
     // the rounds of one sorted window: n_lds Gaussians from LDS, then the rest from global
-    // memory; round r (order entries 8 r .. 8 r + 7) goes to wavefront r mod 4, and the next
-    // round's records are in flight while a round is processed
-    constexpr int PER_ROUND = 64 / BWD_G;
+    // memory
     const int grp = lane / BWD_G;
     auto rounds = [&](int n_lds, int n_all) {
         const int nr = (n_lds + PER_ROUND - 1) / PER_ROUND;
-        // two record buffers used in turn (no copy between rounds)
-        uint32_t ma = 0u, mb = 0u;
-        bool va = false, vb = false;
-        Rec ra, rb;
-        auto fetch = [&](int r, Rec& rec, uint32_t& m, bool& v) {
+#pragma unroll 1
+        for (int q = 0; q < nr; q += 4) {
+            // rounds grow with r: dealt out forwards and backwards in turn
+            const int r = q + (q & 4 ? 3 - wv : wv);
+            if (r >= nr) continue;
             const int ix = r * PER_ROUND + grp;
-            v = ix < n_lds;
-            m = v ? order[ix] : 0u;
-            rec = load_record(a, gi, m);
+            const bool valid = ix < n_lds;
+            const uint32_t m = valid ? order[ix] : 0u;
+            const Rec rec = load_record(a, gi, m);
+            lds_round(a, gi, m, valid, rec, region, t0x, t0y, t0z, (uint32_t)sgpr(round_box[r]));
+        }
+        // From global memory: eight lanes each, or, when few are left, a wavefront each, whose 64
+        // lanes see a box in one or two reads' latency.  (Some 1.5 of a tile's 244 at the 256^3
+        // workload: eight lanes took 50 us of the kernel's time.  With many, as in the block
+        // query, the wavefronts' latencies overlap: radius 3 on 64^3 266 us a step with eight
+        // lanes, 273 with 16, 309 with 64.)
+        auto from_global = [&](auto g_lanes) {
+            constexpr int GG = decltype(g_lanes)::value, PER = 64 / GG;
+#pragma unroll 1
+            for (int r = wv; r < (n_all - n_lds + PER - 1) / PER; r += 4) {
+                const int ix = n_lds + r * PER + lane / GG;
+                const bool valid = ix < n_all;
+                const uint32_t m = valid ? order[ix] : 0u;
+                const Rec gr = load_record(a, gi, m);
+                global_round<MASK, GG>(a, kk, m, valid, gr, mk);
+            }
         };
-        if (wv < nr) fetch(wv, ra, ma, va);
-#pragma unroll 1
-        for (int r = wv; r < nr; r += 8) {
-            if (r + 4 < nr) fetch(r + 4, rb, mb, vb);
-            group_of_gaussians<BWD_G, true>(a, kk, ma, va, ra, region, t0x, t0y, t0z);
-            if (r + 4 >= nr) break;
-            if (r + 8 < nr) fetch(r + 8, ra, ma, va);
-            group_of_gaussians<BWD_G, true>(a, kk, mb, vb, rb, region, t0x, t0y, t0z);
-        }
-        const int ng = (n_all - n_lds + PER_ROUND - 1) / PER_ROUND;
-#pragma unroll 1
-        for (int r = wv; r < ng; r += 4) {
-            const int ix = n_lds + r * PER_ROUND + grp;
-            const bool valid = ix < n_all;
-            const uint32_t mine = valid ? order[ix] : 0u;
-            const Rec rec = load_record(a, gi, mine);
-            group_of_gaussians<BWD_G, false, MASK>(a, kk, mine, valid, rec, region, t0x, t0y,
-                                                   t0z, mk);
-        }
+        if (n_all - n_lds > 16)
+            from_global(std::integral_constant<int, 8>{});
+        else
+            from_global(std::integral_constant<int, 64>{});
     };
 
-    // first window: keys counted while the z planes the home boxes reach (those that fit
-    // the region) are found over the whole list; only those planes are staged
+    // WINB entries of the list at a time.  With the first, the z planes the home boxes reach
+    // (those that fit the region) are found over the whole list and only those planes staged.
     if (tid == 0) zext = 0;
-    for (int i = tid; i < NKEY; i += 256) hist[i] = 0;
-    __syncthreads();
-    int zmax = 0;
-    count_keys(e0, zmax);
-    for (int i = e0 + WINB + tid; i < e1; i += 256) {
-        uint32_t vi;
-        int zr;
-        classify(i, vi, zr);
-        zmax = max(zmax, zr);
-    }
-    if (zmax > 0) atomicMax(&zext, zmax);
-    __syncthreads();
-    if (wv == 0) scan_keys(hist, lane);
-    const int nzr = min(zext, nz - t0z);
-    // rows of RX voxels along x: thread -> (x, y) of a plane, then the planes
-    for (int i = tid; i < RX * RY; i += 256) {
-        const int y = i / RX, x = i - y * RX;
-        const int gx = t0x + x, gy = t0y + y;
-        const bool in = gx < nx && gy < ny;
-        const float* src = g + ((size_t)t0z * ny + gy) * nx + gx;
-        float* dst = region + y * RX + x;
-        for (int z = 0; z < nzr; ++z) {
-            dst[z * RZS] = in ? src[0] : 0.0f;
-            src += (size_t)nx * ny;
-        }
-    }
-    __syncthreads();
-    scatter();
-    __syncthreads();
-    rounds(hist[NKEY - 1], hist[NKEY]);
-    // further windows (lists longer than WINB entries)
 #pragma unroll 1
-    for (int w0 = e0 + WINB; w0 < e1; w0 += WINB) {
-        __syncthreads();                       // order and hist are free again
+    for (int w0 = e0; w0 < e1; w0 += WINB) {
         for (int i = tid; i < NKEY; i += 256) hist[i] = 0;
+        if (tid < WINB / PER_ROUND) round_box[tid] = 0u;
         __syncthreads();
-        int zr = 0;
-        count_keys(w0, zr);
+        int zmax = 0;
+        count_keys(w0, zmax);
+        if (w0 == e0) {
+            for (int i = e0 + WINB + tid; i < e1; i += 256) {
+                uint32_t vi;
+                int zr;
+                classify(i, vi, zr);
+                zmax = max(zmax, zr);
+            }
+            if (zmax > 0) atomicMax(&zext, zmax);
+        }
         __syncthreads();
         if (wv == 0) scan_keys(hist, lane);
+        if (w0 == e0) {
+            const int nzr = min(zext, nz - t0z);
+            // rows of RX voxels along x: thread -> (x, y) of a plane, then the planes
+            for (int i = tid; i < RX * RY; i += 256) {
+                const int y = i / RX, x = i - y * RX;
+                const int gx = t0x + x, gy = t0y + y;
+                const bool in = gx < nx && gy < ny;
+                const float* src = g + ((size_t)t0z * ny + gy) * nx + gx;
+                float* dst = region + y * RX + x;
+                for (int z = 0; z < nzr; ++z) {
+                    dst[z * RZS] = in ? src[0] : 0.0f;
+                    src += (size_t)nx * ny;
+                }
+            }
+        }
         __syncthreads();
         scatter();
         __syncthreads();
         rounds(hist[NKEY - 1], hist[NKEY]);
+        __syncthreads();                       // order, hist and round_box are free again
     }
 }
 
@@ -813,17 +901,33 @@ __global__ __launch_bounds__(POSE_BLOCKS) void k_pose_sum(const double* part, in
 
 }  // namespace
 
-hipError_t launch_backward_partials(const BackwardArgs& a, hipStream_t s)
+// Blocks per tile (log2): as many as leave the launch within what the chip holds at a time, since
+// each part pays the sort and the staging again.  Three 64x64x16 stacks (192 tiles): a step of
+// 128 us with four parts, 137 with one, 129 with eight; three 96x96x24 (648 tiles): 196 with two,
+// 191 with one.  The block query's boxes are many times larger than the staging, and a part more
+// even: 192 tiles at radius 3, 271 us with 16 parts, 286 with 8, 550 with one, 277 with 32.
+static int partial_parts_log2(int64_t tiles, bool block_query)
 {
-    if (a.n == 0 || a.n_ids == 0) return hipSuccess;
-    const int32_t blocks = a.block_start[a.n_ids];   // one per tile of the listed grids
-    if (blocks <= 0) return hipSuccess;
+    const int64_t blocks = block_query ? 4096 : 1024;
+    int lg = 0;
+    while (lg < 4 && tiles << (lg + 1) <= blocks) ++lg;
+    return lg;
+}
+
+hipError_t launch_backward_partials(const BackwardArgs& args, hipStream_t s)
+{
+    if (args.n == 0 || args.n_ids == 0) return hipSuccess;
+    const int32_t tiles = args.block_start[args.n_ids];   // of the listed grids
+    if (tiles <= 0) return hipSuccess;
+    BackwardArgs a = args;
+    a.parts_log2 = partial_parts_log2(tiles, a.block_query != 0);
     bool masked = false;
     for (int k = 0; k < a.n_ids; ++k) masked = masked || a.masked[k];
+    const dim3 grid((unsigned)tiles << a.parts_log2);
     if (masked)
-        hipLaunchKernelGGL(k_partials<true>, dim3((unsigned)blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_partials<true>, grid, dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(k_partials<false>, dim3((unsigned)blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_partials<false>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -175,7 +175,8 @@ struct BackwardArgs {
     const int32_t* tile_start;          // CSR rows of the tile lists
     int64_t tile_base[GM_MAX_GRIDS];    // global id of each listed grid's first tile
     int32_t ntx[GM_MAX_GRIDS], nty[GM_MAX_GRIDS];
-    int32_t block_start[GM_MAX_GRIDS + 1];  // first block (= tile) of each listed grid
+    int32_t block_start[GM_MAX_GRIDS + 1];  // first tile of each listed grid
+    int32_t parts_log2;                 // blocks per tile (log2), each a part of its list
     BlockQuery bq;                      // read on masked grids
     int32_t block_query;                // the bins come from the block query (any grid)
     int32_t masked[GM_MAX_GRIDS];       // the block query on a rotated grid
