@@ -287,25 +287,24 @@ gm_status gm_nrf_workspace(const gm_nrf* nrf, int64_t n_points, size_t* bytes);
  * or 0) with respect to every weight
  * and bias of the field; accumulates into grads.  dl_dr is grid-sized [nz][ny][nx].  With a
  * random subset of n voxels and scale = (grid voxels) / n this is an unbiased estimate of the
- * full gradient (the paper trains on sampled points).  Recomputes the forward, writes the
- * per-layer dZ and activations in BF16 to the workspace, forms dA = W^T dZ and
- * dW = dZ A^T on MFMA (split over points, partial sums added in fixed order). */
+ * full gradient (the paper trains on sampled points).  Recomputes the forward and forms
+ * dA = W^T dZ and dW = dZ A^T (dZ and activations in BF16) on MFMA in one kernel, split over
+ * points; the workspace takes the blocks' partial sums, which are added in fixed order. */
 gm_status gm_nrf_backward(const gm_nrf* nrf, const gm_grid* grid, const int32_t* idx,
                           int64_t n_points, const float* dl_dr, float scale,
                           gm_nrf_grads* grads, void* workspace, size_t workspace_bytes,
                           gm_stream stream);
 
 /* [host out] device workspace bytes gm_nrf_backward_grids needs for n_grids point lists of
- * n_points[k] points (each rounded up to a multiple of 16 in the workspace). */
+ * n_points[k] points. */
 gm_status gm_nrf_workspace_grids(const gm_nrf* nrf, int32_t n_grids, const int64_t* n_points,
                                  size_t* bytes);
 
 /* The backward of gm_nrf_backward summed over several grids in one pass: the gradient of
  * sum_k scales[k] sum_{j < n_points[k]} dl_dr[k][v_kj] r(x_{v_kj}), v_kj = idx[k][j] (idx[k]
  * NULL = every voxel of grids[k]), accumulated into grads.  Equal to the n_grids calls of
- * gm_nrf_backward up to the order of the FP32 sums: the chain kernel runs once per grid into
- * one workspace, then the weight-gradient GEMMs and their sums run once over all the points
- * (the paper's sampled training points of every stack, Sec. 3.4).  grids, idx, n_points,
+ * gm_nrf_backward up to the order of the FP32 sums, in one launch over all the points and one
+ * for the partial sums (the paper's sampled training points of every stack, Sec. 3.4).  grids, idx, n_points,
  * dl_dr, scales: [host] arrays of n_grids (1 <= n_grids <= GM_MAX_GRIDS); idx[k] and dl_dr[k]
  * device pointers; other arguments and errors as for gm_nrf_backward, with workspace_bytes at
  * least what gm_nrf_workspace_grids gives. */

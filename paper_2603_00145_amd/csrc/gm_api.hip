@@ -256,26 +256,11 @@ NrfArgs nrf_args(const gm_nrf* n, const gm_grid& g, const double* M)
     return a;
 }
 
-struct NrfLayout {
-    size_t bytes;
-    size_t off_dzo, off_dz[4], off_a[5], off_part;
-    int64_t P;
-};
+int64_t nrf_rounds(int64_t n_points) { return (n_points + NRF_ROUND - 1) / NRF_ROUND; }
 
-NrfLayout nrf_layout(const gm_nrf* n, int64_t npts)
+size_t nrf_bytes(const gm_nrf* n, int64_t rounds)
 {
-    NrfLayout L;
-    memset(&L, 0, sizeof L);
-    L.P = ((npts + 15) / 16) * 16;
-    size_t o = 0;
-    auto take = [&](size_t b) { const size_t r = o; o += align256(b); return r; };
-    L.off_dzo = take((size_t)L.P * 4);
-    for (int l = 0; l < n->depth; ++l) L.off_dz[l] = take((size_t)64 * L.P * 2);
-    L.off_a[0] = take((size_t)n->in_pad * L.P * 2);
-    for (int l = 1; l <= n->depth; ++l) L.off_a[l] = take((size_t)64 * L.P * 2);
-    L.off_part = take(nrf_part_floats(L.P, n->in_pad) * 4);
-    L.bytes = o;
-    return L;
+    return align256(nrf_part_floats(rounds, n->in_pad, n->depth) * 4);
 }
 
 // workspace of a warm-start batch; with base NULL only the size
@@ -750,25 +735,11 @@ gm_status gm_nrf_workspace(const gm_nrf* nrf, int64_t n_points, size_t* bytes)
     if (st != GM_OK) return st;
     if (n_points < 0 || n_points > 0x7fffffffLL || !bytes)
         return fail(GM_ERR_INVALID_ARGUMENT, "n_points outside [0, 2^31) or bytes NULL");
-    *bytes = nrf_layout(nrf, n_points).bytes;
+    *bytes = nrf_bytes(nrf, nrf_rounds(n_points));
     return GM_OK;
 }
 
 namespace {
-
-// the workspace views of a layout over P points
-NrfWork nrf_work(const gm_nrf* nrf, const NrfLayout& L, void* workspace)
-{
-    char* base = reinterpret_cast<char*>(workspace);
-    NrfWork w;
-    memset(&w, 0, sizeof w);
-    w.P = L.P;
-    w.dzo = reinterpret_cast<float*>(base + L.off_dzo);
-    for (int l = 0; l < nrf->depth; ++l) w.dz[l] = reinterpret_cast<uint16_t*>(base + L.off_dz[l]);
-    for (int l = 0; l <= nrf->depth; ++l) w.a[l] = reinterpret_cast<uint16_t*>(base + L.off_a[l]);
-    w.part = reinterpret_cast<float*>(base + L.off_part);
-    return w;
-}
 
 gm_status check_nrf_grads(const gm_nrf* nrf, const gm_nrf_grads* grads)
 {
@@ -785,9 +756,9 @@ gm_status check_nrf_grads(const gm_nrf* nrf, const gm_nrf_grads* grads)
 }
 
 // one grid's point list of a backward call, checked
-gm_status nrf_backward_grid(const gm_nrf* nrf, int k, const gm_grid& grid, const int32_t* idx,
+gm_status nrf_backward_grid(int k, const gm_grid& grid, const int32_t* idx,
                             int64_t n_points, const float* dl_dr, float scale,
-                            const gm_nrf_grads* grads, NrfArgs* out)
+                            NrfGrids* out)
 {
     gm_status st = check_grid(grid, k);
     if (st != GM_OK) return st;
@@ -801,18 +772,41 @@ gm_status nrf_backward_grid(const gm_nrf* nrf, int k, const gm_grid& grid, const
     double M[12];
     if (!index_to_world(grid, M))
         return fail(GM_ERR_INVALID_ARGUMENT, "grid %d: singular grid affine", k);
-    NrfArgs a = nrf_args(nrf, grid, M);
-    a.n_points = n_points;
-    a.idx = idx;
-    a.dl_dr = dl_dr;
-    a.scale = scale;
+    auto& e = out->g[k];
+    e.n_points = n_points;
+    e.idx = idx;
+    e.dl_dr = dl_dr;
+    e.scale = scale;
+    e.nx = grid.nx;
+    e.ny = grid.ny;
+    memcpy(e.m, M, sizeof M);
+    out->n = k + 1;
+    out->round0[k + 1] = out->round0[k] + nrf_rounds(n_points);
+    return GM_OK;
+}
+
+// the checks that remain once there are points, and the launch
+gm_status nrf_backward_impl(const gm_nrf* nrf, const gm_grid& grid, const NrfGrids& gs,
+                            gm_nrf_grads* grads, void* workspace, size_t workspace_bytes,
+                            gm_stream stream)
+{
+    REQ_PTR(workspace, "workspace");
+    gm_status st = check_nrf_grads(nrf, grads);
+    if (st != GM_OK) return st;
+    const size_t need = nrf_bytes(nrf, gs.round0[gs.n]);
+    if (workspace_bytes < need)
+        return fail(GM_ERR_INVALID_ARGUMENT, "workspace %zu bytes < required %zu", workspace_bytes,
+                    need);
+    NrfArgs a = nrf_args(nrf, grid, gs.g[0].m);   // the weights; the grids are in gs
     a.g_w_in = grads->w_in;
     a.g_b_in = grads->b_in;
     a.g_w_hid = grads->w_hid;
     a.g_b_hid = grads->b_hid;
     a.g_w_out = grads->w_out;
     a.g_b_out = grads->b_out;
-    *out = a;
+    GM_HIP(launch_nrf_backward(a, gs, reinterpret_cast<float*>(workspace),
+                               reinterpret_cast<hipStream_t>(stream)),
+           "nrf backward");
     return GM_OK;
 }
 
@@ -833,20 +827,12 @@ gm_status gm_nrf_backward(const gm_nrf* nrf, const gm_grid* grid, const int32_t*
     gm_status st = check_nrf(nrf);
     if (st != GM_OK) return st;
     if (!grid || !grads) return fail(GM_ERR_INVALID_ARGUMENT, "grid / grads is NULL");
-    NrfArgs a;
-    st = nrf_backward_grid(nrf, 0, *grid, idx, n_points, dl_dr, scale, grads, &a);
+    NrfGrids gs;
+    memset(&gs, 0, sizeof gs);
+    st = nrf_backward_grid(0, *grid, idx, n_points, dl_dr, scale, &gs);
     if (st != GM_OK) return st;
     if (n_points == 0) return GM_OK;
-    REQ_PTR(workspace, "workspace");
-    st = check_nrf_grads(nrf, grads);
-    if (st != GM_OK) return st;
-    const NrfLayout L = nrf_layout(nrf, n_points);
-    if (workspace_bytes < L.bytes)
-        return fail(GM_ERR_INVALID_ARGUMENT, "workspace %zu bytes < required %zu", workspace_bytes,
-                    L.bytes);
-    const NrfWork w = nrf_work(nrf, L, workspace);
-    GM_HIP(launch_nrf_backward(a, w, reinterpret_cast<hipStream_t>(stream)), "nrf backward");
-    return GM_OK;
+    return nrf_backward_impl(nrf, *grid, gs, grads, workspace, workspace_bytes, stream);
 }
 
 gm_status gm_nrf_workspace_grids(const gm_nrf* nrf, int32_t n_grids, const int64_t* n_points,
@@ -863,7 +849,9 @@ gm_status gm_nrf_workspace_grids(const gm_nrf* nrf, int32_t n_grids, const int64
             return fail(GM_ERR_INVALID_ARGUMENT, "n_points[%d] outside [0, 2^31)", k);
     const int64_t P = rounded_points(n_grids, n_points);
     if (P > 0x7fffffffLL) return fail(GM_ERR_INVALID_ARGUMENT, "more than 2^31 points in all");
-    *bytes = nrf_layout(nrf, P).bytes;
+    int64_t rounds = 0;
+    for (int k = 0; k < n_grids; ++k) rounds += nrf_rounds(n_points[k]);
+    *bytes = nrf_bytes(nrf, rounds);
     return GM_OK;
 }
 
@@ -880,26 +868,16 @@ gm_status gm_nrf_backward_grids(const gm_nrf* nrf, int32_t n_grids, const gm_gri
         return fail(GM_ERR_INVALID_ARGUMENT, "n_grids outside [1, %d]", GM_MAX_GRIDS);
     if (!grids || !idx || !n_points || !dl_dr || !scales || !grads)
         return fail(GM_ERR_INVALID_ARGUMENT, "grids / idx / n_points / dl_dr / scales / grads NULL");
-    NrfArgs as[GM_MAX_GRIDS];
+    NrfGrids gs;
+    memset(&gs, 0, sizeof gs);
     for (int k = 0; k < n_grids; ++k) {
-        st = nrf_backward_grid(nrf, k, grids[k], idx[k], n_points[k], dl_dr[k], scales[k], grads,
-                               &as[k]);
+        st = nrf_backward_grid(k, grids[k], idx[k], n_points[k], dl_dr[k], scales[k], &gs);
         if (st != GM_OK) return st;
     }
     const int64_t P = rounded_points(n_grids, n_points);
     if (P == 0) return GM_OK;
     if (P > 0x7fffffffLL) return fail(GM_ERR_INVALID_ARGUMENT, "more than 2^31 points in all");
-    REQ_PTR(workspace, "workspace");
-    st = check_nrf_grads(nrf, grads);
-    if (st != GM_OK) return st;
-    const NrfLayout L = nrf_layout(nrf, P);
-    if (workspace_bytes < L.bytes)
-        return fail(GM_ERR_INVALID_ARGUMENT, "workspace %zu bytes < required %zu", workspace_bytes,
-                    L.bytes);
-    const NrfWork w = nrf_work(nrf, L, workspace);
-    GM_HIP(launch_nrf_backward_grids(as, n_grids, w, reinterpret_cast<hipStream_t>(stream)),
-           "nrf backward over grids");
-    return GM_OK;
+    return nrf_backward_impl(nrf, grids[0], gs, grads, workspace, workspace_bytes, stream);
 }
 
 gm_status gm_f32_to_bf16(const float* in, uint16_t* out, int64_t n, gm_stream stream)

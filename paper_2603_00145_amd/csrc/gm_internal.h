@@ -309,8 +309,6 @@ struct NrfArgs {
     const int32_t* idx;      // voxel linear indices, or NULL for every voxel in order
     double m[12];            // index -> world affine
     float* out;              // forward: out[v] += r
-    const float* dl_dr;      // backward: per-voxel dL/dr of the grid
-    float scale;
     float* g_w_in;
     float* g_b_in;
     float* g_w_hid;
@@ -318,28 +316,28 @@ struct NrfArgs {
     float* g_w_out;
     float* g_b_out;
 };
-struct NrfWork {
-    int64_t P;               // workspace points (every grid's, each rounded up to 16)
-    float* dzo;              // [P]
-    uint16_t* dz[4];         // [64][P] per layer
-    uint16_t* a[5];          // a[0] [in_pad][P], a[l] [64][P]
-    float* part;             // split-K partials
-    // the chain kernel's grid: its points sit at workspace columns p0 .. p0 + np (np its point
-    // count rounded up to 16), its wavefronts' output-layer partials at rows wave0 .. of
-    // nwaves_total
-    int64_t p0, np, wave0, nwaves_total;
+// The field backward's grids: point lists by rounds of NRF_ROUND points (no round holds two
+// grids' points); round0[n] = all the rounds
+constexpr int NRF_ROUND = 64;
+struct NrfGrids {
+    int32_t n;
+    int64_t round0[GM_MAX_GRIDS + 1];
+    struct {
+        int64_t n_points;
+        const int32_t* idx;      // voxel linear indices, or NULL for every voxel in order
+        const float* dl_dr;      // per-voxel dL/dr
+        float scale;
+        int32_t nx, ny;
+        double m[12];            // index -> world affine
+    } g[GM_MAX_GRIDS];
 };
 // most frequency bands the kernels encode with in_pad 64 / 128 input features
 int nrf_max_bands(int in_pad);
 hipError_t launch_nrf_forward(const NrfArgs& a, hipStream_t s);
-// floats of split-K / row-sum partials gm_nrf_backward needs for P points
-size_t nrf_part_floats(int64_t P, int in_pad);
-hipError_t launch_nrf_backward(const NrfArgs& a, const NrfWork& w, hipStream_t s);
-// the backward summed over n grids' point lists (a[k]: grid k's arguments, the weights and
-// gradients the same in all), into one workspace of w.P = sum of the rounded point counts
-hipError_t launch_nrf_backward_grids(const NrfArgs* a, int n, const NrfWork& w, hipStream_t s);
-// chain kernel blocks (4 wavefronts each) for np points
-unsigned nrf_chain_blocks(const NrfArgs& a, int64_t np);
+// floats of per-block partial gradients the backward needs for a number of rounds
+size_t nrf_part_floats(int64_t rounds, int in_pad, int depth);
+// the backward summed over the grids' point lists; a: the weights and gradients
+hipError_t launch_nrf_backward(const NrfArgs& a, const NrfGrids& gs, float* part, hipStream_t s);
 hipError_t launch_to_bf16(const float* in, uint16_t* out, int64_t n, hipStream_t s);
 
 struct WsGatherArgs {

@@ -11,254 +11,338 @@
 // the same K order), so activations never leave registers inside a layer stack.  The encoding
 // is computed directly in that layout.
 //
-// Backward (for a list of sampled voxels): recompute, then per layer dZ_l = dA_l * SiLU'(Z_l),
-// dA_{l-1} = W_l^T dZ_l (MFMA); dZ_l and A_{l-1} are written feature-major (BF16) and the
-// weight gradients dW_l = dZ_l A_{l-1}^T are formed by a split-K MFMA GEMM over the points.
-// The forward alone (k_nrf_forward) is in nrf_fwd.hip.
+// Backward (for lists of sampled voxels): recompute, then per layer dZ_l = dA_l * SiLU'(Z_l),
+// dW_l += dZ_l A_{l-1}^T over the points, dA_{l-1} = W_l^T dZ_l, all in one kernel.  The forward
+// alone (k_nrf_forward) is in nrf_fwd.hip.
 #include "nrf_core.h"
 
 namespace {
 
 using namespace nrfcore;
 
-// Recompute a tile and write, feature-major with point stride P: DZO (f32, per point), and
-// for each layer l (1..D) dZ_l [W][P] and A_{l-1} [in_l][P] (BF16), plus A_D [W][P].
-template <int KT, int DEPTH>
-__global__ __launch_bounds__(256) void k_nrf_chain(const NrfArgs a, NrfWork w)
+constexpr int MAX_BLOCKS = 512;      // two blocks on each of 256 CUs, all resident at once
+
+// Floats of one block's partial gradients: dW of the first layer in the GPU's K order [W][16 KT],
+// the hidden layers' [depth - 1][W][W], the biases [depth][W], w_out [W], b_out
+__host__ __device__ constexpr int part_floats(int in_pad, int depth)
 {
-    __shared__ LdsChain<KT, DEPTH> s;
-    load_weights<KT, DEPTH>(a, s.f, s.w_hid_t);
+    return W * in_pad + (depth - 1) * W * W + depth * W + W + 1;
+}
+
+typedef __attribute__((address_space(3))) v4s* LdsQuad;
+
+// gfx950's transposing LDS read: within each 16 lanes, source lane 4 j + c (its own address)
+// gives element d to lane 4 c + d as that lane's element j
+__device__ __forceinline__ v4s read_tr(const v4s* p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)(p));
+}
+
+template <int KT, int DEPTH>
+struct GradLds {
+    Lds<KT, DEPTH> w;
+    v4f bias[DEPTH][16];           // [l][4 o + g]
+    v4s w_out[16];                 // [4 o + g]
+    // the round's four tiles [t][tile][quad], a lane's quad (point row, features 4 g ..) at
+    // swizzle(lane)
+    v4s enc[KT * 4 * 64];
+    v4s act[DEPTH > 1 ? DEPTH - 1 : 1][4 * 4 * 64];
+    v4s dz[4 * 4 * 64];            // of one layer at a time
+    float out[4][W + 1];           // the output layer's sums, per wavefront
+};
+
+// Where the quad of lane 16 g + row is stored: rows of the upper two lane groups with row bit 2
+// flipped, so that both the quads of one g (the writes, and the weights' plain reads) and the four
+// g of four rows (the transposing reads) lie in 16 different bank pairs.
+__device__ __forceinline__ int swizzle(int lane) { return lane ^ ((lane >> 3) & 4); }
+
+// The quad that lane 16 G + 4 j + c reads for read_tr to give it rows 4 G .. 4 G + 3 of feature
+// 4 j + c: row 4 G + j of lane group c
+__device__ __forceinline__ int transposed(int lane)
+{
+    return swizzle((lane & 3) * 16 + (lane >> 4) * 4 + ((lane >> 2) & 3));
+}
+
+template <int KT, int DEPTH>
+struct GradWeights {
+    const GradLds<KT, DEPTH>& s;
+    int lane, slot, slot_tr;       // swizzle(lane), transposed(lane)
+    __device__ v4f bias(const NrfArgs&, int l, int o) const { return s.bias[l][4 * o + (lane >> 4)]; }
+    __device__ v4s in(int o, int t) const { return s.w.w_in[(o * KT + t) * 64 + lane]; }
+    __device__ v4s hid(int l, int o, int t) const
+    {
+        return s.w.w_hid[((l - 1) * 16 + o * 4 + t) * 64 + slot];
+    }
+    // W_l^T as A operand (i-tile of inputs, o-tile of outputs): lane (g, row) gets
+    // W_l[16 o + 4 g + j][16 i + row], from the quads of W_l's operand (o, i)
+    __device__ v4s hid_t(int l, int i, int o) const
+    {
+        return read_tr(&s.w.w_hid[((l - 1) * 16 + o * 4 + i) * 64 + slot_tr]);
+    }
+};
+
+// A lane's point of a round: its grid (uniform), voxel and dL/dr there
+struct Point {
+    int k;
+    bool valid;
+    uint32_t v;
+    float dl;
+};
+
+// A block takes rounds of 64 points, a tile of 16 to each wavefront, which runs the tile's forward
+// and backward in registers.  For the weight gradients the K dimension is the points, so each
+// layer's dZ and input go through LDS once: written as the quads (4 features of a point) that
+// the lanes hold, read back transposed (4 points of a feature) as MFMA operands over all four
+// tiles.  The output tiles of dW_l are dealt to the wavefronts as 2 x 2 (half the rows, half the
+// columns), each wavefront's FP32 accumulators staying in registers over all its rounds; row
+// sums (the bias gradients) are one more product, with ones.  W_l^T is read from the staged W_l,
+// also transposed.  Every block leaves one partial of every gradient.
+//
+// Bound by vector issue: per tile some 1000 instructions, most of them the encoding, SiLU and
+// SiLU'.  3 x 262144 points, 16 bands, depth 3: 177 us for all three grids in one launch and 10
+// for the partials' sums (the biases read from global memory, each read a wait in the middle of
+// a layer: 261).  With dZ and the activations written out in BF16 (700 MB, two bytes
+// a lane at a time), a GEMM pass over them per layer and a chain launch per grid, the chain took
+// 375, the GEMMs 220 and the partials' sums 80.
+template <int KT, int DEPTH>
+__global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfArgs a, const NrfGrids gs,
+                                                     float* __restrict__ part)
+{
+    __shared__ GradLds<KT, DEPTH> s;
+    constexpr int CT = KT / 2;      // column tiles of dW_0 per wavefront
     const int lane = threadIdx.x & 63, g = lane >> 4, row = lane & 15;
-    v4s wo[4];
-    load_wout(a, wo);
-    const int64_t P = w.P;
-    const int64_t ntiles = w.np / 16;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wv >> 1, wc = wv & 1;
+    if (threadIdx.x < 16) s.w_out[threadIdx.x] = reinterpret_cast<const v4s*>(a.w_out)[threadIdx.x];
+    if (threadIdx.x < 16 * DEPTH) {
+        const int l = threadIdx.x >> 4, q = threadIdx.x & 15;
+        const float* b = (l == 0 ? a.b_in : a.b_hid + (l - 1) * W) + 4 * q;
+        s.bias[l][q] = v4f{b[0], b[1], b[2], b[3]};
+    }
+    load_weights<KT, DEPTH, true>(a, s.w);
+    const GradWeights<KT, DEPTH> ws{s, lane, swizzle(lane), transposed(lane)};
+    // dW accumulators.  Row tile i of the wavefront is 2 wr + (i ^ wc), so that i = 0 is the one
+    // whose row sums it takes.
+    v4f acc0[2][CT], acch[DEPTH > 1 ? DEPTH - 1 : 1][2][2], accb[DEPTH];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc0[i][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int l = 0; l < DEPTH - 1; ++l)
+            acch[l][i][0] = acch[l][i][1] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int l = 0; l < DEPTH; ++l) accb[l] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     // the output layer's gradient over this wavefront's points: gwo[4 o + j] for feature
     // 16 o + 4 g + j (sum of dzo a_D), gbo the sum of dzo (lanes of group 0)
     float gwo[16], gbo = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) gwo[i] = 0.0f;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); tile < ntiles;
-         tile += (int64_t)gridDim.x * 4) {
-        const int64_t p = tile * 16 + row;
-        const bool valid = p < a.n_points;
+
+    const int64_t rounds = gs.round0[gs.n];
+    auto point = [&](int64_t r, int k) {   // round r's voxel (grid k or a later one)
+        Point p{k, false, 0u, 0.0f};
+        if (r >= rounds) return p;
+        while (r >= gs.round0[p.k + 1]) ++p.k;
+        const int64_t i = (r - gs.round0[p.k]) * NRF_ROUND + 16 * wv + row;
+        p.valid = i < gs.g[p.k].n_points;
+        const int32_t* idx = gs.g[p.k].idx;
+        if (p.valid) p.v = idx ? (uint32_t)idx[i] : (uint32_t)i;
+        return p;
+    };
+    auto fetch_dl = [&](Point& p) { if (p.valid) p.dl = gs.g[p.k].dl_dr[p.v]; };
+    Point cur, nxt = point(blockIdx.x, 0), far = point((int64_t)blockIdx.x + gridDim.x, nxt.k);
+    fetch_dl(nxt);
+#pragma unroll 1
+    for (int64_t r = blockIdx.x; r < rounds; r += gridDim.x) {
+        // voxels are read two rounds ahead and dL/dr one
+        cur = nxt;
+        nxt = far;
+        fetch_dl(nxt);
+        far = point(r + 2 * (int64_t)gridDim.x, far.k);
+        const double* m = gs.g[cur.k].m;
         int vx = 0, vy = 0, vz = 0;
-        if (valid) point_xyz(a, p, &vx, &vy, &vz);
-        const float x[3] = {world_coord(a.m, vx, vy, vz), world_coord(a.m + 4, vx, vy, vz),
-                            world_coord(a.m + 8, vx, vy, vz)};
+        if (cur.valid)
+            voxel_xyz(cur.v, (uint32_t)gs.g[cur.k].nx, (uint32_t)gs.g[cur.k].ny, &vx, &vy, &vz);
+        const float x[3] = {world_coord(m, vx, vy, vz), world_coord(m + 4, vx, vy, vz),
+                            world_coord(m + 8, vx, vy, vz)};
         Tile<KT, DEPTH> T;
-        tile_forward<KT, DEPTH>(a, s.f, x, T, &w, w.p0 + p);
-        // z_o of the lane's point, from lane group 0 to all four
-        const float zo = __shfl(tile_output<KT, DEPTH>(a, T, wo), row, 64);
-        float dl = 0.0f;
-        if (valid) dl = a.dl_dr[((int64_t)vz * a.ny + vy) * a.nx + vx];
-        const float th = tanhf(zo);
-        const float dzo = valid ? dl * a.scale * a.out_scale * (1.0f - th * th) : 0.0f;
+        tile_forward_w<KT, DEPTH>(a, ws, x, T);
+        __syncthreads();            // the last round's products are done
+        const int slot = wv * 64 + ws.slot;
 #pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            const v4s h = T.act[DEPTH - 1][o];
-            gwo[4 * o + 0] += dzo * from_bf16((uint16_t)h.x);
-            gwo[4 * o + 1] += dzo * from_bf16((uint16_t)h.y);
-            gwo[4 * o + 2] += dzo * from_bf16((uint16_t)h.z);
-            gwo[4 * o + 3] += dzo * from_bf16((uint16_t)h.w);
-        }
-        if (g == 0) gbo += dzo;
+        for (int t = 0; t < KT; ++t) s.enc[t * 256 + slot] = T.enc[t];
+#pragma unroll
+        for (int l = 0; l < DEPTH - 1; ++l)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s.act[l][t * 256 + slot] = T.act[l][t];
+        // z_o of the lane's point, from lane group 0 to all four
+        v4s wo[4];                  // w_out as the MFMA operand of row 0
+#pragma unroll
+        for (int o = 0; o < 4; ++o) wo[o] = row == 0 ? s.w_out[4 * o + g] : v4s{0, 0, 0, 0};
+        const float zo = __shfl(tile_output<KT, DEPTH>(a, T, wo), row, 64);
+        const float th = tanhf(zo);
+        const float dzo = cur.valid ? cur.dl * gs.g[cur.k].scale * a.out_scale * (1.0f - th * th)
+                                    : 0.0f;
         // dA_D = dzo w_out, then back through the layers
         v4f da[4];
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-            const int f = 16 * o + 4 * g;
-            da[o].x = dzo * from_bf16(a.w_out[f]);
-            da[o].y = dzo * from_bf16(a.w_out[f + 1]);
-            da[o].z = dzo * from_bf16(a.w_out[f + 2]);
-            da[o].w = dzo * from_bf16(a.w_out[f + 3]);
+            const v4s h = T.act[DEPTH - 1][o], q = s.w_out[4 * o + g];
+            gwo[4 * o + 0] += dzo * from_bf16((uint16_t)h.x);
+            gwo[4 * o + 1] += dzo * from_bf16((uint16_t)h.y);
+            gwo[4 * o + 2] += dzo * from_bf16((uint16_t)h.z);
+            gwo[4 * o + 3] += dzo * from_bf16((uint16_t)h.w);
+            da[o] = v4f{dzo * from_bf16((uint16_t)q.x), dzo * from_bf16((uint16_t)q.y),
+                        dzo * from_bf16((uint16_t)q.z), dzo * from_bf16((uint16_t)q.w)};
         }
+        if (g == 0) gbo += dzo;
 #pragma unroll
         for (int l = DEPTH - 1; l >= 0; --l) {
             v4s dz[4];
 #pragma unroll
             for (int o = 0; o < 4; ++o) {
-                const v4f z = T.z[l][o];
-                const v4f d = da[o];
-                dz[o] = pack4(d.x * dsilu(z.x), d.y * dsilu(z.y), d.z * dsilu(z.z), d.w * dsilu(z.w));
-                store_fm(w.dz[l], 16 * o + 4 * g, P, w.p0 + p, dz[o]);
+                const v4f d = T.d[l][o];
+                dz[o] = pack4(da[o].x * d.x, da[o].y * d.y, da[o].z * d.z, da[o].w * d.w);
             }
-            if (l == 0) break;
-            // dA_{l-1} = W_l^T dZ_l
-            const v4s* Wt = s.w_hid_t + (l - 1) * 16 * 64;
+            if (l < DEPTH - 1) __syncthreads();   // the products of the layer above are done
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int o = 0; o < 4; ++o) s.dz[o * 256 + slot] = dz[o];
+            __syncthreads();
+            if (l > 0) {
+                // dA_{l-1} = W_l^T dZ_l
 #pragma unroll
-                for (int o = 0; o < 4; o += 2)
-                    acc = mfma2(Wt[(i * 4 + o) * 64 + lane], Wt[(i * 4 + o + 1) * 64 + lane], dz[o],
-                                dz[o + 1], acc);
-                da[i] = acc;
+                for (int i = 0; i < 4; ++i) {
+                    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int o = 0; o < 4; o += 2)
+                        acc = mfma2(ws.hid_t(l, i, o), ws.hid_t(l, i, o + 1), dz[o], dz[o + 1], acc);
+                    da[i] = acc;
+                }
+            }
+            // dW_l += dZ_l A_{l-1}^T over the round's points, 32 at a time
+            const v4s* in = l == 0 ? s.enc : s.act[l > 0 ? l - 1 : 0];
+            const v4s ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+#pragma unroll
+            for (int st = 0; st < 4; st += 2) {
+                v4s z[2][2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const v4s* q = &s.dz[((2 * wr + (i ^ wc)) * 4 + st) * 64 + ws.slot_tr];
+                    z[i][0] = read_tr(q);
+                    z[i][1] = read_tr(q + 64);
+                }
+                accb[l] = mfma2(z[0][0], z[0][1], ones, ones, accb[l]);
+#pragma unroll
+                for (int t = 0; t < (l == 0 ? CT : 2); ++t) {
+                    const v4s* q = &in[((wc * (l == 0 ? CT : 2) + t) * 4 + st) * 64 + ws.slot_tr];
+                    const v4s b0 = read_tr(q), b1 = read_tr(q + 64);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        v4f& c = l == 0 ? acc0[i][t] : acch[l > 0 ? l - 1 : 0][i][t & 1];
+                        c = mfma2(z[i][0], z[i][1], b0, b1, c);
+                    }
+                }
             }
         }
     }
-    // sum over the 16 points of each lane group, then one partial per wavefront:
-    // part[wave][64] for w_out, then part[nwaves * 64 + wave] for b_out (waves counted over
-    // every grid of the call)
+    // acc holds rows 4 g + j of its row tile, column lane & 15 of its column tile
+    constexpr int N = 16 * KT;
+    float* out = part + (int64_t)blockIdx.x * part_floats(N, DEPTH);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m0 = 16 * (2 * wr + (i ^ wc)) + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t) out[(m0 + j) * N + 16 * (wc * CT + t) + row] = acc0[i][t][j];
+#pragma unroll
+            for (int l = 0; l < DEPTH - 1; ++l)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    out[W * N + (l * W + m0 + j) * W + 16 * (wc * 2 + t) + row] = acch[l][i][t][j];
+        }
+    }
+    out += W * N + (DEPTH - 1) * W * W;
+    if (row == 0) {
+#pragma unroll
+        for (int l = 0; l < DEPTH; ++l)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) out[l * W + 16 * (2 * wr + wc) + 4 * g + j] = accb[l][j];
+    }
+    out += DEPTH * W;
+    // the output layer: sum over the 16 points of each lane group, then over the wavefronts
 #pragma unroll
     for (int i = 0; i < 16; ++i)
         for (int o = 1; o < 16; o <<= 1) gwo[i] += __shfl_xor(gwo[i], o, 64);
     for (int o = 1; o < 16; o <<= 1) gbo += __shfl_xor(gbo, o, 64);
-    const int64_t nwaves = w.nwaves_total;
-    const int64_t wid = w.wave0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row == 0) {
 #pragma unroll
         for (int o = 0; o < 4; ++o)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w.part[wid * W + 16 * o + 4 * g + j] = gwo[4 * o + j];
-        if (g == 0) w.part[nwaves * W + wid] = gbo;
+            for (int j = 0; j < 4; ++j) s.out[wv][16 * o + 4 * g + j] = gwo[4 * o + j];
+        if (g == 0) s.out[wv][W] = gbo;
     }
+    __syncthreads();
+    if (threadIdx.x <= W)
+        out[threadIdx.x] = (s.out[0][threadIdx.x] + s.out[1][threadIdx.x]) +
+                           (s.out[2][threadIdx.x] + s.out[3][threadIdx.x]);
 }
 
-// Split-K GEMM over points: part[blk][m][n] = sum over block blk's points p of L[m][p] R[n][p],
-// L [64][P] and R [N][P] BF16 (N = 16 NT, P a multiple of 16), FP32 accumulation on MFMA.  Each
-// block owns a contiguous range of GPB points and every output tile: per round it stages 64
-// points of all 64 + N rows in LDS (each row's 128 bytes read as one coalesced segment), laid
-// out so that every MFMA operand is 512 contiguous bytes, and wavefront w multiplies output
-// rows 16 w .. 16 w + 15 against all N columns, its A operand loaded once per 16 points.  With
-// rowpart the block also writes the row sums of L over its points (rowpart[blk][64]).
-constexpr int GPB = 1024;   // points per block
-constexpr int GK = 64;      // points per LDS round
-
-template <int NT>
-__global__ __launch_bounds__(256) void k_gemm_nt_rows(const uint16_t* __restrict__ L,
-                                                      const uint16_t* __restrict__ R, int64_t P,
-                                                      float* __restrict__ part,
-                                                      float* __restrict__ rowpart)
-{
-    constexpr int ROWS = 64 + 16 * NT;
-    constexpr int PER = ROWS * 16 / 256;   // 8-byte segments each thread stages per round
-    static_assert(ROWS * 16 % 256 == 0, "rounds split evenly over the block");
-    __shared__ v4s sl[4 * 4 * 64];     // [row block][16-point step][lane]
-    __shared__ v4s sr[NT * 4 * 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    v4f acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    const int64_t p0 = (int64_t)blockIdx.x * GPB;
-    const int64_t p1 = min(p0 + (int64_t)GPB, P);
-    // the next round's segments are fetched into registers while this round multiplies
-    v4s nxt[PER];
-    auto fetch = [&](int64_t q0) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = (int)threadIdx.x + i * 256;
-            const int r = e >> 4, c = e & 15;
-            const int64_t q = q0 + 4 * c;
-            const bool isl = r < 64;
-            const uint16_t* src = (isl ? L : R) + (int64_t)(isl ? r : r - 64) * P;
-            nxt[i] = q < p1 ? *reinterpret_cast<const v4s*>(src + q) : v4s{0, 0, 0, 0};
-        }
-    };
-    if (p0 < p1) fetch(p0);
-    float rsum = 0.0f;
-    for (int64_t q0 = p0; q0 < p1; q0 += GK) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = (int)threadIdx.x + i * 256;
-            const int r = e >> 4, c = e & 15;
-            const bool isl = r < 64;
-            const int rr = isl ? r : r - 64;
-            const int slot = ((rr >> 4) * 4 + (c >> 2)) * 64 + (rr & 15) + 16 * (c & 3);
-            if (isl)
-                sl[slot] = nxt[i];
-            else
-                sr[slot] = nxt[i];
-        }
-        __syncthreads();
-        if (q0 + GK < p1) fetch(q0 + GK);
-#pragma unroll
-        for (int st = 0; st < 4; st += 2) {
-            const v4s a0 = sl[(w * 4 + st) * 64 + lane];
-            const v4s a1 = sl[(w * 4 + st + 1) * 64 + lane];
-            rsum += (from_bf16((uint16_t)a0.x) + from_bf16((uint16_t)a0.y)) +
-                    (from_bf16((uint16_t)a0.z) + from_bf16((uint16_t)a0.w));
-            rsum += (from_bf16((uint16_t)a1.x) + from_bf16((uint16_t)a1.y)) +
-                    (from_bf16((uint16_t)a1.z) + from_bf16((uint16_t)a1.w));
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                acc[t] = mfma2(a0, a1, sr[(t * 4 + st) * 64 + lane], sr[(t * 4 + st + 1) * 64 + lane],
-                               acc[t]);
-        }
-    }
-    // row sums of L (the bias gradient when L = dZ): lane (row, g) holds a quarter of row
-    // 16 w + row; the four quarters are added across g
-    rsum += __shfl_xor(rsum, 16, 64);
-    rsum += __shfl_xor(rsum, 32, 64);
-    if (rowpart && lane < 16) rowpart[(int64_t)blockIdx.x * 64 + 16 * w + lane] = rsum;
-    // acc[t] holds output rows 16 w + 4 g + j, column 16 t + (lane & 15)
-    const int g = lane >> 4, col = lane & 15;
-    float* out = part + (int64_t)blockIdx.x * 64 * (16 * NT);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        out[(16 * w + 4 * g + 0) * (16 * NT) + 16 * t + col] = acc[t].x;
-        out[(16 * w + 4 * g + 1) * (16 * NT) + 16 * t + col] = acc[t].y;
-        out[(16 * w + 4 * g + 2) * (16 * NT) + 16 * t + col] = acc[t].z;
-        out[(16 * w + 4 * g + 3) * (16 * NT) + 16 * t + col] = acc[t].w;
-    }
-}
-
-// out[e] += sum_c part[c][e] in a fixed order: 64 elements per block, wavefront w summing
-// chunks w, w + 4, ..., then the four sums added in order
-// Sum over the nchunk partials of element e: SUM_WAVES wavefronts of the block share the
-// chunks (chunk c to wavefront c mod SUM_WAVES), each with four independent accumulators so
-// that its loads are in flight together, then the wavefronts' sums are added in a fixed order.
+// Every gradient += the sum of its nb partials, in a fixed order: 64 elements per block, whose
+// SUM_WAVES wavefronts share the partials (partial c to wavefront c mod SUM_WAVES), each with
+// four independent accumulators so that its loads are in flight together, then the wavefronts'
+// sums are added in order.  The first layer's weights go from the GPU's K order to the natural
+// one (padding slots are dropped).
 constexpr int SUM_WAVES = 16;
 constexpr int SUM_THREADS = 64 * SUM_WAVES;
 
-__device__ __forceinline__ float sum_chunks(const float* __restrict__ part, int64_t nchunk,
-                                            int64_t n, int64_t e)
+template <int KT, int DEPTH>
+__global__ __launch_bounds__(SUM_THREADS) void k_nrf_sums(const NrfArgs a,
+                                                          const float* __restrict__ part, int nb)
 {
+    constexpr int N = 16 * KT, n = part_floats(N, DEPTH);
     __shared__ float sh[SUM_WAVES][64];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    int e = blockIdx.x * 64 + l;
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
     if (e < n) {
-        int64_t c = w;
-        for (; c + 3 * SUM_WAVES < nchunk; c += 4 * SUM_WAVES) {
-            a0 += part[c * n + e];
-            a1 += part[(c + SUM_WAVES) * n + e];
-            a2 += part[(c + 2 * SUM_WAVES) * n + e];
-            a3 += part[(c + 3 * SUM_WAVES) * n + e];
+        const float* p = part + e;
+        int c = w;
+        for (; c + 3 * SUM_WAVES < nb; c += 4 * SUM_WAVES) {
+            a0 += p[(int64_t)c * n];
+            a1 += p[(int64_t)(c + SUM_WAVES) * n];
+            a2 += p[(int64_t)(c + 2 * SUM_WAVES) * n];
+            a3 += p[(int64_t)(c + 3 * SUM_WAVES) * n];
         }
-        for (; c < nchunk; c += SUM_WAVES) a0 += part[c * n + e];
+        for (; c < nb; c += SUM_WAVES) a0 += p[(int64_t)c * n];
     }
     sh[w][l] = (a0 + a1) + (a2 + a3);
     __syncthreads();
-    float t = 0.0f;
+    if (threadIdx.x >= 64 || e >= n) return;
+    float sum = 0.0f;
 #pragma unroll
-    for (int i = 0; i < SUM_WAVES; ++i) t += sh[i][l];
-    return t;
-}
-
-__global__ __launch_bounds__(SUM_THREADS) void k_sum_parts(const float* __restrict__ part,
-                                                           int64_t nchunk, int64_t n,
-                                                           float* __restrict__ out)
-{
-    const int64_t e = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-    const float s = sum_chunks(part, nchunk, n, e);
-    if (threadIdx.x < 64 && e < n) out[e] += s;
-}
-
-// The same for the first layer's weights, whose K dimension the GPU holds in its own encoding
-// order: out[m][natural_feature(i)] += sum_c part[c][m][i]; padding slots are dropped.
-template <int KT>
-__global__ __launch_bounds__(SUM_THREADS) void k_sum_parts_in(const float* __restrict__ part,
-                                                      int64_t nchunk, int n_freq,
-                                                      float* __restrict__ out)
-{
-    constexpr int N = 16 * KT;
-    const int e = blockIdx.x * 64 + (threadIdx.x & 63);
-    const float s = sum_chunks(part, nchunk, W * N, e);
-    if (threadIdx.x >= 64 || e >= W * N) return;
-    const int m = e / N, nf = natural_feature<KT>(e % N, n_freq);
-    if (nf < 0) return;
-    out[m * N + nf] += s;
+    for (int i = 0; i < SUM_WAVES; ++i) sum += sh[i][l];
+    if (e < W * N) {
+        const int nf = natural_feature<KT>(e % N, a.n_freq);
+        if (nf >= 0) a.g_w_in[e / N * N + nf] += sum;
+        return;
+    }
+    e -= W * N;
+    if (e < (DEPTH - 1) * W * W) {
+        a.g_w_hid[e] += sum;
+        return;
+    }
+    e -= (DEPTH - 1) * W * W;
+    if (e < W)
+        a.g_b_in[e] += sum;
+    else if (e < DEPTH * W)
+        a.g_b_hid[e - W] += sum;
+    else if (e < DEPTH * W + W)
+        a.g_w_out[e - DEPTH * W] += sum;
+    else
+        a.g_b_out[0] += sum;
 }
 
 __global__ __launch_bounds__(256) void k_to_bf16(const float* __restrict__ in,
@@ -269,116 +353,33 @@ __global__ __launch_bounds__(256) void k_to_bf16(const float* __restrict__ in,
         out[i] = to_bf16(in[i]);
 }
 
+int grad_blocks(int64_t rounds) { return (int)(rounds < MAX_BLOCKS ? rounds : MAX_BLOCKS); }
+
+template <int KT, int DEPTH>
+void launch_grad_t(const NrfArgs& a, const NrfGrids& gs, float* part, hipStream_t s)
+{
+    const int nb = grad_blocks(gs.round0[gs.n]);
+    hipLaunchKernelGGL((k_nrf_grad<KT, DEPTH>), dim3((unsigned)nb), dim3(256), 0, s, a, gs, part);
+    hipLaunchKernelGGL((k_nrf_sums<KT, DEPTH>),
+                       dim3((unsigned)((part_floats(16 * KT, DEPTH) + 63) / 64)), dim3(SUM_THREADS), 0,
+                       s, a, part, nb);
+}
+
 }  // namespace
-
-template <int KT, int DEPTH>
-void chain_blocks_t(const NrfArgs& a, int64_t np, unsigned* nb)
-{
-    (void)a;
-    *nb = nrfcore::blocks_for_tiles(k_nrf_chain<KT, DEPTH>, np / 16);
-}
-
-template <int KT, int DEPTH>
-void launch_chain_t(const NrfArgs& a, const NrfWork& w, unsigned nb, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_nrf_chain<KT, DEPTH>), dim3(nb), dim3(256), 0, s, a, w);
-}
 
 int nrf_max_bands(int in_pad) { return in_pad == 64 ? max_bands<4>() : max_bands<8>(); }
 
-size_t nrf_part_floats(int64_t P, int in_pad)
+size_t nrf_part_floats(int64_t rounds, int in_pad, int depth)
 {
-    const int64_t gemm = ((P + GPB - 1) / GPB) * W * ((in_pad > W ? in_pad : W) + 1);
-    // the chain kernel's output-layer partials: W + 1 per wavefront, at most np/16 + 3 of them
-    // for each grid of a call
-    const int64_t rows = (int64_t)(W + 1) * (P / 16 + 4 * GM_MAX_GRIDS);
-    return (size_t)(gemm > rows ? gemm : rows);
+    const int nb = grad_blocks(rounds);
+    return (size_t)(nb > 0 ? nb : 1) * part_floats(in_pad, depth);
 }
 
-unsigned nrf_chain_blocks(const NrfArgs& a, int64_t np)
+hipError_t launch_nrf_backward(const NrfArgs& a, const NrfGrids& gs, float* part, hipStream_t s)
 {
-    unsigned nb = 0;
-    switch ((a.in_pad >> 4) * 8 + a.depth) {
-    case 4 * 8 + 1: chain_blocks_t<4, 1>(a, np, &nb); break;
-    case 4 * 8 + 2: chain_blocks_t<4, 2>(a, np, &nb); break;
-    case 4 * 8 + 3: chain_blocks_t<4, 3>(a, np, &nb); break;
-    case 4 * 8 + 4: chain_blocks_t<4, 4>(a, np, &nb); break;
-    case 8 * 8 + 1: chain_blocks_t<8, 1>(a, np, &nb); break;
-    case 8 * 8 + 2: chain_blocks_t<8, 2>(a, np, &nb); break;
-    case 8 * 8 + 3: chain_blocks_t<8, 3>(a, np, &nb); break;
-    case 8 * 8 + 4: chain_blocks_t<8, 4>(a, np, &nb); break;
-    default: break;
-    }
-    return nb;
-}
-
-// One chain launch per grid, each writing its points' columns of the shared workspace and its
-// wavefronts' output-layer partials; then the output layer's sums and, once over all the
-// points, the layers' weight-gradient GEMMs and sums.
-hipError_t launch_nrf_backward_grids(const NrfArgs* as, int n, const NrfWork& w, hipStream_t s)
-{
-    const NrfArgs& a = as[0];
-    unsigned nb[GM_MAX_GRIDS];
-    int64_t np[GM_MAX_GRIDS], totw = 0;
-    for (int k = 0; k < n; ++k) {
-        np[k] = ((as[k].n_points + 15) / 16) * 16;
-        nb[k] = np[k] > 0 ? nrf_chain_blocks(as[k], np[k]) : 0;
-        if (np[k] > 0 && nb[k] == 0) return hipErrorInvalidValue;
-        totw += (int64_t)nb[k] * 4;
-    }
-    if (totw == 0) return hipSuccess;
-    int64_t p0 = 0, wave0 = 0;
-    for (int k = 0; k < n; ++k) {
-        if (np[k] == 0) continue;
-        NrfWork wk = w;
-        wk.p0 = p0;
-        wk.np = np[k];
-        wk.wave0 = wave0;
-        wk.nwaves_total = totw;
-        const NrfArgs& ak = as[k];
-        GM_NRF_DISPATCH(launch_chain_t, ak, wk, nb[k], s)
-        p0 += np[k];
-        wave0 += (int64_t)nb[k] * 4;
-    }
-    // the output layer's gradient from the chain kernels' per-wavefront partials (the layer
-    // GEMMs below reuse the partial buffer after these sums)
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(SUM_THREADS), 0, s, w.part, totw, (int64_t)W,
-                       a.g_w_out);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(SUM_THREADS), 0, s, w.part + totw * W, totw,
-                       (int64_t)1, a.g_b_out);
-    const int64_t nchunk = (w.P + GPB - 1) / GPB;
-    for (int l = 0; l < a.depth; ++l) {
-        const int N = l == 0 ? a.in_pad : W;
-        float* dst = l == 0 ? a.g_w_in : a.g_w_hid + (int64_t)(l - 1) * W * W;
-        float* dbias = l == 0 ? a.g_b_in : a.g_b_hid + (int64_t)(l - 1) * W;
-        // block row sums of dZ_l (the bias gradient) after the GEMM partials
-        float* rowpart = w.part + nchunk * W * N;
-        if (N == 128)
-            hipLaunchKernelGGL(k_gemm_nt_rows<8>, dim3((unsigned)nchunk), dim3(256), 0, s, w.dz[l],
-                               w.a[l], w.P, w.part, rowpart);
-        else
-            hipLaunchKernelGGL(k_gemm_nt_rows<4>, dim3((unsigned)nchunk), dim3(256), 0, s, w.dz[l],
-                               w.a[l], w.P, w.part, rowpart);
-        const int64_t ne = (int64_t)W * N;
-        const dim3 grid((unsigned)((ne + 63) / 64));
-        if (l > 0)
-            hipLaunchKernelGGL(k_sum_parts, grid, dim3(SUM_THREADS), 0, s, w.part, nchunk, ne, dst);
-        else if (N == 64)
-            hipLaunchKernelGGL(k_sum_parts_in<4>, grid, dim3(SUM_THREADS), 0, s, w.part, nchunk,
-                               a.n_freq, dst);
-        else
-            hipLaunchKernelGGL(k_sum_parts_in<8>, grid, dim3(SUM_THREADS), 0, s, w.part, nchunk,
-                               a.n_freq, dst);
-        hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(SUM_THREADS), 0, s, rowpart, nchunk, (int64_t)W,
-                           dbias);
-    }
+    if (gs.round0[gs.n] <= 0) return hipSuccess;
+    GM_NRF_DISPATCH(launch_grad_t, a, gs, part, s)
     return hipGetLastError();
-}
-
-hipError_t launch_nrf_backward(const NrfArgs& a, const NrfWork& w, hipStream_t s)
-{
-    if (a.n_points <= 0) return hipSuccess;
-    return launch_nrf_backward_grids(&a, 1, w, s);
 }
 
 hipError_t launch_to_bf16(const float* in, uint16_t* out, int64_t n, hipStream_t s)

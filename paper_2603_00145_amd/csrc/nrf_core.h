@@ -48,11 +48,9 @@ __device__ __forceinline__ v4f mfma2(v4s a0, v4s a1, v4s b0, v4s b1, v4f c)
 // +inf for very negative z, whose reciprocal is 0, the right limit
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
-__device__ __forceinline__ float dsilu(float z)
-{
-    const float s = sigm(z);
-    return s * (1.0f + z * (1.0f - s));
-}
+// SiLU'(z) from z and its sigmoid
+__device__ __forceinline__ float dsilu(float z, float s) { return s * (1.0f + z * (1.0f - s)); }
+__device__ __forceinline__ float dsilu(float z) { return dsilu(z, sigm(z)); }
 
 // World coordinate of voxel (vx, vy, vz): binary64 without contraction (hipcc fuses a * b + c
 // by default, the pragma stops it here), rounded once to binary32.
@@ -125,17 +123,11 @@ struct Lds {
     v4s w_in[4 * KT * 64];                                 // [o][t][lane], GPU encoding order
     v4s w_hid[(DEPTH > 1 ? DEPTH - 1 : 1) * 16 * 64];      // [l][o][t][lane]
 };
-// the backward also needs W_l^T as A operand: [l][i][o][lane], lane (g, row) holding
-// W_l[16 o + 4 g + j][16 i + row]
-template <int KT, int DEPTH>
-struct LdsChain {
-    Lds<KT, DEPTH> f;
-    v4s w_hid_t[(DEPTH > 1 ? DEPTH - 1 : 1) * 16 * 64];
-};
-
 // Stages the weights (every thread of the block takes part; ends with a block barrier).
-template <int KT, int DEPTH>
-__device__ void load_weights(const NrfArgs& a, Lds<KT, DEPTH>& s, v4s* w_hid_t = nullptr)
+// SWZ: within an operand the upper lanes' quads of the hidden layers are stored at lane ^ 4, so that
+// the transposing reads of the backward find 16 quads of every lane group in different banks too.
+template <int KT, int DEPTH, bool SWZ = false>
+__device__ void load_weights(const NrfArgs& a, Lds<KT, DEPTH>& s)
 {
     for (int e = threadIdx.x; e < 4 * KT * 64; e += blockDim.x) {
         const int lane = e & 63, t = (e >> 6) % KT, o = (e >> 6) / KT;
@@ -154,55 +146,61 @@ __device__ void load_weights(const NrfArgs& a, Lds<KT, DEPTH>& s, v4s* w_hid_t =
         const int lane = e & 63, t = (e >> 6) & 3, o = (e >> 8) & 3, l = e >> 10;
         const int g = lane >> 4, row = lane & 15;
         const uint16_t* Wl = a.w_hid + l * W * W;
-        short v[4], vt[4];
+        short v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[j] = (short)Wl[(16 * o + row) * W + 16 * t + 4 * g + j];
-            vt[j] = (short)Wl[(16 * t + 4 * g + j) * W + 16 * o + row];
-        }
-        s.w_hid[e] = v4s{v[0], v[1], v[2], v[3]};
-        if (w_hid_t) w_hid_t[e] = v4s{vt[0], vt[1], vt[2], vt[3]};
+        for (int j = 0; j < 4; ++j) v[j] = (short)Wl[(16 * o + row) * W + 16 * t + 4 * g + j];
+        s.w_hid[SWZ ? e ^ ((e >> 3) & 4) : e] = v4s{v[0], v[1], v[2], v[3]};
     }
     __syncthreads();
 }
 
-// voxel (x, y, z) of point p (grids hold < 2^31 voxels, so 32-bit division suffices)
-__device__ __forceinline__ void point_xyz(const NrfArgs& a, int64_t p, int* vx, int* vy, int* vz)
+// (x, y, z) of voxel v (grids hold < 2^31 voxels, so 32-bit division suffices)
+__device__ __forceinline__ void voxel_xyz(uint32_t v, uint32_t nx, uint32_t ny, int* vx, int* vy,
+                                          int* vz)
 {
-    uint32_t v = a.idx ? (uint32_t)a.idx[p] : (uint32_t)p;
-    const uint32_t nx = (uint32_t)a.nx, ny = (uint32_t)a.ny;
     const uint32_t q = v / nx;
     *vx = (int)(v - q * nx);
     const uint32_t r = q / ny;
     *vy = (int)(q - r * ny);
     *vz = (int)r;
 }
+__device__ __forceinline__ void point_xyz(const NrfArgs& a, int64_t p, int* vx, int* vy, int* vz)
+{
+    voxel_xyz(a.idx ? (uint32_t)a.idx[p] : (uint32_t)p, (uint32_t)a.nx, (uint32_t)a.ny, vx, vy, vz);
+}
 
-// Forward for the 16 points of a tile: Z (pre-activations) and the BF16 activations A
-// (register layout: o-tile x 4 features of point lane&15).
+// Forward for the 16 points of a tile, in the register layout o-tile x 4 features of point
+// lane & 15: the encoding (GPU order) and the BF16 activations, and for the backward SiLU' of
+// every pre-activation (not formed where it is not used).
 template <int KT, int DEPTH>
 struct Tile {
-    v4f z[DEPTH][4];
+    v4s enc[KT];
     v4s act[DEPTH][4];
+    v4f d[DEPTH][4];
+    __device__ __forceinline__ void layer(int l, int o, v4f z)
+    {
+        const v4f s = {sigm(z.x), sigm(z.y), sigm(z.z), sigm(z.w)};
+        act[l][o] = pack4(z.x * s.x, z.y * s.y, z.z * s.z, z.w * s.w);
+        d[l][o] = v4f{dsilu(z.x, s.x), dsilu(z.y, s.y), dsilu(z.z, s.z), dsilu(z.w, s.w)};
+    }
 };
-
-// Store a register tile (4 features x point p) feature-major into dst [features][P].
-__device__ __forceinline__ void store_fm(uint16_t* dst, int f, int64_t P, int64_t p, v4s v)
-{
-    dst[(int64_t)(f + 0) * P + p] = (uint16_t)v.x;
-    dst[(int64_t)(f + 1) * P + p] = (uint16_t)v.y;
-    dst[(int64_t)(f + 2) * P + p] = (uint16_t)v.z;
-    dst[(int64_t)(f + 3) * P + p] = (uint16_t)v.w;
-}
 
 // Where tile_forward takes the layers' MFMA A operands from: the LDS stage, read at each use,
 // or the wavefront's registers (each lane its quad of every operand, 4 KT + 16 (DEPTH - 1)
 // quads, copied once from the stage; the per-tile LDS reads of the weights, 512 bytes per lane,
 // then disappear).
+// the lane's four biases of o-tile o of layer l
+__device__ __forceinline__ v4f global_bias(const NrfArgs& a, int l, int o)
+{
+    const int f = 16 * o + 4 * ((threadIdx.x >> 4) & 3);
+    const float* b = l == 0 ? a.b_in : a.b_hid + (l - 1) * W;
+    return v4f{b[f], b[f + 1], b[f + 2], b[f + 3]};
+}
 template <int KT, int DEPTH>
 struct WeightsLds {
     const Lds<KT, DEPTH>& s;
     int lane;
+    __device__ v4f bias(const NrfArgs& a, int l, int o) const { return global_bias(a, l, o); }
     __device__ v4s in(int o, int t) const { return s.w_in[(o * KT + t) * 64 + lane]; }
     __device__ v4s hid(int l, int o, int t) const
     {
@@ -220,52 +218,36 @@ struct WeightsReg {
 #pragma unroll
         for (int i = 0; i < (DEPTH - 1) * 16; ++i) w_hid[i] = s.w_hid[i * 64 + lane];
     }
+    __device__ v4f bias(const NrfArgs& a, int l, int o) const { return global_bias(a, l, o); }
     __device__ v4s in(int o, int t) const { return w_in[o * KT + t]; }
     __device__ v4s hid(int l, int o, int t) const { return w_hid[(l - 1) * 16 + o * 4 + t]; }
 };
 
-// With a workspace (w != NULL) the encoding (in the GPU order) and each layer's BF16
-// activations are written out feature-major as soon as they are formed (the backward needs
-// them for dW), so they need not stay live in registers.
 template <int KT, int DEPTH, typename WS>
 __device__ __forceinline__ void tile_forward_w(const NrfArgs& a, const WS& ws, const float x[3],
-                                               Tile<KT, DEPTH>& T, const NrfWork* w = nullptr,
-                                               int64_t p = 0)
+                                               Tile<KT, DEPTH>& T)
 {
-    const int lane = threadIdx.x & 63, g = lane >> 4;
-    v4s b0[KT];
-    encode<KT>(x, a.n_freq, b0);
-    if (w) {
-#pragma unroll
-        for (int t = 0; t < KT; ++t) store_fm(w->a[0], 16 * t + 4 * g, w->P, p, b0[t]);
-    }
+    encode<KT>(x, a.n_freq, T.enc);
     // layer 1
 #pragma unroll
     for (int o = 0; o < 4; ++o) {
-        const int f = 16 * o + 4 * g;
-        v4f acc = {a.b_in[f], a.b_in[f + 1], a.b_in[f + 2], a.b_in[f + 3]};   // bias as C
+        v4f acc = ws.bias(a, 0, o);   // bias as C
 #pragma unroll
         for (int t = 0; t < KT; t += 2)
-            acc = mfma2(ws.in(o, t), ws.in(o, t + 1), b0[t], b0[t + 1], acc);
-        T.z[0][o] = acc;
-        T.act[0][o] = pack4(silu(acc.x), silu(acc.y), silu(acc.z), silu(acc.w));
-        if (w && DEPTH > 1) store_fm(w->a[1], f, w->P, p, T.act[0][o]);
+            acc = mfma2(ws.in(o, t), ws.in(o, t + 1), T.enc[t], T.enc[t + 1], acc);
+        T.layer(0, o, acc);
     }
     // hidden layers
 #pragma unroll
     for (int l = 1; l < DEPTH; ++l) {
-        const float* bl = a.b_hid + (l - 1) * W;
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-            const int f = 16 * o + 4 * g;
-            v4f acc = {bl[f], bl[f + 1], bl[f + 2], bl[f + 3]};
+            v4f acc = ws.bias(a, l, o);
 #pragma unroll
             for (int t = 0; t < 4; t += 2)
                 acc = mfma2(ws.hid(l, o, t), ws.hid(l, o, t + 1), T.act[l - 1][t],
                             T.act[l - 1][t + 1], acc);
-            T.z[l][o] = acc;
-            T.act[l][o] = pack4(silu(acc.x), silu(acc.y), silu(acc.z), silu(acc.w));
-            if (w && l + 1 < DEPTH) store_fm(w->a[l + 1], f, w->P, p, T.act[l][o]);
+            T.layer(l, o, acc);
         }
     }
 }
@@ -273,11 +255,10 @@ __device__ __forceinline__ void tile_forward_w(const NrfArgs& a, const WS& ws, c
 // tile_forward_w with the weights read from the LDS stage at each use
 template <int KT, int DEPTH>
 __device__ __forceinline__ void tile_forward(const NrfArgs& a, const Lds<KT, DEPTH>& s, const float x[3],
-                                             Tile<KT, DEPTH>& T, const NrfWork* w = nullptr,
-                                             int64_t p = 0)
+                                             Tile<KT, DEPTH>& T)
 {
     const WeightsLds<KT, DEPTH> ws{s, (int)(threadIdx.x & 63)};
-    tile_forward_w<KT, DEPTH>(a, ws, x, T, w, p);
+    tile_forward_w<KT, DEPTH>(a, ws, x, T);
 }
 
 // The output layer as a 16-row MFMA A operand whose row 0 is w_out and the other rows zero:

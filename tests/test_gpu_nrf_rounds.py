@@ -1,0 +1,85 @@
+"""The field's backward at the edges of its work split: point counts around a tile of 16, a round
+of 64 and the launch's 512 blocks, for every number of K-tiles and layers the kernel is built for."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import nrf as onrf
+from paper_2603_00145_amd import _lib, api, inputs, nrf
+
+pytestmark = pytest.mark.gpu
+TOL_BF16 = 2e-2     # of the sum of the terms' magnitudes, as in the several-grids parity test
+
+
+def _flat(g, depth):
+    out = {"w_in": g["W"][0], "b_in": g["b"][0], "w_out": g["w_out"], "b_out": np.reshape(g["b_out"], 1)}
+    if depth > 1:
+        out["w_hid"] = np.stack([g["W"][l] for l in range(1, depth)])
+        out["b_hid"] = np.stack([g["b"][l] for l in range(1, depth)])
+    return out
+
+
+@pytest.mark.parametrize("n_freq", [6, 16])
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+@pytest.mark.parametrize("counts", [(1,), (64, 0, 17), (65, 63)])
+def test_counts_against_oracle(n_freq, depth, counts):
+    rng = np.random.default_rng(n_freq + 10 * depth + counts[0])
+    net = nrf.NRF(n_freq=n_freq, depth=depth, seed=4, zero_last=False)
+    grids = [inputs.stack_grid(v, 24, 6, 1.0, *inputs.random_rigid(rng, 2, 1, 24))
+             for v in ("axial", "coronal", "sagittal")[:len(counts)]]
+    dls = [rng.normal(size=g.shape).astype(np.float32) for g in grids]
+    idxs = [rng.choice(g.n_voxels, size=c, replace=False).astype(np.int32)
+            for g, c in zip(grids, counts)]
+    net.zero_grad()
+    _, scales = net.backward_grids(grids, [torch.from_numpy(d).cuda() for d in dls],
+                                   idxs=[torch.from_numpy(i).cuda() for i in idxs])
+    ref, mag = {}, {}
+    for g, d, i, sc in zip(grids, dls, idxs, scales):
+        z, rem = np.divmod(i.astype(np.int64), g.nx * g.ny)
+        y, x = np.divmod(rem, g.nx)
+        feats = onrf.encode(onrf.world_coords(np.stack([x, y, z], 1),
+                                              onrf.index_to_world(g.world_to_index)), n_freq, net.in_pad)
+        ds = d.reshape(-1)[i].astype(np.float64) * sc
+        for p in range(len(i)):
+            one = _flat(onrf.backward(net.weights_host(), feats[p:p + 1], ds[p:p + 1],
+                                      net.out_scale), depth)
+            for k, v in one.items():
+                ref[k] = ref.get(k, 0.0) + v
+                mag[k] = mag.get(k, 0.0) + np.abs(v)
+    for k, v in ref.items():
+        got = net.g[k].cpu().numpy().astype(np.float64).reshape(v.shape)
+        assert np.max(np.abs(got - v)) <= TOL_BF16 * np.max(mag[k]), k
+
+
+@pytest.mark.parametrize("points", [512 * 64, 512 * 64 + 1, 3 * 512 * 64 + 70])
+def test_many_rounds_equal_their_pieces(points):
+    """One call against calls over pieces of the point list: the same terms in another order of
+    the FP32 sums; and the same bits on every run."""
+    rng = np.random.default_rng(points)
+    grid = inputs.stack_grid("coronal", 80, 20, 1.0, *inputs.random_rigid(rng, 2, 1, 80))
+    net = nrf.NRF(n_freq=16, depth=3, seed=8, zero_last=False)
+    # of one sign, so that no sum cancels below the terms' rounding
+    dl = torch.from_numpy(np.abs(rng.normal(size=grid.shape)).astype(np.float32)).cuda()
+    idx = torch.from_numpy(rng.choice(grid.n_voxels, size=points, replace=False).astype(np.int32)).cuda()
+    net.zero_grad()
+    _, scale = net.backward(grid, dl, idx=idx)
+    one = {k: v.clone() for k, v in net.g.items()}
+    net.zero_grad()
+    net.backward(grid, dl, idx=idx)
+    assert all(torch.equal(v, one[k]) for k, v in net.g.items())
+    total = {k: torch.zeros_like(v, dtype=torch.float64) for k, v in net.g.items()}
+    # at the one call's scale: another would move the BF16 roundings of dZ
+    lib, net_s = _lib.load(), net.struct()
+    for c in idx.split(9000):
+        net.zero_grad()
+        c, grads = c.clone(), net.grads_struct()
+        _lib.check(lib.gm_nrf_backward(
+            ctypes.byref(net_s), ctypes.byref(_lib.grid_struct(grid)), ctypes.c_void_p(c.data_ptr()),
+            c.numel(), ctypes.c_void_p(dl.data_ptr()), float(scale), ctypes.byref(grads),
+            ctypes.c_void_p(net._ws.data_ptr()), net._ws.numel() * 4, api._stream()))
+        for k, v in net.g.items():
+            total[k] += v.double()
+    for k, v in total.items():
+        assert (one[k].double() - v).abs().max() <= 1e-5 * v.abs().max(), k
