@@ -177,11 +177,10 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
         for (int l = 0; l < DEPTH - 1; ++l)
 #pragma unroll
             for (int t = 0; t < 4; ++t) s.act[l][t * 256 + slot] = T.act[l][t];
-        // z_o of the lane's point, from lane group 0 to all four
-        v4s wo[4];                  // w_out as the MFMA operand of row 0
+        v4s wo[4];                  // w_out as load_wout's operand
 #pragma unroll
-        for (int o = 0; o < 4; ++o) wo[o] = row == 0 ? s.w_out[4 * o + g] : v4s{0, 0, 0, 0};
-        const float zo = __shfl(tile_output<KT, DEPTH>(a, T, wo), row, 64);
+        for (int o = 0; o < 4; ++o) wo[o] = (row & 3) == 0 ? s.w_out[4 * o + g] : v4s{0, 0, 0, 0};
+        const float zo = tile_output<KT, DEPTH>(a, T, wo);
         const float th = tanhf(zo);
         const float dzo = cur.valid ? cur.dl * gs.g[cur.k].scale * a.out_scale * (1.0f - th * th)
                                     : 0.0f;

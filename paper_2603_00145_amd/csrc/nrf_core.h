@@ -86,32 +86,32 @@ __device__ __forceinline__ int natural_feature(int i, int n_freq)
     return band < n_freq ? 3 + 6 * band + m : -1;
 }
 
-// The encoding of the lane's point, in the B operand layout of the K-tiles.
+// The encoding of the lane's point, in the B operand layout of the K-tiles.  Slots of bands past
+// n_freq hold any finite value: their weights are staged as zeros and their weight gradients
+// dropped (the lane groups of a band group that n_freq cuts are not masked, a band group past it
+// is left out).
 template <int KT>
 __device__ __forceinline__ void encode(const float x[3], int n_freq, v4s b0[KT])
 {
     const int g = (threadIdx.x >> 4) & 3;
-    const float xg = g == 0 ? x[0] : (g == 1 ? x[1] : x[2]);
-    const int nb = n_freq - g;          // band 4 q + g exists for 4 q < nb
+    float v[4 * KT];
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-        float v[4];
+    for (int c = 0; c < 4 * KT - 1; ++c) v[c] = 0.0f;
+    v[4 * KT - 1] = g == 0 ? x[0] : g == 1 ? x[1] : g == 2 ? x[2] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = 4 * t + j;
-            if (c == 4 * KT - 1) {
-                v[j] = g < 3 ? xg : 0.0f;
-            } else {
-                const int q = c / 6, m = c % 6;
-                const float phi = ldexpf(x[m % 3], 4 * q - 1 + g);   // exact power-of-two scaling
-                const float frac = phi - rintf(phi);                  // exact
-                // v_sin_f32 / v_cos_f32 take their argument in revolutions
-                const float sc = m < 3 ? __builtin_amdgcn_sinf(frac) : __builtin_amdgcn_cosf(frac);
-                v[j] = 4 * q < nb ? sc : 0.0f;
-            }
+    for (int q = 0; q < max_bands<KT>() / 4; ++q) {
+        if (q > 0 && 4 * q >= n_freq) continue;   // uniform
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float phi = ldexpf(x[a], 4 * q - 1 + g);        // exact power-of-two scaling
+            const float frac = phi - rintf(phi);                  // exact
+            // v_sin_f32 / v_cos_f32 take their argument in revolutions
+            v[6 * q + a] = __builtin_amdgcn_sinf(frac);
+            v[6 * q + 3 + a] = __builtin_amdgcn_cosf(frac);
         }
-        b0[t] = pack4(v[0], v[1], v[2], v[3]);
     }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) b0[t] = pack4(v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3]);
 }
 
 // Weights staged in LDS in MFMA A-operand order: operand (o, t) of a layer is 64 lanes x 4 BF16,
@@ -261,21 +261,22 @@ __device__ __forceinline__ void tile_forward(const NrfArgs& a, const Lds<KT, DEP
     tile_forward_w<KT, DEPTH>(a, ws, x, T);
 }
 
-// The output layer as a 16-row MFMA A operand whose row 0 is w_out and the other rows zero:
-// lane (g, 0) holds w_out[16 t + 4 g + j] of K-tile t.  Loaded once per wavefront.
+// The output layer as a 16-row MFMA A operand whose rows 0, 4, 8 and 12 are w_out and the other
+// rows zero: lane (g, row) of those rows holds w_out[16 t + 4 g + j] of K-tile t.  Loaded once
+// per wavefront.
 __device__ __forceinline__ void load_wout(const NrfArgs& a, v4s (&wo)[4])
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, row = lane & 15;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const v4s v = *reinterpret_cast<const v4s*>(a.w_out + 16 * t + 4 * g);
-        wo[t] = row == 0 ? v : v4s{0, 0, 0, 0};
+        wo[t] = (row & 3) == 0 ? v : v4s{0, 0, 0, 0};
     }
 }
 
 // output pre-activation z_o of the tile's point from the BF16 activations of the last layer,
-// on the matrix cores (wo from load_wout): row 0 of the product, held by lane group 0, is
-// w_out . a_D for the lane's point.  Valid in lane group 0 only (the other groups get b_out).
+// on the matrix cores (wo from load_wout): row 4 g of the product, held by lane group g, is
+// w_out . a_D for the lane's point.
 template <int KT, int DEPTH>
 __device__ __forceinline__ float tile_output(const NrfArgs& a, const Tile<KT, DEPTH>& T,
                                              const v4s (&wo)[4])

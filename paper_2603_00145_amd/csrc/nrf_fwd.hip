@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void k_nrf_forward(const NrfArgs a)
                             world_coord(a.m + 8, vx, vy, vz)};
         Tile<KT, DEPTH> T;
         tile_forward_w<KT, DEPTH>(a, wr, x, T);
-        const float zo = tile_output<KT, DEPTH>(a, T, wo);     // lane group 0
+        const float zo = tile_output<KT, DEPTH>(a, T, wo);
         if (valid && g == 0) {
             const int64_t v = ((int64_t)vz * a.ny + vy) * a.nx + vx;
             a.out[v] += a.out_scale * tanhf(zo);
