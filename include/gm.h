@@ -425,6 +425,19 @@ gm_status gm_adam_step(float* param, const float* grad, float* m, float* v, int6
                        double lr, double beta1, double beta2, double eps, int32_t step,
                        gm_stream stream);
 
+/* gm_adam_step on count tensors (at most GM_MAX_TENSORS) of n[k] elements in one launch, each
+ * also written as BF16 (gm_f32_to_bf16) to bf16[k] unless that is NULL: the same bits as the
+ * separate calls.  params, grads, m, v, bf16, n: [host] arrays of count (device pointers and
+ * sizes); tensors do not overlap. */
+#define GM_MAX_TENSORS 16
+gm_status gm_adam_many(int32_t count, float* const* params, const float* const* grads,
+                       float* const* m, float* const* v, uint16_t* const* bf16, const int64_t* n,
+                       double lr, double beta1, double beta2, double eps, int32_t step,
+                       gm_stream stream);
+
+/* Fill count tensors (at most GM_MAX_TENSORS) of n[k] floats with zeros in one launch. */
+gm_status gm_zero_many(int32_t count, float* const* tensors, const int64_t* n, gm_stream stream);
+
 /* Devoxelization initialisation (Sec. 3.1; Fig. 1b): fill n = g^3 Gaussians (g >= 1) laid on
  * the cell centres of a uniform g^3 grid over [-1,1]^3 (Gaussian i = (iz g + iy) g + ix), with
  * identity rotation, isotropic log-scale ln(h/2) (h = 2/g) and intensity

@@ -141,6 +141,11 @@ _SIGS = [
     ("gm_adam_step", ctypes.c_int, [P, P, P, P, ctypes.c_int64, ctypes.c_double,
                                      ctypes.c_double, ctypes.c_double, ctypes.c_double,
                                      ctypes.c_int32, P]),
+    ("gm_adam_many", ctypes.c_int, [ctypes.c_int32] + [ctypes.POINTER(P)] * 5 +
+                                    [ctypes.POINTER(ctypes.c_int64)] + [ctypes.c_double] * 4 +
+                                    [ctypes.c_int32, P]),
+    ("gm_zero_many", ctypes.c_int, [ctypes.c_int32, ctypes.POINTER(P),
+                                    ctypes.POINTER(ctypes.c_int64), P]),
     ("gm_mse", ctypes.c_int, [P, P, ctypes.c_int64, P, P, P]),
     ("gm_index_to_world", ctypes.c_int, [ctypes.POINTER(GmGrid), ctypes.POINTER(ctypes.c_double)]),
     ("gm_nrf_forward", ctypes.c_int, [ctypes.POINTER(GmNrf), ctypes.POINTER(GmGrid), P, P]),

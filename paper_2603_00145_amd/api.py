@@ -416,6 +416,40 @@ def adam_step(p: torch.Tensor, g: torch.Tensor, m: torch.Tensor, v: torch.Tensor
                               float(beta2), float(eps), int(step), _stream()))
 
 
+MAX_TENSORS = 16      # GM_MAX_TENSORS
+
+
+def _sizes(ts):
+    return (ctypes.c_int64 * len(ts))(*[t.numel() for t in ts])
+
+
+def adam_step_many(ps, gs, ms, vs, bfs, lr: float, step: int, beta1: float = 0.9,
+                   beta2: float = 0.999, eps: float = 1e-8):
+    """adam_step on every (p, g, m, v), and p's BF16 bits into its entry of bfs (int16, or None),
+    in one launch per MAX_TENSORS tensors; same bits as the separate calls."""
+    for ts, nm in ((ps, "param"), (gs, "grad"), (ms, "m"), (vs, "v")):
+        for t in ts:
+            _need(t, torch.float32, nm)
+    for k in range(0, len(ps), MAX_TENSORS):
+        s = slice(k, k + MAX_TENSORS)
+        ptrs = [ptr_array([t.data_ptr() for t in ts[s]]) for ts in (ps, gs, ms, vs)]
+        bf = ptr_array([0 if t is None else t.data_ptr() for t in bfs[s]])
+        check(load().gm_adam_many(len(ps[s]), *ptrs, bf, _sizes(ps[s]), float(lr), float(beta1),
+                                  float(beta2), float(eps), int(step), _stream()))
+
+
+def zero_many(ts):
+    """Zeros into every tensor, in one launch per MAX_TENSORS of them."""
+    if any(not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous() for t in ts):
+        for t in ts:
+            t.zero_()
+        return
+    for k in range(0, len(ts), MAX_TENSORS):
+        s = ts[k:k + MAX_TENSORS]
+        check(load().gm_zero_many(len(s), ptr_array([t.data_ptr() for t in s]), _sizes(s),
+                                  _stream()))
+
+
 def mse(vol: torch.Tensor, ref: torch.Tensor):
     _need(vol, torch.float32, "vol")
     _need(ref, torch.float32, "ref")

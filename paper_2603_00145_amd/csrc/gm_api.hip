@@ -1232,6 +1232,64 @@ gm_status gm_adam_step(float* param, const float* grad, float* m, float* v, int6
     return GM_OK;
 }
 
+gm_status gm_adam_many(int32_t count, float* const* params, const float* const* grads,
+                       float* const* m, float* const* v, uint16_t* const* bf16, const int64_t* n,
+                       double lr, double beta1, double beta2, double eps, int32_t step,
+                       gm_stream stream)
+{
+    g_err.clear();
+    if (count < 0 || count > GM_MAX_TENSORS)
+        return fail(GM_ERR_INVALID_ARGUMENT, "count outside [0, %d]", GM_MAX_TENSORS);
+    if (step < 1) return fail(GM_ERR_INVALID_ARGUMENT, "step must be >= 1");
+    if (!(beta1 >= 0.0 && beta1 < 1.0 && beta2 >= 0.0 && beta2 < 1.0) || !(eps >= 0.0) ||
+        !isfinite(lr) || !isfinite(eps))
+        return fail(GM_ERR_INVALID_ARGUMENT, "bad Adam hyperparameters");
+    if (count == 0) return GM_OK;
+    if (!params || !grads || !m || !v || !bf16 || !n)
+        return fail(GM_ERR_INVALID_ARGUMENT, "params / grads / m / v / bf16 / n NULL");
+    TensorList t;
+    memset(&t, 0, sizeof t);
+    t.count = count;
+    for (int k = 0; k < count; ++k) {
+        if (n[k] < 0) return fail(GM_ERR_INVALID_ARGUMENT, "n[%d] < 0", k);
+        t.n[k] = n[k];
+        if (n[k] == 0) continue;
+        REQ_PTR(params[k], "params[k]");
+        REQ_PTR(grads[k], "grads[k]");
+        REQ_PTR(m[k], "m[k]");
+        REQ_PTR(v[k], "v[k]");
+        t.p[k] = params[k];
+        t.g[k] = grads[k];
+        t.m[k] = m[k];
+        t.v[k] = v[k];
+        t.bf16[k] = bf16[k];
+    }
+    GM_HIP(launch_adam_many(t, adam_scalars(lr, beta1, beta2, eps, step),
+                            reinterpret_cast<hipStream_t>(stream)), "adam over tensors");
+    return GM_OK;
+}
+
+gm_status gm_zero_many(int32_t count, float* const* tensors, const int64_t* n, gm_stream stream)
+{
+    g_err.clear();
+    if (count < 0 || count > GM_MAX_TENSORS)
+        return fail(GM_ERR_INVALID_ARGUMENT, "count outside [0, %d]", GM_MAX_TENSORS);
+    if (count == 0) return GM_OK;
+    if (!tensors || !n) return fail(GM_ERR_INVALID_ARGUMENT, "tensors / n NULL");
+    TensorList t;
+    memset(&t, 0, sizeof t);
+    t.count = count;
+    for (int k = 0; k < count; ++k) {
+        if (n[k] < 0) return fail(GM_ERR_INVALID_ARGUMENT, "n[%d] < 0", k);
+        t.n[k] = n[k];
+        if (n[k] == 0) continue;
+        REQ_PTR(tensors[k], "tensors[k]");
+        t.p[k] = tensors[k];
+    }
+    GM_HIP(launch_zero_many(t, reinterpret_cast<hipStream_t>(stream)), "zero tensors");
+    return GM_OK;
+}
+
 gm_status gm_upsample_lattice(int32_t g_old, const gm_gaussians* old, int32_t g_new,
                               float* mean, float* quat, float* log_scale, float* logit,
                               gm_stream stream)

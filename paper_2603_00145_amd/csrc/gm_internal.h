@@ -270,6 +270,19 @@ hipError_t launch_mse(const float* a, const float* b, int64_t n, float* mse, voi
 // sqrt(1 - beta2^t)
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n,
                        const AdamScalars& c, hipStream_t s);
+// Several tensors of one optimiser in a launch: tensor k's blocks start at block0[k]
+struct TensorList {
+    int32_t count;
+    int32_t block0[GM_MAX_TENSORS + 1];
+    int64_t n[GM_MAX_TENSORS];
+    float* p[GM_MAX_TENSORS];
+    const float* g[GM_MAX_TENSORS];
+    float* m[GM_MAX_TENSORS];
+    float* v[GM_MAX_TENSORS];
+    uint16_t* bf16[GM_MAX_TENSORS];   // the updated parameters in BF16, or NULL
+};
+hipError_t launch_adam_many(TensorList& t, const AdamScalars& c, hipStream_t s);
+hipError_t launch_zero_many(TensorList& t, hipStream_t s);   // p = 0
 
 struct DevoxArgs {
     int32_t g;

@@ -96,6 +96,65 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float
     }
 }
 
+// Small networks' tensors (6 to 10 of 1 to 6e4 elements) updated, converted and cleared one
+// launch for all (a warm-start training step of 1024 patches: 205 us; with a launch for each of its
+// 10 Adam steps, 4 conversions and 10 clears, 241).
+constexpr int MANY_PER_BLOCK = 1024;    // elements, four per thread
+
+__device__ __forceinline__ int many_tensor(const TensorList& t)
+{
+    int k = 0;
+    while (k + 1 < t.count && (int)blockIdx.x >= t.block0[k + 1]) ++k;
+    return k;
+}
+
+__global__ __launch_bounds__(256) void k_adam_many(const TensorList t, const AdamScalars c)
+{
+    const int k = many_tensor(t);
+    float* __restrict__ p = t.p[k];
+    const float* __restrict__ g = t.g[k];
+    float* __restrict__ m = t.m[k];
+    float* __restrict__ v = t.v[k];
+    uint16_t* __restrict__ h = t.bf16[k];
+    const int64_t n = t.n[k], i0 = (int64_t)((int)blockIdx.x - t.block0[k]) * MANY_PER_BLOCK;
+#pragma unroll
+    for (int u = 0; u < MANY_PER_BLOCK / 256; ++u) {
+        const int64_t i = i0 + u * 256 + threadIdx.x;
+        if (i >= n) return;
+        float pi = p[i], mi = m[i], vi = v[i];
+        adam_elem(pi, mi, vi, g[i], c);
+        m[i] = mi;
+        v[i] = vi;
+        p[i] = pi;
+        if (h) h[i] = __builtin_bit_cast(uint16_t, (__bf16)pi);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_zero_many(const TensorList t)
+{
+    const int k = many_tensor(t);
+    float* __restrict__ p = t.p[k];
+    const int64_t n = t.n[k], i0 = (int64_t)((int)blockIdx.x - t.block0[k]) * MANY_PER_BLOCK;
+#pragma unroll
+    for (int u = 0; u < MANY_PER_BLOCK / 256; ++u) {
+        const int64_t i = i0 + u * 256 + threadIdx.x;
+        if (i < n) p[i] = 0.0f;
+    }
+}
+
+// the launch's blocks, or 0 (nothing to do) or -1 (more than a grid holds)
+int64_t many_blocks(TensorList& t)
+{
+    int64_t nb = 0;
+    for (int k = 0; k < t.count; ++k) {
+        t.block0[k] = (int32_t)nb;
+        nb += (t.n[k] + MANY_PER_BLOCK - 1) / MANY_PER_BLOCK;
+        if (nb > 0x7fffffffLL) return -1;
+    }
+    t.block0[t.count] = (int32_t)nb;
+    return nb;
+}
+
 unsigned red_blocks(int64_t n)
 {
     int64_t b = (n + RED_THREADS - 1) / RED_THREADS;
@@ -145,6 +204,22 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n,
     int64_t nb = (n + 255) / 256;
     if (nb > 8192) nb = 8192;
     hipLaunchKernelGGL(k_adam, dim3((unsigned)nb), dim3(256), 0, s, p, g, m, v, n, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_adam_many(TensorList& t, const AdamScalars& c, hipStream_t s)
+{
+    const int64_t nb = many_blocks(t);
+    if (nb < 0) return hipErrorInvalidValue;
+    if (nb > 0) hipLaunchKernelGGL(k_adam_many, dim3((unsigned)nb), dim3(256), 0, s, t, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero_many(TensorList& t, hipStream_t s)
+{
+    const int64_t nb = many_blocks(t);
+    if (nb < 0) return hipErrorInvalidValue;
+    if (nb > 0) hipLaunchKernelGGL(k_zero_many, dim3((unsigned)nb), dim3(256), 0, s, t);
     return hipGetLastError();
 }
 

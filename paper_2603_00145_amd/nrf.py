@@ -80,8 +80,7 @@ class NRF:
                                     ctypes.c_void_p(out.data_ptr()), api._stream()))
 
     def zero_grad(self):
-        for t in self.g.values():
-            t.zero_()
+        api.zero_many(list(self.g.values()))
 
     def backward(self, grid, dl_dr: torch.Tensor, idx: Optional[torch.Tensor] = None,
                  n_sample: Optional[int] = None, generator: Optional[torch.Generator] = None):
@@ -145,9 +144,8 @@ class NRF:
 
     def adam_step(self, lr: float = 1e-4):
         self.step_no += 1
-        for k in self.p:
-            api.adam_step(self.p[k], self.g[k], self.m[k], self.v[k], lr, self.step_no)
-        self.sync_bf16()
+        ts = [[d.get(k) for k in self.p] for d in (self.p, self.g, self.m, self.v, self.bf)]
+        api.adam_step_many(*ts, lr, self.step_no)
 
     def weights_host(self):
         """BF16-valued weights as float64 numpy arrays (for the oracle)."""

@@ -120,13 +120,11 @@ class WarmStartNet:
         return loss[0]
 
     def train_step(self, patches, s0, logit0, sig_t, logit_t, lr=1e-3):
-        for t in self.g.values():
-            t.zero_()
+        api.zero_many(list(self.g.values()))
         loss = self.backward(patches, s0, logit0, sig_t, logit_t)
         self.step_no += 1
-        for k in self.p:
-            api.adam_step(self.p[k], self.g[k], self.m[k], self.v[k], lr, self.step_no)
-        self.sync_bf16()
+        ts = [[d.get(k) for k in self.p] for d in (self.p, self.g, self.m, self.v, self.bf)]
+        api.adam_step_many(*ts, lr, self.step_no)
         return loss
 
     def weights_host(self):
