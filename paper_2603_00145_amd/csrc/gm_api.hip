@@ -108,13 +108,11 @@ int64_t grid_tiles(const gm_grid& g)
 
 // scratch layout of gm_bins
 struct BinScratch {
-    int64_t* offsets;   // [n_grids * n + 1]
-    void* scan_ws;
+    BinChunks chunks;
     uint32_t* keys0;
     uint32_t* keys1;
     uint32_t* vals0;
     void* radix_ws;
-    BinReport* report;
     uint32_t* tile_box;  // [n_grids * n][3]
     int4* cells;         // [n]: the Gaussians' cells (block query)
     size_t bytes;
@@ -126,14 +124,15 @@ BinScratch scratch_layout(char* base, int64_t n, int32_t n_grids, int64_t cap)
     size_t o = 0;
     const int64_t m = (int64_t)n_grids * n;
     auto take = [&](size_t b) { char* p = base ? base + o : nullptr; o += align256(b); return p; };
-    s.offsets = reinterpret_cast<int64_t*>(take((size_t)(m + 1) * 8));
-    s.scan_ws = take(scan_workspace_bytes(m));
+    const size_t chunks = (size_t)n_grids * ((n + BIN_CHUNK - 1) / BIN_CHUNK);
+    s.chunks.tiles = reinterpret_cast<unsigned long long*>(take(chunks * 8));
+    s.chunks.volume = reinterpret_cast<unsigned long long*>(take(chunks * 8));
+    s.chunks.flags = reinterpret_cast<uint32_t*>(take(chunks * 4));
     const int64_t c = cap > 0 ? cap : 1;
     s.keys0 = reinterpret_cast<uint32_t*>(take((size_t)c * 4));
     s.keys1 = reinterpret_cast<uint32_t*>(take((size_t)c * 4));
     s.vals0 = reinterpret_cast<uint32_t*>(take((size_t)c * 4));
     s.radix_ws = take(radix_workspace_bytes(c));
-    s.report = reinterpret_cast<BinReport*>(take(sizeof(BinReport)));
     s.tile_box = reinterpret_cast<uint32_t*>(take((size_t)(m > 0 ? m : 1) * 12));
     s.cells = reinterpret_cast<int4*>(take((size_t)(n > 0 ? n : 1) * 16));
     s.bytes = o;
@@ -398,12 +397,8 @@ gm_status gm_bin(const gm_gaussians* g, const gm_grid* grids, int32_t n_grids,
     bins->n_pairs = -1;
 
     const int64_t n = g->n;
-    const int64_t m = (int64_t)n_grids * n;
     BinScratch sc = scratch_layout(reinterpret_cast<char*>(bins->scratch), n, n_grids,
                                    bins->capacity_pairs);
-    static_assert(sizeof(BinReport) % 4 == 0, "report block is cleared as u32 words");
-    GM_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(sc.report), 0u, sizeof(BinReport) / 4, s),
-           "clear report");
     pa.n = n;
     pa.n_grids = n_grids;
     pa.cutoff = cutoff;
@@ -416,26 +411,46 @@ gm_status gm_bin(const gm_gaussians* g, const gm_grid* grids, int32_t n_grids,
     pa.logit = g->logit;
     pa.records = bins->records;
     pa.tile_count = bins->tile_count;
-    pa.box_volume = sc.report->box_volume;
-    pa.flags = sc.report->flags;
+    pa.chunks = sc.chunks;
     pa.grid_grads = bins->grid_grads;
     pa.tile_box = sc.tile_box;
     GM_HIP(launch_preprocess(pa, s), "preprocess");
-    GM_HIP(launch_scan_i32_to_i64(bins->tile_count, sc.offsets, m, sc.scan_ws, s), "scan");
 
     // the report lands in a pinned host block of this thread (allocated once, kept for the
-    // life of the process), written by the report kernel itself
+    // life of the process), written by the kernel that forms it
     static thread_local BinReport* t_report = nullptr;
     if (!t_report) {
         void* hp = nullptr;
         GM_HIP(hipHostMalloc(&hp, sizeof(BinReport), hipHostMallocDefault), "pinned report block");
         t_report = static_cast<BinReport*>(hp);
     }
-    GM_HIP(launch_bin_report(sc.report, sc.offsets, n, bins->box_volume, n_grids, t_report, s),
-           "report");
+    int bits = 0;
+    while ((int64_t(1) << bits) < T) ++bits;
+    const int passes = (bits + 7) / 8;
+    uint32_t* pg = reinterpret_cast<uint32_t*>(bins->pair_gauss);
+    // arrange the ping-pong buffers so the last pass lands in pair_gauss
+    uint32_t *k_in = sc.keys0, *k_alt = sc.keys1;
+    uint32_t *v_in = (passes & 1) ? sc.vals0 : pg, *v_alt = (passes & 1) ? pg : sc.vals0;
+    EmitArgs ea;
+    memset(&ea, 0, sizeof ea);
+    ea.n = n;
+    ea.n_grids = n_grids;
+    ea.tile_box = sc.tile_box;
+    ea.tile_count = bins->tile_count;
+    ea.chunks = sc.chunks;
+    ea.capacity = bins->capacity_pairs;
+    ea.keys = k_in;
+    ea.vals = v_in;
+    for (int k = 0; k < n_grids; ++k) ea.g[k] = pa.g[k];
     // The host waits for the report only (an event after it, one per device and thread); the
-    // pair emission is enqueued first, sized by the Gaussians and guarded by the capacity on
-    // the device, so that the GPU emits while the host wakes up.
+    // pair emission, sized by the Gaussians and guarded by the capacity on the device, is
+    // enqueued with it or after it, so that the GPU emits while the host wakes up.
+    const int64_t per_grid = (n + BIN_CHUNK - 1) / BIN_CHUNK;
+    const bool scanned = n == 0 || per_grid * n_grids > BIN_FEW_CHUNKS;
+    if (scanned)
+        GM_HIP(launch_bin_scan(sc.chunks, per_grid, n_grids, bins->box_volume, t_report, s), "scan");
+    else
+        GM_HIP(launch_emit(ea, false, bins->box_volume, t_report, s), "emit");
     static thread_local hipEvent_t t_done[64] = {};
     int dev = 0;
     if (s) {
@@ -456,27 +471,7 @@ gm_status gm_bin(const gm_gaussians* g, const gm_grid* grids, int32_t n_grids,
         GM_HIP(ce, "report event");
     }
     GM_HIP(hipEventRecord(t_done[dev], s), "record report event");
-
-    int bits = 0;
-    while ((int64_t(1) << bits) < T) ++bits;
-    const int passes = (bits + 7) / 8;
-    uint32_t* pg = reinterpret_cast<uint32_t*>(bins->pair_gauss);
-    // arrange the ping-pong buffers so the last pass lands in pair_gauss
-    uint32_t *k_in = sc.keys0, *k_alt = sc.keys1;
-    uint32_t *v_in = (passes & 1) ? sc.vals0 : pg, *v_alt = (passes & 1) ? pg : sc.vals0;
-    {
-        EmitArgs ea;
-        memset(&ea, 0, sizeof ea);
-        ea.n = n;
-        ea.n_grids = n_grids;
-        ea.tile_box = sc.tile_box;
-        ea.offsets = sc.offsets;
-        ea.capacity = bins->capacity_pairs;
-        ea.keys = k_in;
-        ea.vals = v_in;
-        for (int k = 0; k < n_grids; ++k) ea.g[k] = pa.g[k];
-        GM_HIP(launch_emit(ea, s), "emit");
-    }
+    if (scanned) GM_HIP(launch_emit(ea, true, nullptr, nullptr, s), "emit");
     GM_HIP(hipEventSynchronize(t_done[dev]), "synchronise");
     const BinReport rep = *t_report;
     const int64_t total = rep.grid_start[n_grids];
@@ -493,11 +488,9 @@ gm_status gm_bin(const gm_gaussians* g, const gm_grid* grids, int32_t n_grids,
     }
 
     if (total > 0) {
-        int in_alt = 0;
-        GM_HIP(launch_radix_sort(k_in, v_in, k_alt, v_alt, total, bits, sc.radix_ws, &in_alt, s),
+        GM_HIP(launch_radix_sort(k_in, v_in, k_alt, v_alt, total, bits, sc.radix_ws,
+                                 bins->tile_start, T, s),
                "radix sort");
-        GM_HIP(launch_tile_ranges(in_alt ? k_alt : k_in, total, bins->tile_start, T, s),
-               "tile ranges");
     } else {
         GM_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(bins->tile_start), 0u, T + 1, s),
                "zero tile starts");
