@@ -10,19 +10,21 @@
 // with 16 parts; at three 128x128x32 stacks 258 against 105 us.)
 //
 // A wavefront walks its part in batches of 32: a lane loads one record and prepares that
-// Gaussian's piece (box intersect tile) in LDS.  Then the pieces are taken in list order.  A
+// Gaussian's piece (box intersect tile) in LDS.  Then the pieces are taken one pass after the
+// other, in an order that fills the passes (place_piece).  A
 // lane holds one (x, y) column of a piece's footprint and evaluates it on the tile's four
 // planes, so the in-plane part of the exponent is formed once per column.  The tile keeps a
 // column's four voxels side by side: a lane adds its column with one 16-byte read and one
 // 16-byte write whatever planes the piece reaches (a plane outside the box gets exactly 0).
-// What bounds it at the 256^3 workload is vector issue: about 50 instructions per pass, four of
-// them exponentials.  Evaluating only the planes a pass reaches (ten straight-line variants
+// What bounds it at the 256^3 workload is vector issue (89% busy; LDS 72%): about 50
+// instructions per pass, four of them exponentials.  474 us there, 494 for a 320^3 volume of 2M
+// Gaussians; with the pieces in list order and every piece added by itself 505 and 545.  Evaluating only the planes a pass reaches (ten straight-line variants
 // behind one branch) issued fewer but ran 4% slower, fetching the next pass's pieces one pass
 // ahead 2-5% slower, and padding the tile's rows to 17, 20 or 21 columns changed nothing (the
 // 16-byte accesses do not conflict).
 // Two consecutive pieces whose footprints sum to at most 64 columns share the wave (the first
-// piece's columns on the low lanes); the first piece's lanes add into the tile before the
-// second's, so every voxel's sum is formed in a fixed order and the result is the same on every
+// piece's columns on the low lanes).  Where no column is in both they are added at once, otherwise
+// the first piece's lanes add into the tile before the second's, so every voxel's sum is formed in a fixed order and the result is the same on every
 // run.
 //
 // With the paper's block query on a rotated grid (k_render_block, and k_render_field's MASK
@@ -233,6 +235,26 @@ __device__ __forceinline__ Pass load_pass(const Piece* pc, int j, int Fa, int la
     return q;
 }
 
+// Place of a batch's piece with a footprint of F columns (called by the batch's lanes, below 32).
+// Consecutive pieces share a pass where their columns fit 64: pieces of 33 to 48 columns go first,
+// each before one of up to 16, then those of 17 to 32, which fit each other, then what is left.
+// In list order a piece took 0.64 passes and 0.81 adds into the tile (two pieces of a pass that do
+// not meet are added as one) at the 256^3 workload; in this order 0.58 and 0.71.  Sorted by size
+// and matched from both ends it would be 0.55 passes; left and right pieces in turn, 0.68 adds
+// (0.8% faster there, 0.3% slower with the field).
+__device__ __forceinline__ int place_piece(int F)
+{
+    const bool a = F <= 16, b = !a && F <= 32, c = F > 32 && F <= 48;
+    const uint32_t ma = (uint32_t)__ballot(a), mb = (uint32_t)__ballot(b), mc = (uint32_t)__ballot(c);
+    const uint32_t md = (uint32_t)__ballot(F > 48);
+    const int na = __popc(ma), nb = __popc(mb), nc = __popc(mc), m = min(na, nc);
+    const int r = (int)__builtin_amdgcn_mbcnt_lo(a ? ma : b ? mb : c ? mc : md, 0u);
+    if (a) return r < m ? 2 * r + 1 : nc + nb + r;
+    if (b) return nc + m + r;
+    if (c) return r < m ? 2 * r : m + r;
+    return nc + nb + na + r;
+}
+
 // A tile's list [s, e) is cut into 2^a.parts_log2 parts (2 to 16), whole batches each: part k
 // starts at entry part_start(k), and part_start(2^parts_log2) >= e.
 struct TileList {
@@ -331,7 +353,9 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
         wave_sync();
         if (PARTS)
             while (b0 >= next && k < k0 + np) flush();
-        int myF = 0;            // this lane's piece: footprint area
+        // this lane's piece: footprint area with its first and last columns in x and y (4 bits
+        // each, from bit 9 on), and its place in the batch
+        int myF = 0, pos = lane;
         if (lane < nb) {
             const int lox = __float_as_int(r2.z), loy = __float_as_int(r2.w);
             const int loz = __float_as_int(r3.x), hix = __float_as_int(r3.y);
@@ -361,29 +385,37 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
             p.dz2 = zl <= 2 && zh >= 2 ? (d0 + 2.0f) - r0.z : DZ_OUT;
             p.dz3 = zl <= 3 && zh >= 3 ? (d0 + 3.0f) - r0.z : DZ_OUT;
             myF = ok ? wx * wy : 0;
-            pc[lane] = p;
+            const int x0 = ix0 - t0x, y0 = iy0 - t0y;
+            pos = place_piece(myF);
+            pc[pos] = p;
+            if (ok) myF |= x0 << 9 | (x0 + wx - 1) << 13 | y0 << 17 | (y0 + wy - 1) << 21;
             if (MASK && mc.on) {
                 PieceCell q;
                 q.ix0 = ix0;
                 q.iy0 = iy0;
                 q.pad0 = q.pad1 = 0;
                 q.cm = a.bq.cells[(uint32_t)my_entry & GM_ID_MASK];
-                pcc[lane] = q;
+                pcc[pos] = q;
             }
         }
+        myF = __builtin_amdgcn_ds_permute(pos << 2, myF);      // lane j: piece j of the new order
         // pieces j and j + 1 share a pass when their footprints sum to <= 64.  Lane j holds
         // that pass as one word: (columns of both << 16) | footprint of piece j, the upper half
-        // equal to the lower where piece j goes alone
+        // equal to the lower where piece j goes alone, and bit 15 where no column is in both
         const int nextF = __shfl_down(myF, 1, 64);
-        const bool pair = lane + 1 < nb && myF + nextF <= 64;
-        const int pk = myF | ((pair ? myF + nextF : myF) << 16);
+        const int fa = myF & 0x1ff, fb = nextF & 0x1ff;
+        const bool pair = lane + 1 < nb && fa + fb <= 64;
+        const bool apart = (myF >> 13 & 15) < (nextF >> 9 & 15) || (nextF >> 13 & 15) < (myF >> 9 & 15) ||
+                           (myF >> 21 & 15) < (nextF >> 17 & 15) || (nextF >> 21 & 15) < (myF >> 17 & 15);
+        const int pk = fa | (pair && apart ? 0x8000 : 0) | ((pair ? fa + fb : fa) << 16);
         wave_sync();
         int j = 0;
         int k = __builtin_amdgcn_readlane(pk, 0);
-        Pass q = load_pass(pc, 0, k & 0xffff, lane, lane_fh);
+        Pass q = load_pass(pc, 0, k & 0x1ff, lane, lane_fh);
 #pragma unroll 1
         for (;;) {
-            const int Fa = k & 0xffff, Ft = k >> 16;
+            const int Fa = k & 0x1ff, Ft = k >> 16;
+            const int F1 = k & 0x8000 ? Ft : Fa;       // columns added at once
             const int jn = j + (Ft > Fa ? 2 : 1);
             const bool more = jn < nb;
             k = __builtin_amdgcn_readlane(pk, more ? jn : j);
@@ -395,10 +427,12 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
             // every lane evaluates (a lane past its piece's footprint computes values it
             // never stores), so no lane mask is needed around the evaluation
             lds_order();
-            if (lane < Fa) add_column(acc, col, w);
+            if (lane < F1) add_column(acc, col, w);
             lds_order();
-            if (lane >= Fa && lane < Ft) add_column(acc, col, w);
-            lds_order();
+            if (F1 < Ft) {
+                if (lane >= Fa && lane < Ft) add_column(acc, col, w);
+                lds_order();
+            }
 #pragma unroll 1
             for (int f = 64; f < Fa; f += 64) {
                 eval_column(q.p, q.fh + (float)f, w, col);
@@ -409,7 +443,7 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
             }
             if (!more) break;
             j = jn;
-            q = load_pass(pc, j, k & 0xffff, lane, lane_fh);
+            q = load_pass(pc, j, k & 0x1ff, lane, lane_fh);
         }
     }
     wave_sync();
