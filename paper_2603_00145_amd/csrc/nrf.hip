@@ -52,32 +52,35 @@ struct GradLds {
 };
 
 // Where the quad of lane 16 g + row is stored: rows of the upper two lane groups with row bit 2
-// flipped, so that both the quads of one g (the writes, and the weights' plain reads) and the four
-// g of four rows (the transposing reads) lie in 16 different bank pairs.
+// flipped, so that both the quads of one g (the writes) and the four g of four rows (the transposing
+// reads) lie in 16 different bank pairs.
 __device__ __forceinline__ int swizzle(int lane) { return lane ^ ((lane >> 3) & 4); }
 
-// The quad that lane 16 G + 4 j + c reads for read_tr to give it rows 4 G .. 4 G + 3 of feature
+// The lane whose quad lane 16 G + 4 j + c reads for read_tr to give it rows 4 G .. 4 G + 3 of feature
 // 4 j + c: row 4 G + j of lane group c
-__device__ __forceinline__ int transposed(int lane)
+__device__ __forceinline__ int source_lane(int lane)
 {
-    return swizzle((lane & 3) * 16 + (lane >> 4) * 4 + ((lane >> 2) & 3));
+    return (lane & 3) * 16 + (lane >> 4) * 4 + ((lane >> 2) & 3);
 }
 
 template <int KT, int DEPTH>
 struct GradWeights {
     const GradLds<KT, DEPTH>& s;
-    int lane, slot, slot_tr;       // swizzle(lane), transposed(lane)
+    int lane;
+    int wslot, wslot_tr;           // where the lane's piece of a hidden layer lies, and the one it
+                                   // reads for read_tr
     __device__ v4f bias(const NrfArgs&, int l, int o) const { return s.bias[l][4 * o + (lane >> 4)]; }
-    __device__ v4s in(int o, int t) const { return s.w.w_in[(o * KT + t) * 64 + lane]; }
-    __device__ v4s hid(int l, int o, int t) const
+    __device__ v8h in(int o, int u) const { return s.w.w_in[(o * (KT / 2) + u) * 64 + lane]; }
+    __device__ v8h hid(int l, int o, int u) const
     {
-        return s.w.w_hid[((l - 1) * 16 + o * 4 + t) * 64 + slot];
+        return s.w.w_hid[((l - 1) * 8 + o * 2 + u) * 64 + wslot];
     }
     // W_l^T as A operand (i-tile of inputs, o-tile of outputs): lane (g, row) gets
     // W_l[16 o + 4 g + j][16 i + row], from the quads of W_l's operand (o, i)
     __device__ v4s hid_t(int l, int i, int o) const
     {
-        return read_tr(&s.w.w_hid[((l - 1) * 16 + o * 4 + i) * 64 + slot_tr]);
+        return read_tr(reinterpret_cast<const v4s*>(
+                           &s.w.w_hid[((l - 1) * 8 + o * 2 + (i >> 1)) * 64 + wslot_tr]) + (i & 1));
     }
 };
 
@@ -120,7 +123,9 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
         s.bias[l][q] = v4f{b[0], b[1], b[2], b[3]};
     }
     load_weights<KT, DEPTH, true>(a, s.w);
-    const GradWeights<KT, DEPTH> ws{s, lane, swizzle(lane), transposed(lane)};
+    const int lane_tr = source_lane(lane);
+    const GradWeights<KT, DEPTH> ws{s, lane, lane ^ 4 * (lane >> 4), lane_tr ^ 4 * (lane_tr >> 4)};
+    const int slot_tr = swizzle(lane_tr);
     // dW accumulators.  Row tile i of the wavefront is 2 wr + (i ^ wc), so that i = 0 is the one
     // whose row sums it takes.
     v4f acc0[2][CT], acch[DEPTH > 1 ? DEPTH - 1 : 1][2][2], accb[DEPTH];
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
         Tile<KT, DEPTH> T;
         tile_forward_w<KT, DEPTH>(a, ws, x, T);
         __syncthreads();            // the last round's products are done
-        const int slot = wv * 64 + ws.slot;
+        const int slot = wv * 64 + swizzle(lane);
 #pragma unroll
         for (int t = 0; t < KT; ++t) s.enc[t * 256 + slot] = T.enc[t];
 #pragma unroll
@@ -228,14 +233,14 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
                 v4s z[2][2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const v4s* q = &s.dz[((2 * wr + (i ^ wc)) * 4 + st) * 64 + ws.slot_tr];
+                    const v4s* q = &s.dz[((2 * wr + (i ^ wc)) * 4 + st) * 64 + slot_tr];
                     z[i][0] = read_tr(q);
                     z[i][1] = read_tr(q + 64);
                 }
                 accb[l] = mfma2(z[0][0], z[0][1], ones, ones, accb[l]);
 #pragma unroll
                 for (int t = 0; t < (l == 0 ? CT : 2); ++t) {
-                    const v4s* q = &in[((wc * (l == 0 ? CT : 2) + t) * 4 + st) * 64 + ws.slot_tr];
+                    const v4s* q = &in[((wc * (l == 0 ? CT : 2) + t) * 4 + st) * 64 + slot_tr];
                     const v4s b0 = read_tr(q), b1 = read_tr(q + 64);
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {

@@ -44,6 +44,15 @@ __device__ __forceinline__ v4f mfma2(v4s a0, v4s a1, v4s b0, v4s b1, v4f c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+typedef short v8h __attribute__((ext_vector_type(8)));
+
+// the same with both halves of A in one operand
+__device__ __forceinline__ v4f mfma_a8(v8h a, v4s b0, v4s b1, v4f c)
+{
+    const v8bf b = __builtin_bit_cast(v8bf, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), b, c, 0, 0, 0);
+}
+
 // sigmoid with the hardware reciprocal (1 ulp; the field runs in BF16): exp(-z) overflows to
 // +inf for very negative z, whose reciprocal is 0, the right limit
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
@@ -114,42 +123,46 @@ __device__ __forceinline__ void encode(const float x[3], int n_freq, v4s b0[KT])
     for (int t = 0; t < KT; ++t) b0[t] = pack4(v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3]);
 }
 
-// Weights staged in LDS in MFMA A-operand order: operand (o, t) of a layer is 64 lanes x 4 BF16,
-// lane (g, row) holding W[16 o + row][16 t + 4 g + j], so that a wavefront reads an operand as
-// 512 contiguous bytes (one ds_read_b64 per lane, free of bank conflicts).  Sized for KT K-tiles
-// of the first layer and DEPTH - 1 hidden layers.
+// Weights staged in LDS in MFMA A-operand order: operand (o, u) of a layer, K-tiles 2 u and 2 u + 1, is
+// 64 lanes x 8 BF16, lane (g, row) holding W[16 o + row][32 u + 4 g + j] and [.. + 16], so that a
+// wavefront reads an operand as 1 KB of consecutive 16-byte pieces.  (As two 8-byte pieces the reads
+// came paired across operands, and 28 moves a tile put the halves together: with those gone and
+// the biases in LDS, the field on a 256^3 volume went from 1600 to 1554 us, on three 256x256x64
+// stacks from 1427 to 1390.)  Sized for KT K-tiles of the first layer and DEPTH - 1 hidden layers.
 template <int KT, int DEPTH>
 struct Lds {
-    v4s w_in[4 * KT * 64];                                 // [o][t][lane], GPU encoding order
-    v4s w_hid[(DEPTH > 1 ? DEPTH - 1 : 1) * 16 * 64];      // [l][o][t][lane]
+    v8h w_in[2 * KT * 64];                                 // [o][u][lane], GPU encoding order
+    v8h w_hid[(DEPTH > 1 ? DEPTH - 1 : 1) * 8 * 64];       // [l][o][u][lane]
 };
+
 // Stages the weights (every thread of the block takes part; ends with a block barrier).
-// SWZ: within an operand the upper lanes' quads of the hidden layers are stored at lane ^ 4, so that
-// the transposing reads of the backward find 16 quads of every lane group in different banks too.
+// SWZ: within an operand of a hidden layer lane (g, row)'s piece is stored at row ^ 4 g, so that the
+// transposing reads of the backward find 16 pieces of every lane group in different banks too.
 template <int KT, int DEPTH, bool SWZ = false>
 __device__ void load_weights(const NrfArgs& a, Lds<KT, DEPTH>& s)
 {
-    for (int e = threadIdx.x; e < 4 * KT * 64; e += blockDim.x) {
-        const int lane = e & 63, t = (e >> 6) % KT, o = (e >> 6) / KT;
+    constexpr int U = KT / 2;
+    for (int e = threadIdx.x; e < 4 * U * 64; e += blockDim.x) {
+        const int lane = e & 63, u = (e >> 6) % U, o = (e >> 6) / U;
         const int g = lane >> 4, row = lane & 15;
         const uint16_t* src = a.w_in + (16 * o + row) * (16 * KT);
-        short v[4];
+        v8h v;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int nf = natural_feature<KT>(16 * t + 4 * g + j, a.n_freq);
+        for (int j = 0; j < 8; ++j) {
+            const int nf = natural_feature<KT>(32 * u + 16 * (j >> 2) + 4 * g + (j & 3), a.n_freq);
             v[j] = nf >= 0 ? (short)src[nf] : (short)0;
         }
-        s.w_in[e] = v4s{v[0], v[1], v[2], v[3]};
+        s.w_in[e] = v;
     }
-    const int nh = (DEPTH - 1) * 16 * 64;
+    const int nh = (DEPTH - 1) * 8 * 64;
     for (int e = threadIdx.x; e < nh; e += blockDim.x) {
-        const int lane = e & 63, t = (e >> 6) & 3, o = (e >> 8) & 3, l = e >> 10;
+        const int lane = e & 63, u = (e >> 6) & 1, o = (e >> 7) & 3, l = e >> 9;
         const int g = lane >> 4, row = lane & 15;
-        const uint16_t* Wl = a.w_hid + l * W * W;
-        short v[4];
+        const uint16_t* src = a.w_hid + l * W * W + (16 * o + row) * W + 32 * u + 4 * g;
+        v8h v;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (short)Wl[(16 * o + row) * W + 16 * t + 4 * g + j];
-        s.w_hid[SWZ ? e ^ ((e >> 3) & 4) : e] = v4s{v[0], v[1], v[2], v[3]};
+        for (int j = 0; j < 8; ++j) v[j] = (short)src[16 * (j >> 2) + (j & 3)];
+        s.w_hid[SWZ ? e ^ (4 * g) : e] = v;
     }
     __syncthreads();
 }
@@ -186,8 +199,8 @@ struct Tile {
 };
 
 // Where tile_forward takes the layers' MFMA A operands from: the LDS stage, read at each use,
-// or the wavefront's registers (each lane its quad of every operand, 4 KT + 16 (DEPTH - 1)
-// quads, copied once from the stage; the per-tile LDS reads of the weights, 512 bytes per lane,
+// or the wavefront's registers (each lane its piece of every operand, 2 KT + 8 (DEPTH - 1)
+// pieces, copied once from the stage; the per-tile LDS reads of the weights, 512 bytes per lane,
 // then disappear).
 // the lane's four biases of o-tile o of layer l
 __device__ __forceinline__ v4f global_bias(const NrfArgs& a, int l, int o)
@@ -199,28 +212,29 @@ __device__ __forceinline__ v4f global_bias(const NrfArgs& a, int l, int o)
 template <int KT, int DEPTH>
 struct WeightsLds {
     const Lds<KT, DEPTH>& s;
+    const v4f* b;                  // biases, [l][4 o + g]
     int lane;
-    __device__ v4f bias(const NrfArgs& a, int l, int o) const { return global_bias(a, l, o); }
-    __device__ v4s in(int o, int t) const { return s.w_in[(o * KT + t) * 64 + lane]; }
-    __device__ v4s hid(int l, int o, int t) const
+    __device__ v4f bias(const NrfArgs&, int l, int o) const { return b[16 * l + 4 * o + (lane >> 4)]; }
+    __device__ v8h in(int o, int u) const { return s.w_in[(o * (KT / 2) + u) * 64 + lane]; }
+    __device__ v8h hid(int l, int o, int u) const
     {
-        return s.w_hid[((l - 1) * 16 + o * 4 + t) * 64 + lane];
+        return s.w_hid[((l - 1) * 8 + o * 2 + u) * 64 + lane];
     }
 };
 template <int KT, int DEPTH>
 struct WeightsReg {
-    v4s w_in[4 * KT];
-    v4s w_hid[(DEPTH > 1 ? DEPTH - 1 : 1) * 16];
+    v8h w_in[2 * KT];
+    v8h w_hid[(DEPTH > 1 ? DEPTH - 1 : 1) * 8];
     __device__ void load(const Lds<KT, DEPTH>& s, int lane)
     {
 #pragma unroll
-        for (int i = 0; i < 4 * KT; ++i) w_in[i] = s.w_in[i * 64 + lane];
+        for (int i = 0; i < 2 * KT; ++i) w_in[i] = s.w_in[i * 64 + lane];
 #pragma unroll
-        for (int i = 0; i < (DEPTH - 1) * 16; ++i) w_hid[i] = s.w_hid[i * 64 + lane];
+        for (int i = 0; i < (DEPTH - 1) * 8; ++i) w_hid[i] = s.w_hid[i * 64 + lane];
     }
     __device__ v4f bias(const NrfArgs& a, int l, int o) const { return global_bias(a, l, o); }
-    __device__ v4s in(int o, int t) const { return w_in[o * KT + t]; }
-    __device__ v4s hid(int l, int o, int t) const { return w_hid[(l - 1) * 16 + o * 4 + t]; }
+    __device__ v8h in(int o, int u) const { return w_in[o * (KT / 2) + u]; }
+    __device__ v8h hid(int l, int o, int u) const { return w_hid[(l - 1) * 8 + o * 2 + u]; }
 };
 
 template <int KT, int DEPTH, typename WS>
@@ -234,7 +248,7 @@ __device__ __forceinline__ void tile_forward_w(const NrfArgs& a, const WS& ws, c
         v4f acc = ws.bias(a, 0, o);   // bias as C
 #pragma unroll
         for (int t = 0; t < KT; t += 2)
-            acc = mfma2(ws.in(o, t), ws.in(o, t + 1), T.enc[t], T.enc[t + 1], acc);
+            acc = mfma_a8(ws.in(o, t / 2), T.enc[t], T.enc[t + 1], acc);
         T.layer(0, o, acc);
     }
     // hidden layers
@@ -245,20 +259,20 @@ __device__ __forceinline__ void tile_forward_w(const NrfArgs& a, const WS& ws, c
             v4f acc = ws.bias(a, l, o);
 #pragma unroll
             for (int t = 0; t < 4; t += 2)
-                acc = mfma2(ws.hid(l, o, t), ws.hid(l, o, t + 1), T.act[l - 1][t],
-                            T.act[l - 1][t + 1], acc);
+                acc = mfma_a8(ws.hid(l, o, t / 2), T.act[l - 1][t], T.act[l - 1][t + 1], acc);
             T.layer(l, o, acc);
         }
     }
 }
 
-// tile_forward_w with the weights read from the LDS stage at each use
-template <int KT, int DEPTH>
-__device__ __forceinline__ void tile_forward(const NrfArgs& a, const Lds<KT, DEPTH>& s, const float x[3],
-                                             Tile<KT, DEPTH>& T)
+// Stages the biases for WeightsLds: quad e of 16 DEPTH by thread e (of at least that many)
+template <int DEPTH>
+__device__ __forceinline__ void load_biases(const NrfArgs& a, v4f* b, int e)
 {
-    const WeightsLds<KT, DEPTH> ws{s, (int)(threadIdx.x & 63)};
-    tile_forward_w<KT, DEPTH>(a, ws, x, T);
+    if (e < 16 * DEPTH) {
+        const float* q = e < 16 ? a.b_in + 4 * e : a.b_hid + 4 * (e - 16);
+        b[e] = v4f{q[0], q[1], q[2], q[3]};
+    }
 }
 
 // The output layer as a 16-row MFMA A operand whose rows 0, 4, 8 and 12 are w_out and the other

@@ -630,6 +630,14 @@ __global__ __launch_bounds__(64 * FW, (field_waves<KT, DEPTH>(MASK))) void k_ren
             }
             __syncthreads();
         }
+        // the biases go where the wavefront's pieces were (read from global memory, under this
+        // kernel's register pressure, each was waited for in the middle of a layer)
+        nrfcore::v4f* bias = reinterpret_cast<nrfcore::v4f*>(sh.pcs[w]);
+        static_assert(sizeof sh.pcs[0] >= 16 * DEPTH * sizeof(nrfcore::v4f), "room for the biases");
+        wave_sync();
+        nrfcore::load_biases<DEPTH>(f, bias, lane);
+        wave_sync();
+        const nrfcore::WeightsLds<KT, DEPTH> ws{sw, bias, lane};
         // Four rows at a time: lane group j keeps row j's output, so that one tanh (some 50
         // instructions, and all four groups used to form the same 16) serves all four.  With this
         // and the encoding's bands past n_freq left out, a 256^3 volume with the field went from
@@ -647,7 +655,7 @@ __global__ __launch_bounds__(64 * FW, (field_waves<KT, DEPTH>(MASK))) void k_ren
                                     nrfcore::world_coord(G.index_to_world + 4, vx, vy, vz),
                                     nrfcore::world_coord(G.index_to_world + 8, vx, vy, vz)};
                 nrfcore::Tile<KT, DEPTH> Tl;
-                nrfcore::tile_forward<KT, DEPTH>(f, sw, x, Tl);
+                nrfcore::tile_forward_w<KT, DEPTH>(f, ws, x, Tl);
                 const float z = nrfcore::tile_output<KT, DEPTH>(f, Tl, wo);
                 zo = g == j ? z : zo;
             }
