@@ -715,9 +715,10 @@ __global__ __launch_bounds__(FIN_THREADS) void k_render_loss_finish(const double
 // Parts a tile's list is cut into, by the tiles of its grid (a property of the grid alone, so
 // that every kernel and every listing of grids sums a tile the same way).  A small grid has too
 // few tiles to fill the chip with a wavefront each.  Measured training iterations (us) at 2 / 4 /
-// 8 / 16 wavefronts per tile: 64 tiles per grid 200 / 165 / 149 / 137; 216: 239 / 209 / 197 /
-// 207; 512: 429 / 394 / 383 / 420; 1728: 582 / 561 / 569 / 709; 4096: 1172 / 1148 / 1179 / 1537
-// (one: 277, 307, 515, 633, 1239); rendering one grid of 32000 tiles 804 / 816 / 911 / 1623.
+// 8 / 16 wavefronts per tile: 64 tiles per grid 166 / 126 / 109 / 100; 216: 220 / 176 / 164 /
+// 175; 512: 417 / 380 / 367 / 400; 1728: 553 / 524 / 527 / 674; 4096: 1150 / 1116 / 1142 / 1498;
+// rendering one grid of 32000 tiles 675 / 686 / 773 / 1423.  (One wavefront per tile was slower by
+// 3 to 40% than two at each.)
 int parts_of(const RenderGrid& g)
 {
     const int64_t tiles = (int64_t)g.ntx * g.nty * g.ntz;
