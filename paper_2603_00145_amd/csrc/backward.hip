@@ -94,12 +94,20 @@ constexpr int KEY_X = 4, KEY_Z = 5, KEY_Y = 12;
 constexpr int NKEY = KEY_X * KEY_Z * KEY_Y + 1;
 static_assert(RZS % 32 == 8, "z-plane stride must be 8 mod 32 banks");
 
-// Column sums s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge (ge = g 2^Q_k) over the first NK
-// rows of a column whose rows are RX floats apart in the staged region, all NK reads issued at
-// immediate offsets before the first use; rows past the column (k >= ncol) are masked where they
-// are used.  NK is the wavefront's longest column (up to NK_MAX), a compile-time constant, so
-// the steps carry no branches.  (No contraction: a Gaussian's sums must not depend on the NK its
-// wavefront takes.)
+// The row of a box that an LDS column's walk counts from.  Q_k and the moments are formed around
+// it, so the closer it lies to the Gaussian's centre, the less cancels (a 3-sigma box of a 1-voxel
+// Gaussian has 7 rows).  Counted from row 0, in the same time, the quaternions' gradients of 1M
+// Gaussians on three 256x256x64 stacks were 3 times as far from binary64 (99 of 100 within 2.3e-7
+// of the largest; now 7.4e-8).  Row 3 gave 5.7e-8, but a larger error in boxes of few rows (the
+// worst centre gradient 1.1e-6 against 3.9e-7).
+constexpr int YC = 2;
+
+// Column sums s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge (ge = g 2^Q_k, k = row - YC) over the
+// first NK rows of a column whose rows are RX floats apart in the staged region, all NK reads
+// issued at immediate offsets before the first use; rows past the column (row >= ncol) are masked
+// where they are used.  NK is the wavefront's longest column (up to NK_MAX), a compile-time
+// constant, so the steps carry no branches.  (No contraction: a Gaussian's sums must not depend on
+// the NK its wavefront takes.)
 template <int NK, bool MASK>
 __device__ __forceinline__ void lds_column(const float* __restrict__ region, uint32_t off,
                                            int ncol, float A, float B, float kyy, float& s0,
@@ -108,24 +116,32 @@ __device__ __forceinline__ void lds_column(const float* __restrict__ region, uin
 #pragma clang fp contract(off)
     float gv[NK];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) gv[k] = region[off + k * RX];
-    s1 = s2 = 0.0f;
+    for (int r = 0; r < NK; ++r) gv[r] = region[off + r * RX];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
+    for (int r = 0; r < NK; ++r) {
+        const int k = r - YC;
         const float Q = k == 0 ? A : fmaf((float)k, fmaf((float)k, kyy, B), A);
         // without MASK every active column of the wavefront is at least NK long
-        const float gk = (k == 0 || !MASK) ? gv[k] : (k < ncol ? gv[k] : 0.0f);
-        const float ge = gk * __builtin_amdgcn_exp2f(Q);
-        s0 = k == 0 ? ge : s0 + ge;
-        if (k == 1) s1 = s2 = ge;
-        if (k > 1) {
+        const float gr = (r == 0 || !MASK) ? gv[r] : (r < ncol ? gv[r] : 0.0f);
+        const float ge = gr * __builtin_amdgcn_exp2f(Q);
+        if (r == 0) {
+            s0 = ge;
+            s1 = (float)k * ge;
+            s2 = (float)(k * k) * ge;
+            continue;
+        }
+        s0 += ge;
+        if (k == 1 || k == -1) {
+            s1 = k > 0 ? s1 + ge : s1 - ge;
+            s2 += ge;
+        } else if (k != 0) {
             s1 = fmaf((float)k, ge, s1);
             s2 = fmaf((float)(k * k), ge, s2);
         }
     }
 }
 
-// Sums over the planes of a lane's (y, z) sheet: S = sum gE, k (the row index) and dz moments.
+// Sums over the planes of a lane's (y, z) sheet: sum gE, k (the row less YC) and dz moments.
 struct Sheet {
     float s, k, kk, z, zz, kz;
 };
@@ -154,11 +170,11 @@ __device__ __forceinline__ void lds_sheet(const float* __restrict__ region, uint
         lds_column<NK, MASK>(region, o, ncol, A, B, kyy, s0, s1, s2);
         if (NK == NK_MAX) {
 #pragma unroll 1
-            for (int k = NK_MAX; k < max_wy; ++k) {
-                const float t = region[o + min(k, ncol - 1) * RX];
-                const float gk = k < ncol ? t : 0.0f;
-                const float fk = (float)k;
-                const float ge = gk * __builtin_amdgcn_exp2f(fmaf(fk, fmaf(fk, kyy, B), A));
+            for (int r = NK_MAX; r < max_wy; ++r) {
+                const float t = region[o + min(r, ncol - 1) * RX];
+                const float gr = r < ncol ? t : 0.0f;
+                const float fk = (float)(r - YC);
+                const float ge = gr * __builtin_amdgcn_exp2f(fmaf(fk, fmaf(fk, kyy, B), A));
                 s0 += ge;
                 s1 = fmaf(fk, ge, s1);
                 s2 = fmaf(fk * fk, ge, s2);
@@ -257,7 +273,7 @@ __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_
     if (max_wy == KEY_Y) max_wy = group_max<BWD_G>(gvalid ? wy : 0);
     if (max_wz == KEY_Z) max_wz = group_max<BWD_G>(gvalid ? wz : 0);
     if (max_wx == KEY_X * BWD_G) max_wx = group_max<BWD_G>(wx);
-    const float dy0 = -r0.y;                      // dy = dy0 + k at step k of a column
+    const float dy0 = (float)YC - r0.y;           // dy = dy0 + k at step k of a column
     const float g1 = dy0 * kxy, g2 = dy0 * kyz, A0 = kyy * dy0 * dy0, B0 = 2.0f * kyy * dy0;
     const uint32_t base = (uint32_t)((loz - t0z) * RZS + (loy - t0y) * RX + (lox - t0x));
     Moments v = {};
@@ -295,7 +311,7 @@ __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_
         k1x = fmaf(S.k, dx, k1x);
         k1z += S.kz;
     }
-    // from sums over the step index k to moments in dy = dy0 + k (dy0 is the Gaussian's):
+    // from sums over the step k to moments in dy = dy0 + k (dy0 is the Gaussian's):
     // sum (dy0 + k) gE = k1 + dy0 m, sum (dy0 + k)^2 gE = k2 + dy0 (2 k1 + dy0 m), and the
     // products with dx and dz likewise
     v.y = fmaf(dy0, v.m, k1);
