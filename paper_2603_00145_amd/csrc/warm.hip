@@ -13,63 +13,91 @@ namespace {
 using namespace warmcore;
 
 // ---- patch gather -------------------------------------------------------------------------
-// One block per Gaussian: thread t samples the patch points t and t + 256 in every stack, so that
-// the 24 reads of a point are independent.  The two x neighbours of a corner pair are one 8-byte
-// read (four reads per sample instead of eight) at 32-bit offsets.  Bound by the address rate of
-// the scattered reads: 3.9 ms for a million patches (one thread per sample and 64-bit indices:
-// 10.4 ms), which write 3.1 GB.
+// One block per Gaussian: a thread samples four patch points of a z column in every stack, so that
+// the terms of x and y in the three index sums are formed once and 16 reads are in flight (a point
+// outside the stack reads voxel 0).  NEAR, where every stack is wider than one voxel and small
+// enough for 24-bit rows and 32-bit byte offsets: the two x neighbours of a corner pair are one
+// 8-byte read, and the four pairs lie at one offset from four uniform bases (the clamp leaves
+// y0 + 1 and z0 + 1 inside wherever the stack has two rows or planes).  Otherwise eight reads at
+// 64-bit offsets.  A million patches (3.1 GB written) 3.2 ms at 57 vector
+// instructions a sample; with two points a thread, a branch around each and the row offsets formed
+// per corner, 93 instructions, 3.9 ms.
 struct __attribute__((packed, aligned(4))) XPair {
     float a, b;
 };
 
 __device__ __forceinline__ float lerp(float a, float b, float f) { return fmaf(1.0f - f, a, f * b); }
 
-__global__ __launch_bounds__(256) void k_ws_gather(const WsGatherArgs a)
+constexpr int GATHER_THREADS = 128;
+
+template <bool NEAR>
+__global__ __launch_bounds__(GATHER_THREADS) void k_ws_gather(const WsGatherArgs a)
 {
+    constexpr int ZSTEP = GATHER_THREADS / 64, POINTS = 8 / ZSTEP;
     const int64_t b = blockIdx.x;
-    const float m0 = a.means[3 * b], m1 = a.means[3 * b + 1], m2 = a.means[3 * b + 2];
+    const int v0 = threadIdx.x;
+    const int x = v0 % 8, y = (v0 / 8) % 8, z = v0 / 64;
+    const double wx = (double)fmaf(a.spacing, (float)x - 3.5f, a.means[3 * b]);
+    const double wy = (double)fmaf(a.spacing, (float)y - 3.5f, a.means[3 * b + 1]);
+    double wz[POINTS];
 #pragma unroll
-    for (int v = threadIdx.x; v < 512; v += 256) {
-        const int z = v / 64, y = (v / 8) % 8, x = v % 8;
-        const float wx = fmaf(a.spacing, (float)x - 3.5f, m0);
-        const float wy = fmaf(a.spacing, (float)y - 3.5f, m1);
-        const float wz = fmaf(a.spacing, (float)z - 3.5f, m2);
+    for (int j = 0; j < POINTS; ++j)
+        wz[j] = (double)fmaf(a.spacing, (float)(z + j * ZSTEP) - 3.5f, a.means[3 * b + 2]);
+    uint16_t* out = a.patches + b * 3 * 512;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const GridConst& S = a.s[k];
-            auto index = [&](int r) {
-                return (float)(fma(S.L[3 * r + 2], (double)wz,
-                                   fma(S.L[3 * r], (double)wx, S.L[3 * r + 1] * (double)wy)) +
-                               S.t[r]);
-            };
-            const float px = index(0), py = index(1), pz = index(2);
-            float val = 0.0f;
-            if (px >= 0.0f && py >= 0.0f && pz >= 0.0f && px <= (float)(S.nx - 1) &&
-                py <= (float)(S.ny - 1) && pz <= (float)(S.nz - 1)) {
-                const int x0 = min((int)px, max(S.nx - 2, 0)), y0 = min((int)py, max(S.ny - 2, 0)),
-                          z0 = min((int)pz, max(S.nz - 2, 0));
-                const int y1 = min(y0 + 1, S.ny - 1), z1 = min(z0 + 1, S.nz - 1);
-                const float fx = px - (float)x0, fy = py - (float)y0, fz = pz - (float)z0;
-                const float* d = a.data[k];
-                XPair p00, p10, p01, p11;      // (y0, z0), (y1, z0), (y0, z1), (y1, z1)
-                const int r00 = (z0 * S.ny + y0) * S.nx + x0, r10 = (z0 * S.ny + y1) * S.nx + x0;
-                const int r01 = (z1 * S.ny + y0) * S.nx + x0, r11 = (z1 * S.ny + y1) * S.nx + x0;
-                if (S.nx > 1) {                // x0 + 1 lies in the stack
-                    p00 = *reinterpret_cast<const XPair*>(d + r00);
-                    p10 = *reinterpret_cast<const XPair*>(d + r10);
-                    p01 = *reinterpret_cast<const XPair*>(d + r01);
-                    p11 = *reinterpret_cast<const XPair*>(d + r11);
-                } else {
-                    p00 = XPair{d[r00], d[r00]};
-                    p10 = XPair{d[r10], d[r10]};
-                    p01 = XPair{d[r01], d[r01]};
-                    p11 = XPair{d[r11], d[r11]};
-                }
-                const float c00 = lerp(p00.a, p00.b, fx), c10 = lerp(p10.a, p10.b, fx);
-                const float c01 = lerp(p01.a, p01.b, fx), c11 = lerp(p11.a, p11.b, fx);
-                val = lerp(lerp(c00, c10, fy), lerp(c01, c11, fy), fz);
+    for (int k = 0; k < 3; ++k) {
+        const GridConst& S = a.s[k];
+        double xy[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) xy[r] = fma(S.L[3 * r], wx, S.L[3 * r + 1] * wy);
+        const float ex = (float)(S.nx - 1), ey = (float)(S.ny - 1), ez = (float)(S.nz - 1);
+        const int lx = max(S.nx - 2, 0), ly = max(S.ny - 2, 0), lz = max(S.nz - 2, 0);
+        const int64_t dx = S.nx > 1 ? 1 : 0, dy = S.ny > 1 ? S.nx : 0;
+        const int64_t dz = S.nz > 1 ? (int64_t)S.ny * S.nx : 0;
+        const float* const d00 = a.data[k];
+        const float* const d10 = d00 + dy;
+        const float* const d01 = d00 + dz;
+        const float* const d11 = d01 + dy;
+        XPair p00[POINTS], p10[POINTS], p01[POINTS], p11[POINTS];   // p<y><z>: rows y0 + y, z0 + z
+        float fx[POINTS], fy[POINTS], fz[POINTS];
+        bool in[POINTS];
+#pragma unroll
+        for (int j = 0; j < POINTS; ++j) {
+            float px = (float)(fma(S.L[2], wz[j], xy[0]) + S.t[0]);
+            float py = (float)(fma(S.L[5], wz[j], xy[1]) + S.t[1]);
+            float pz = (float)(fma(S.L[8], wz[j], xy[2]) + S.t[2]);
+            in[j] = px >= 0.0f && py >= 0.0f && pz >= 0.0f && px <= ex && py <= ey && pz <= ez;
+            px = in[j] ? px : 0.0f;
+            py = in[j] ? py : 0.0f;
+            pz = in[j] ? pz : 0.0f;
+            const int x0 = min((int)px, lx), y0 = min((int)py, ly), z0 = min((int)pz, lz);
+            fx[j] = px - (float)x0;
+            fy[j] = py - (float)y0;
+            fz[j] = pz - (float)z0;
+            if (NEAR) {
+                const uint32_t o = (__umul24(__umul24(z0, S.ny) + y0, S.nx) + x0) * 4u;
+                auto pair = [o](const float* d) {
+                    return *reinterpret_cast<const XPair*>(reinterpret_cast<const char*>(d) + o);
+                };
+                p00[j] = pair(d00);
+                p10[j] = pair(d10);
+                p01[j] = pair(d01);
+                p11[j] = pair(d11);
+            } else {
+                const int64_t o = ((int64_t)z0 * S.ny + y0) * S.nx + x0;
+                auto pair = [o, dx](const float* d) { return XPair{d[o], d[o + dx]}; };
+                p00[j] = pair(d00);
+                p10[j] = pair(d10);
+                p01[j] = pair(d01);
+                p11[j] = pair(d11);
             }
-            a.patches[(b * 3 + k) * 512 + v] = to_bf16(val);
+        }
+#pragma unroll
+        for (int j = 0; j < POINTS; ++j) {
+            const float c00 = lerp(p00[j].a, p00[j].b, fx[j]), c10 = lerp(p10[j].a, p10[j].b, fx[j]);
+            const float c01 = lerp(p01[j].a, p01[j].b, fx[j]), c11 = lerp(p11[j].a, p11[j].b, fx[j]);
+            const float val = lerp(lerp(c00, c10, fy[j]), lerp(c01, c11, fy[j]), fz[j]);
+            out[k * 512 + v0 + j * ZSTEP * 64] = to_bf16(in[j] ? val : 0.0f);
         }
     }
 }
@@ -126,7 +154,12 @@ __global__ __launch_bounds__(256) void k_ws_targets(const float* __restrict__ ls
 hipError_t launch_ws_gather(const WsGatherArgs& a, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ws_gather, dim3((unsigned)a.n), dim3(256), 0, s, a);
+    bool near = true;
+    for (const GridConst& S : a.s)
+        near = near && S.nx > 1 && (int64_t)S.ny * S.nz < (1 << 24) &&
+               (int64_t)S.nx * S.ny * S.nz < (1 << 30);
+    auto kernel = near ? k_ws_gather<true> : k_ws_gather<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.n), dim3(GATHER_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
