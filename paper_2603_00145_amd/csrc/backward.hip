@@ -96,10 +96,10 @@ static_assert(RZS % 32 == 8, "z-plane stride must be 8 mod 32 banks");
 
 // The row of a box that an LDS column's walk counts from.  Q_k and the moments are formed around
 // it, so the closer it lies to the Gaussian's centre, the less cancels (a 3-sigma box of a 1-voxel
-// Gaussian has 7 rows).  Counted from row 0, in the same time, the quaternions' gradients of 1M
-// Gaussians on three 256x256x64 stacks were 3 times as far from binary64 (99 of 100 within 2.3e-7
-// of the largest; now 7.4e-8).  Row 3 gave 5.7e-8, but a larger error in boxes of few rows (the
-// worst centre gradient 1.1e-6 against 3.9e-7).
+// Gaussian has 7 rows).  Counted from row 0 (1.7% fewer instructions, 353 against 355 us) the
+// quaternions' gradients of 1M Gaussians on three 256x256x64 stacks were 3 times as far from
+// binary64 (99 of 100 within 2.3e-7 of the largest; now 7.4e-8).  Row 3 gave 5.7e-8, but a larger
+// error in boxes of few rows (the worst centre gradient 1.1e-6 against 3.9e-7).
 constexpr int YC = 2;
 
 // Column sums s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge (ge = g 2^Q_k, k = row - YC) over the
@@ -471,7 +471,7 @@ __device__ __forceinline__ void scan_keys(int* hist, int lane)
 // round, so the order the atomics give within a key does not change any result bit.  Gaussians
 // with an empty box are in no list; gm_bin wrote their zeros.
 //
-// Bound by vector issue (166 M VALU instructions at the 256^3 workload, half of them walking
+// Bound by vector issue (169 M VALU instructions at the 256^3 workload, half of them walking
 // boxes) and by latency: list, records, region and sort precede a block's first round, and five
 // blocks a CU (29 KB of LDS, 96 VGPRs) have to cover that.  1M Gaussians on three 256x256x64
 // stacks 378 us, 200k on 128x128x32 90, 20k on 64x64x16 38 (29 with the list in four parts); with
