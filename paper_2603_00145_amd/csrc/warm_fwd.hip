@@ -66,6 +66,7 @@ __global__ __launch_bounds__(256, 2) void k_ws_conv12(const uint16_t* __restrict
     for (int i = threadIdx.x; i < 2 * IN_COPY; i += 256) s.in[i] = 0u;
     for (int i = threadIdx.x; i < 9 * A_Z / 8; i += 256)
         reinterpret_cast<uint4*>(s.a1)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();    // a patch's rows are staged by other wavefronts than the ones that clear them
     v4f bias1[2], bias2;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
