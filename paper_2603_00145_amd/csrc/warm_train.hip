@@ -139,6 +139,7 @@ __global__ __launch_bounds__(256, 1) void k_ws_train12(const WsNet net, const ui
         const int k = natural_k(i), c = k / 27, t = k % 27;
         s.off[i] = (uint16_t)((t / 9) * A_Z + (t / 3 % 3) * A_ROW + a_x(t % 3) * A_POS + c);
     }
+    __syncthreads();    // a patch's rows are staged by other wavefronts than the ones that clear them
     float bias1[2][4], bias2[2][4];
 #pragma unroll
     for (int m = 0; m < 2; ++m)

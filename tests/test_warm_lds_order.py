@@ -21,11 +21,22 @@ def _inference_rows():
         r = (t >> 6) * c + ((t >> 3 & 7) + 1) * z + ((t & 7) + 1) * row
         out.update({r + i: t for i in range(5)})
         out.update({r + copy + i: t for i in range(4)})
-    return out, 2 * copy, 1
+    return out, 2 * copy
 
 
-# kernel -> source, {LDS unit: staging thread} and the units, cleared `per` a thread
-KERNELS = {"k_ws_conv12": ("warm_fwd.hip", _inference_rows)}
+def _training_rows():
+    """element -> staging thread, as stage_patch lays a row out (five words of two)."""
+    out = {}
+    for t in range(192):
+        r = ((t >> 6) * 100 + ((t >> 3 & 7) + 1) * 10 + (t & 7) + 1) * 12
+        out.update({r + i: t for i in range(10)})
+    return out, 3600
+
+
+# kernel -> source, {LDS unit: staging thread} and the units, cleared one a thread in turn
+KERNELS = {"k_ws_conv12": ("warm_fwd.hip", _inference_rows),
+           "k_ws_train12": ("warm_train.hip", _training_rows),
+           "k_ws_back12": ("warm_train.hip", _training_rows)}
 
 
 def _before_first_sample(src, kernel):
@@ -40,8 +51,8 @@ def _before_first_sample(src, kernel):
 @pytest.mark.parametrize("kernel", KERNELS)
 def test_clearing_and_staging_are_ordered(kernel):
     src, layout = KERNELS[kernel]
-    staged, units, per = layout()
+    staged, units = layout()
     assert max(staged) < units
-    shared = sum((u // per) % THREADS // WAVE != t // WAVE for u, t in staged.items())
+    shared = sum(u % THREADS // WAVE != t // WAVE for u, t in staged.items())
     assert shared > 0      # wavefronts do write each other's words
     assert "__syncthreads();" in _before_first_sample(src, kernel)
