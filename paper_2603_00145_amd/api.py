@@ -426,6 +426,7 @@ def adam_step(p: torch.Tensor, g: torch.Tensor, m: torch.Tensor, v: torch.Tensor
 
 
 MAX_TENSORS = 16      # GM_MAX_TENSORS
+_ADAM_TYPES = (torch.float32,) * 3 + (torch.int16,)     # grad, m, v, bf16
 
 
 def _sizes(ts):
@@ -435,10 +436,20 @@ def _sizes(ts):
 def adam_step_many(ps, gs, ms, vs, bfs, lr: float, step: int, beta1: float = 0.9,
                    beta2: float = 0.999, eps: float = 1e-8):
     """adam_step on every (p, g, m, v), and p's BF16 bits into its entry of bfs (int16, or None),
-    in one launch per MAX_TENSORS tensors; same bits as the separate calls."""
-    for ts, nm in ((ps, "param"), (gs, "grad"), (ms, "m"), (vs, "v")):
-        for t in ts:
-            _need(t, torch.float32, nm)
+    in one launch per MAX_TENSORS tensors; same bits as the separate calls.  Lists of other lengths,
+    or an entry that does not have its parameter's element count and device, are a ValueError: the
+    launch takes every size from ps."""
+    if not len(ps) == len(gs) == len(ms) == len(vs) == len(bfs):
+        raise ValueError("param, grad, m, v and bf16 lists differ in length")
+    for p, *rest, h in zip(ps, gs, ms, vs, bfs):
+        _need(p, torch.float32, "param")
+        n, dev = p.numel(), p.device
+        for t, dtype, nm in zip(rest + [h], _ADAM_TYPES, ("grad", "m", "v", "bf16")):
+            if t is None and nm == "bf16":
+                continue
+            _need(t, dtype, nm)
+            if t.numel() != n or t.device != dev:
+                raise ValueError(f"{nm} must have its parameter's {n} elements on {dev}")
     for k in range(0, len(ps), MAX_TENSORS):
         s = slice(k, k + MAX_TENSORS)
         ptrs = [ptr_array([t.data_ptr() for t in ts[s]]) for ts in (ps, gs, ms, vs)]
