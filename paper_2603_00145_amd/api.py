@@ -459,8 +459,10 @@ def adam_step_many(ps, gs, ms, vs, bfs, lr: float, step: int, beta1: float = 0.9
 
 
 def zero_many(ts):
-    """Zeros into every tensor, in one launch per MAX_TENSORS of them."""
-    if any(not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous() for t in ts):
+    """Zeros into every tensor, in one launch per MAX_TENSORS of them (each by itself where one is not
+    float32, contiguous and on the current device, whose stream the launch goes to)."""
+    if any(not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous() or
+           t.get_device() != torch.cuda.current_device() for t in ts):
         for t in ts:
             t.zero_()
         return

@@ -62,3 +62,35 @@ def test_entries_that_do_not_fit_are_refused(lib, bad):
     with pytest.raises(ValueError):
         api.adam_step_many(*ls, 1e-3, 1)
     assert lib.calls == 0
+
+
+class _DeviceTensor:
+    """A device tensor as zero_many looks at it."""
+    dtype, is_cuda = torch.float32, True
+
+    def __init__(self, device):
+        self.device_index, self.cleared = device, False
+
+    def is_contiguous(self):
+        return True
+
+    def get_device(self):
+        return self.device_index
+
+    def data_ptr(self):
+        return 0
+
+    def numel(self):
+        return 0
+
+    def zero_(self):
+        self.cleared = True
+
+
+@pytest.mark.parametrize("devices,launches", [((0, 0), 1), ((0, 1), 0), ((1, 1), 0)])
+def test_clears_go_to_the_current_device_only(lib, monkeypatch, devices, launches):
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    ts = [_DeviceTensor(d) for d in devices]
+    api.zero_many(ts)
+    assert lib.calls == launches
+    assert all(t.cleared == (launches == 0) for t in ts)
