@@ -87,11 +87,15 @@ constexpr int EPT = WINB / 256;  // ... per thread
 // longest column of lds_column: it reads that many rows whatever the box's length, so at most
 // NK_MAX - 8 rows past the last plane's end (masked where they are used)
 constexpr int NK_MAX = 12;
-constexpr int REGION = RZ * RZS + (NK_MAX - 8) * RX;
+// and a box of fewer than 3 rows is walked from SHIFT rows above it (masked too), which lie PAD floats
+// before the region at most
+constexpr int SHIFT = 2, PAD = SHIFT * RX;
+constexpr int REGION = PAD + RZ * RZS + (NK_MAX - 8) * RX;
 // sort keys of home entries: boxes inside the staged region by (lane passes in x, z planes, y
 // length), each capped; then one key for boxes reaching past the region
 constexpr int KEY_X = 4, KEY_Z = 5, KEY_Y = 12;
 constexpr int NKEY = KEY_X * KEY_Z * KEY_Y + 1;
+constexpr uint32_t KEY_FEW = 1u << (KEY_X + KEY_Z + KEY_Y);   // a round's bit for short boxes
 static_assert(RZS % 32 == 8, "z-plane stride must be 8 mod 32 banks");
 
 // The row of a box that an LDS column's walk counts from.  Q_k and the moments are formed around
@@ -100,18 +104,24 @@ static_assert(RZS % 32 == 8, "z-plane stride must be 8 mod 32 banks");
 // quaternions' gradients of 1M Gaussians on three 256x256x64 stacks were 3 times as far from
 // binary64 (99 of 100 within 2.3e-7 of the largest; now 7.4e-8).  Row 3 gave 5.7e-8, but a larger
 // error in boxes of few rows (the worst centre gradient 1.1e-6 against 3.9e-7).
+// Boxes of one or two rows are walked from SHIFT = YC rows above them and so count from their first:
+// their own row 2 lies outside them, where the exponent of a Gaussian a fraction of a voxel wide is
+// large and cancels in the rows inside (at a width of 0.1 voxel sums were off by 1.8e-5 and second
+// moments wholly lost; counted from their first row 4e-7).  From three rows on row 2 is no further
+// from any row than row 0 is.
 constexpr int YC = 2;
+static_assert(SHIFT == YC, "a short box's first row is the one its walk counts from");
 
 // Column sums s0 = sum ge, s1 = sum k ge, s2 = sum k^2 ge (ge = g 2^Q_k, k = row - YC) over the
 // first NK rows of a column whose rows are RX floats apart in the staged region, all NK reads
 // issued at immediate offsets before the first use; rows past the column (row >= ncol) are masked
-// where they are used.  NK is the wavefront's longest column (up to NK_MAX), a compile-time
-// constant, so the steps carry no branches.  (No contraction: a Gaussian's sums must not depend on
+// where they are used, and so are the first SHIFT of a short box's.  NK is the wavefront's longest
+// column (up to NK_MAX), a compile-time constant, so the steps carry no branches.  (No contraction: a Gaussian's sums must not depend on
 // the NK its wavefront takes.)
 template <int NK, bool MASK>
 __device__ __forceinline__ void lds_column(const float* __restrict__ region, uint32_t off,
-                                           int ncol, float A, float B, float kyy, float& s0,
-                                           float& s1, float& s2)
+                                           bool few, int ncol, float A, float B, float kyy,
+                                           float& s0, float& s1, float& s2)
 {
 #pragma clang fp contract(off)
     float gv[NK];
@@ -121,8 +131,9 @@ __device__ __forceinline__ void lds_column(const float* __restrict__ region, uin
     for (int r = 0; r < NK; ++r) {
         const int k = r - YC;
         const float Q = k == 0 ? A : fmaf((float)k, fmaf((float)k, kyy, B), A);
-        // without MASK every active column of the wavefront is at least NK long
-        const float gr = (r == 0 || !MASK) ? gv[r] : (r < ncol ? gv[r] : 0.0f);
+        // without MASK every active column of the wavefront is at least NK long and none is short
+        const bool in = (r == 0 || r < ncol) && (r >= SHIFT || !few);
+        const float gr = !MASK || in ? gv[r] : 0.0f;
         const float ge = gr * __builtin_amdgcn_exp2f(Q);
         if (r == 0) {
             s0 = ge;
@@ -147,13 +158,13 @@ struct Sheet {
 };
 
 // A lane's sheet of its Gaussian's box: planes 0 .. wz - 1 (none for an inactive lane), whose
-// first voxel is region[off].  max_wz, max_wy: the wavefront's.  Q along a plane's column is
+// walk starts at region[off].  max_wz, max_wy: the wavefront's.  Q along a plane's column is
 // A + k (B + k kyy) with A = Ab + dz (hz + kzz dz) and B = Bx + kyz dz.
 template <int NK, bool MASK>
 __device__ __forceinline__ void lds_sheet(const float* __restrict__ region, uint32_t off, int wz,
-                                          int max_wz, int ncol, int max_wy, float cz, float Ab,
-                                          float hz, float kzz, float Bx, float kyz, float kyy,
-                                          Sheet& S)
+                                          int max_wz, bool few, int ncol, int max_wy, float cz,
+                                          float Ab, float hz, float kzz, float Bx, float kyz,
+                                          float kyy, Sheet& S)
 {
 #pragma clang fp contract(off)
     float zf = 0.0f;
@@ -163,11 +174,11 @@ __device__ __forceinline__ void lds_sheet(const float* __restrict__ region, uint
         // a lane past its planes reads the region's first column and gets A = -inf, so its
         // every term is exactly zero
         const bool in = z < wz;
-        const uint32_t o = in ? off : 0u;
+        const uint32_t o = in ? off : (uint32_t)PAD;
         const float A = in ? fmaf(dz, fmaf(kzz, dz, hz), Ab) : -__builtin_inff();
         const float B = fmaf(kyz, dz, Bx);
         float s0, s1, s2;
-        lds_column<NK, MASK>(region, o, ncol, A, B, kyy, s0, s1, s2);
+        lds_column<NK, MASK>(region, o, few, ncol, A, B, kyy, s0, s1, s2);
         if (NK == NK_MAX) {
 #pragma unroll 1
             for (int r = NK_MAX; r < max_wy; ++r) {
@@ -252,7 +263,8 @@ __device__ __forceinline__ void store_partials(const BackwardArgs& a, int gi, ui
 // A lane takes every BWD_G-th x of its box and walks the (y, z) sheet there, plane by plane, so
 // everything that depends on x alone is formed once, a plane costs three FMAs to set up, and
 // the x moments follow from the sheet's sums at the end.  rb: the round's keys, from bit 0 a bit
-// per y length, then per plane count, then per number of x passes.
+// per number of rows walked, then per plane count, then per number of x passes, then one for short
+// boxes.
 __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_t mine, bool gvalid,
                                           const Rec& rec, const float* __restrict__ region,
                                           int t0x, int t0y, int t0z, uint32_t rb)
@@ -261,7 +273,11 @@ __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_
     const float4 r0 = rec.r0, r1 = rec.r1, r2 = rec.r2, r3 = rec.r3;
     const int lox = __float_as_int(r2.z), loy = __float_as_int(r2.w), loz = __float_as_int(r3.x);
     const int wx = gvalid ? __float_as_int(r3.y) - lox + 1 : 0;
-    const int wy = __float_as_int(r3.z) - loy + 1, wz = __float_as_int(r3.w) - loz + 1;
+    int wy = __float_as_int(r3.z) - loy + 1;
+    const int wz = __float_as_int(r3.w) - loz + 1;
+    const bool few = wy <= SHIFT;
+    const int shift = few ? SHIFT : 0;
+    wy += shift;                                  // rows walked
     const float cx = r0.x, cz = r0.z;
     const float kxx = r1.x, kyy = r1.y, kzz = r1.z, kxy = r1.w;
     const float kxz = r2.x, kyz = r2.y;
@@ -269,17 +285,18 @@ __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_
     int max_wy = 32 - __clz(rb & ((1 << KEY_Y) - 1));
     const int min_wy = __ffs(rb & ((1 << KEY_Y) - 1));
     int max_wz = 32 - __clz((rb >> KEY_Y) & ((1 << KEY_Z) - 1));
-    int max_wx = (32 - __clz(rb >> (KEY_Y + KEY_Z))) * BWD_G;
+    int max_wx = (32 - __clz((rb & ~KEY_FEW) >> (KEY_Y + KEY_Z))) * BWD_G;
     if (max_wy == KEY_Y) max_wy = group_max<BWD_G>(gvalid ? wy : 0);
     if (max_wz == KEY_Z) max_wz = group_max<BWD_G>(gvalid ? wz : 0);
     if (max_wx == KEY_X * BWD_G) max_wx = group_max<BWD_G>(wx);
-    const float dy0 = (float)YC - r0.y;           // dy = dy0 + k at step k of a column
+    const float dy0 = (float)(YC - shift) - r0.y; // dy = dy0 + k at step k of a column
     const float g1 = dy0 * kxy, g2 = dy0 * kyz, A0 = kyy * dy0 * dy0, B0 = 2.0f * kyy * dy0;
-    const uint32_t base = (uint32_t)((loz - t0z) * RZS + (loy - t0y) * RX + (lox - t0x));
+    const uint32_t base =
+        (uint32_t)(PAD + (loz - t0z) * RZS + (loy - t0y - shift) * RX + (lox - t0x));
     Moments v = {};
     float k1 = 0.0f, k2 = 0.0f, k1x = 0.0f, k1z = 0.0f;
     const int nk = min(max_wy, NK_MAX);
-    const bool whole = min_wy >= nk;
+    const bool whole = min_wy >= nk && !(rb & KEY_FEW);
 #pragma unroll 1
     for (int x = ql; x - ql < max_wx; x += BWD_G) {
         const float dx = (float)x - cx;
@@ -290,10 +307,10 @@ __device__ __forceinline__ void lds_round(const BackwardArgs& a, int gi, uint32_
         const float Bx = fmaf(kxy, dx, B0);
         Sheet S = {};
 #define SHEET(K, M) \
-        lds_sheet<K, M>(region, off, nz, max_wz, ncol, max_wy, cz, Ab, hz, kzz, Bx, kyz, kyy, S)
+        lds_sheet<K, M>(region, off, nz, max_wz, few, ncol, max_wy, cz, Ab, hz, kzz, Bx, kyz, kyy, S)
 #define SHEETS(K) case K: if (whole) SHEET(K, false); else SHEET(K, true); break
         switch (nk) {
-        SHEETS(1); SHEETS(2); SHEETS(3); SHEETS(4); SHEETS(5); SHEETS(6); SHEETS(7); SHEETS(8);
+        SHEETS(3); SHEETS(4); SHEETS(5); SHEETS(6); SHEETS(7); SHEETS(8);
         SHEETS(9); SHEETS(10); SHEETS(11);
         default: SHEET(NK_MAX, true); break;
         }
@@ -482,7 +499,7 @@ __device__ __forceinline__ void scan_keys(int* hist, int lane)
 template <bool MASK>
 __global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardArgs a)
 {
-    __shared__ float region[REGION];
+    __shared__ float region[REGION];        // from PAD on
     __shared__ uint32_t order[WINB];
     __shared__ int hist[NKEY + 1];
     __shared__ uint32_t round_box[WINB / PER_ROUND];
@@ -555,7 +572,9 @@ __global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardAr
                 order[pos] = v[h];
                 if (key[h] < NKEY - 1) {
                     const int zx = key[h] / KEY_Y;
-                    atomicOr(&round_box[pos / PER_ROUND], (1u << (key[h] - zx * KEY_Y)) |
+                    const int y = key[h] - zx * KEY_Y;
+                    atomicOr(&round_box[pos / PER_ROUND],
+                             (y < SHIFT ? KEY_FEW | (1u << (y + SHIFT)) : 1u << y) |
                              (1u << (KEY_Y + zx % KEY_Z)) | (1u << (KEY_Y + KEY_Z + zx / KEY_Z)));
                 }
             }
@@ -627,7 +646,7 @@ __global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardAr
                 const int gx = t0x + x, gy = t0y + y;
                 const bool in = gx < nx && gy < ny;
                 const float* src = g + ((size_t)t0z * ny + gy) * nx + gx;
-                float* dst = region + y * RX + x;
+                float* dst = region + PAD + y * RX + x;
                 for (int z = 0; z < nzr; ++z) {
                     dst[z * RZS] = in ? src[0] : 0.0f;
                     src += (size_t)nx * ny;
