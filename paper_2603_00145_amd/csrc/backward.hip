@@ -595,11 +595,13 @@ __global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardAr
             const Rec rec = load_record(a, gi, m);
             lds_round(a, gi, m, valid, rec, region, t0x, t0y, t0z, (uint32_t)sgpr(round_box[r]));
         }
-        // From global memory: eight lanes each, or, when few are left, a wavefront each, whose 64
-        // lanes see a box in one or two reads' latency.  (Some 1.5 of a tile's 244 at the 256^3
-        // workload: eight lanes took 50 us of the kernel's time.  With many, as in the block
-        // query, the wavefronts' latencies overlap: radius 3 on 64^3 266 us a step with eight
-        // lanes, 273 with 16, 309 with 64.)
+        // From global memory: a wavefront each, whose 64 lanes see a box in one or two reads'
+        // latency, or eight lanes each with the block query, whose many small boxes past the region
+        // are better taken eight at a time.  The width is the query's alone, so that a Gaussian's
+        // sums do not depend on the others listed.  Partials of Gaussians 1, 2, 3 and 5 voxels wide
+        // on three 256x256x64 stacks, us with 64 lanes and with 8: 367 and 398, 388 and 616, 390 and
+        // 1048, 251 and 2003 (8 where a window holds more than 16 such boxes: 367, 447, 424, 363);
+        // three 64x64x16 stacks, block query of radius 2, 3 and 4: 93 and 43, 115 and 73, 232 and 166.
         auto from_global = [&](auto g_lanes) {
             constexpr int GG = decltype(g_lanes)::value, PER = 64 / GG;
 #pragma unroll 1
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(256, MASK ? 4 : 5) void k_partials(const BackwardAr
                 global_round<MASK, GG>(a, kk, m, valid, gr, mk);
             }
         };
-        if (n_all - n_lds > 16)
+        if (a.block_query)
             from_global(std::integral_constant<int, 8>{});
         else
             from_global(std::integral_constant<int, 64>{});

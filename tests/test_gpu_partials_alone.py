@@ -1,0 +1,49 @@
+"""A Gaussian's grid-frame partials are its own: the same bits whichever other grids are listed with
+its grid and whichever other Gaussians share its tile, also for boxes that reach past the region a
+block stages (few or many of them to a tile) and with the block query."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_00145_amd import api, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _grid(dims):
+    A = np.zeros((3, 4))
+    for k, m in enumerate(dims):
+        A[k, k], A[k, 3] = m / 2.0, m / 2.0 - 0.5
+    return inputs.Grid(*dims, A, 0.0)
+
+
+def _params(k, rng, size):
+    mean = (np.array([-0.6, -0.55, -0.7]) + rng.uniform(-0.03, 0.03, (k, 3))).astype(np.float32)
+    quat = np.concatenate([np.ones((k, 1)), rng.normal(0, 0.05, (k, 3))], 1).astype(np.float32)
+    ls = (np.log(size) + rng.normal(0, 0.1, (k, 3))).astype(np.float32)
+    return mean, quat, ls, rng.normal(0, 1, k).astype(np.float32)
+
+
+def _partials(arrays, m, grids, ids, dls, radius):
+    p = api.GaussParams.from_host(inputs.Gaussians(*(a[:m] for a in arrays)))
+    b = api.Bins(p.n, grids, capacity=1 << 18, block_radius=radius, cell_resolution=24 if radius else 0)
+    b.bin(p)
+    api.grid_partials(p, b, ids, [dls[i] for i in ids])
+    return b.grid_grads[ids].clone()
+
+
+@pytest.mark.parametrize("radius", [0, 3])
+@pytest.mark.parametrize("size", [0.03, 0.12])       # 1 and 4 voxels of the small grid
+@pytest.mark.parametrize("count", [10, 40, 90])
+def test_partials_do_not_depend_on_company(count, size, radius):
+    rng = np.random.default_rng(count)
+    grids = [_grid((64, 64, 16)), _grid((160, 144, 48)), _grid((64, 48, 20))]
+    dls = [torch.from_numpy(rng.standard_normal(g.shape).astype(np.float32)).cuda() for g in grids]
+    arrays = _params(count, rng, size)
+    every = _partials(arrays, count, grids, [0, 1, 2], dls, radius)
+    for ids in ([0], [1], [0, 2]):
+        got = _partials(arrays, count, grids, ids, dls, radius)
+        assert all(torch.equal(got[i], every[k]) for i, k in enumerate(ids)), ids
+    for m in (1, 8, count - 1):
+        got = _partials(arrays, m, grids, [0, 1, 2], dls, radius)
+        assert torch.equal(got, every[:, :m]), m
