@@ -26,7 +26,7 @@ LIB = os.path.join(HERE, "libgm.so")
 
 SOURCES = ["gm_api.hip", "preprocess.hip", "binning.hip", "render.hip", "backward.hip",
            "optim.hip", "init.hip", "nrf.hip", "nrf_fwd.hip", "warm.hip", "warm_fwd.hip",
-           "warm_train.hip", "ssim.hip"]
+           "warm_train.hip", "ssim.hip", "ssim_tiles.hip"]
 NO_CONTRACT = {"preprocess.hip"}
 # MFMA results in ordinary VGPRs rather than AGPRs: the field's forward reads every accumulator
 # back for the activation, which AGPRs would cost one v_accvgpr_read each (the field's chain

@@ -257,12 +257,12 @@ struct LossArgs {
 hipError_t launch_smooth_l1(const LossArgs& a, float* loss, void* ws, hipStream_t s);
 
 // SSIM term on whole stack slices (Eq. 10): every z-slice is a 2D image, cut into strips of columns
-// and segments of rows (the fields marked * are set by the launcher)
+// and segments of rows or into tiles (the fields marked * are set by the launcher)
 constexpr double GM_SSIM_C1 = 0.01 * 0.01, GM_SSIM_C2 = 0.03 * 0.03;
 struct SsimArgs {
     int32_t n_stacks;
     int32_t nx[GM_MAX_GRIDS], ny[GM_MAX_GRIDS];
-    int32_t tiles_x[GM_MAX_GRIDS], tiles_y[GM_MAX_GRIDS];   // * strips, segments of a slice
+    int32_t tiles_x[GM_MAX_GRIDS], tiles_y[GM_MAX_GRIDS];   // * strips or tiles, and segments or rows of tiles, of a slice
     int32_t rows[GM_MAX_GRIDS];             // * rows of a segment
     int64_t tile_begin[GM_MAX_GRIDS + 1];   // * prefix of nz * tiles_y * tiles_x
     const float* pred[GM_MAX_GRIDS];

@@ -1,5 +1,5 @@
 // SSIM term of the reconstruction loss (Sec. 3.5.2, Eq. 10) on whole stack slices, with its
-// gradient, in one pass down strips of the slices.
+// gradient, in one pass down strips of the slices (small stacks in tiles, ssim_tiles.hip).
 //
 // Every z-slice of a stack is a 2D image.  The SSIM map uses an 11 x 11 Gaussian window (the
 // outer product of 11 taps g, sigma 1.5), zero padding outside the slice, C1 = 0.01^2 and
@@ -34,26 +34,17 @@
 // FP64 sums are added in a fixed order, so loss and gradient are the same on every run.
 #include <utility>
 
-#include "gm_internal.h"
+#include "ssim_core.h"
 
 namespace {
 
-constexpr int R = 5, WN = 2 * R + 1;
+using namespace ssimcore;
+
 constexpr int OUT_X = 64 - 2 * R;                 // output columns of a strip
 constexpr int ROW = 64 + 2 * R;                   // input columns of a strip
-constexpr int MAX_BLOCKS = GM_REDUCE_WORKSPACE_BYTES / 8;   // one FP64 sum each
 // two wavefronts per SIMD (up to 256 registers each) on 256 CUs: all blocks resident at once
-constexpr int SLOTS = 2048;
-static_assert(SLOTS <= MAX_BLOCKS, "a sum for every block");
-
-// 1/d from the hardware reciprocal refined by two Newton steps (error ~1 ulp); here
-// d = b1 b2 lies in [C1 C2, 4.1]
-__device__ __forceinline__ double recip(double d)
-{
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(r, fma(-d, r, 1.0), r);
-    return fma(r, fma(-d, r, 1.0), r);
-}
+constexpr int SIMDS = 1024, SLOTS = 2 * SIMDS;
+static_assert(SLOTS <= MAX_PARTS, "a sum for every block");
 
 struct Lds {
     float x[2][ROW], y[2][ROW];
@@ -298,24 +289,60 @@ __global__ __launch_bounds__(256) void k_ssim_finish(const double* part, int nb,
     if (threadIdx.x == 0) *loss = inv_n > 0.0 ? (float)(1.0 - sh[0] * inv_n) : 0.0f;
 }
 
-// Rows per segment: the stacks' strips are cut so that the rounds of resident wavefronts times the
-// 11-row cycles of a round (20 rows are read on top of the segment's own) are fewest.
-int segment_rows(const SsimArgs& a, const int32_t* nz)
+// Which form a launch takes, and how its strips are cut, by what each is measured to take (us, the
+// loss's sum included).  A wavefront of a strip walks its rows in whole cycles of 11 rows, 20 rows on
+// top of the segment's own and one to finish.  Per cycle, with wavefronts for at most 1, 2, 3 or 4
+// times the chip's SIMDs:
+//     wavefronts     up to 1024   2048   3072   4096   6144
+//     us a cycle     9 - 11       15     21     29     42
+// A lone wavefront's rows are one dependent chain, so that a second on its SIMD adds half of its time
+// and a short segment still costs three cycles.  The tiles of ssim_tiles.hip take 14, 24.5, 35, 53, 87,
+// 163 and 330 us for up to 1, 2, 3, 5, 9, 18 and 38 times 256 tiles.  So the tiles are faster where
+// they are few, or where the strips' 54 columns are badly filled.  Three stacks of square slices, us in
+// tiles and in strips (the rule takes the smaller but for 72 of 128 x 128, 53.6):
+//     slices      18        36        72       144       288       576
+//     33 x 33               14 26     25 27    36 28     54 30     88 43
+//     54 x 54     14 26     14 26     25 28    35 29     54 38     88 58
+//     55 x 55     14 26     14 27     25 30    36 38     54 58     88 101
+//     64 x 64     14 26     14 28     25 30    35 39     54 61     87 100
+//     80 x 80     14 26     24 28     34 30    61 46     102 72    185 121
+//     128 x 128   24 29     35 39     54 51    88 76     163 122
+//     256 x 256   54 46     88 74     163 106
+double strip_us(int64_t wavefronts, int64_t rows)
 {
-    int best = 1 << 30;
-    int64_t least = INT64_MAX;
+    const int64_t n = (wavefronts + SIMDS - 1) / SIMDS;
+    const double cycle = n <= 1 ? 8.9 + 2.3 / SIMDS * (double)wavefronts
+                                : 14.8 * (double)(n / 2) + 6.3 * (double)(n % 2);
+    return cycle * (double)((rows + 4 * R + 1 + WN - 1) / WN);
+}
+double tiles_us(int64_t tiles)
+{
+    const double n = (double)((tiles + 255) / 256), few = 4.0 + 10.2 * n, many = 9.0 + 8.8 * n;
+    return few < many ? few : many;
+}
+
+struct Plan {
+    int rows;          // of a strip's segment; 0: tiles
+    double us;
+};
+
+Plan plan(const SsimArgs& a, const int32_t* nz)
+{
+    int64_t tiles = 0;
     int most = 1;
-    for (int k = 0; k < a.n_stacks; ++k) most = a.ny[k] > most ? a.ny[k] : most;
+    for (int k = 0; k < a.n_stacks; ++k) {
+        most = a.ny[k] > most ? a.ny[k] : most;
+        tiles += (int64_t)nz[k] * ((a.nx[k] + SSIM_TILE - 1) / SSIM_TILE) *
+                 ((a.ny[k] + SSIM_TILE - 1) / SSIM_TILE);
+    }
+    Plan best = {0, tiles_us(tiles)};
     for (int segs = 1; segs <= 64; ++segs) {
         const int rows = (most + segs - 1) / segs;
         int64_t items = 0;
         for (int k = 0; k < a.n_stacks; ++k)
-            items += (int64_t)nz[k] * a.tiles_x[k] * ((a.ny[k] + rows - 1) / rows);
-        const int64_t cost = (items + SLOTS - 1) / SLOTS * ((rows + 4 * R + 1 + WN - 1) / WN);
-        if (cost < least) {
-            least = cost;
-            best = rows;
-        }
+            items += (int64_t)nz[k] * ((a.nx[k] + OUT_X - 1) / OUT_X) * ((a.ny[k] + rows - 1) / rows);
+        const double us = strip_us(items, rows);
+        if (us < best.us) best = {rows, us};
         if (rows <= 4) break;
     }
     return best;
@@ -327,18 +354,22 @@ hipError_t launch_ssim(SsimArgs& a, const int32_t* nz, int64_t n_voxels, float* 
                        hipStream_t s)
 {
     double* part = reinterpret_cast<double*>(ws);
-    for (int k = 0; k < a.n_stacks; ++k) a.tiles_x[k] = (a.nx[k] + OUT_X - 1) / OUT_X;
-    const int rows = segment_rows(a, nz);
+    const int rows = plan(a, nz).rows;
+    const int w = rows ? OUT_X : SSIM_TILE, h = rows ? rows : SSIM_TILE;
     int64_t total = 0;
     for (int k = 0; k < a.n_stacks; ++k) {
-        a.rows[k] = rows;
-        a.tiles_y[k] = (a.ny[k] + rows - 1) / rows;
+        a.rows[k] = h;
+        a.tiles_x[k] = (a.nx[k] + w - 1) / w;
+        a.tiles_y[k] = (a.ny[k] + h - 1) / h;
         a.tile_begin[k] = total;
         total += (int64_t)nz[k] * a.tiles_x[k] * a.tiles_y[k];
     }
     a.tile_begin[a.n_stacks] = total;
-    const int nb = (int)(total < SLOTS ? total : SLOTS);
-    if (nb > 0) hipLaunchKernelGGL(k_ssim, dim3((unsigned)nb), dim3(64), 0, s, a, part);
+    int nb = (int)(total < SLOTS ? total : SLOTS);
+    if (!rows)
+        nb = launch_ssim_tiles(a, part, s);
+    else if (nb > 0)
+        hipLaunchKernelGGL(k_ssim, dim3((unsigned)nb), dim3(64), 0, s, a, part);
     hipLaunchKernelGGL(k_ssim_finish, dim3(1), dim3(256), 0, s, part, nb,
                        n_voxels > 0 ? 1.0 / (double)n_voxels : 0.0, loss);
     return hipGetLastError();
