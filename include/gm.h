@@ -435,7 +435,8 @@ gm_status gm_adam_many(int32_t count, float* const* params, const float* const* 
                        double lr, double beta1, double beta2, double eps, int32_t step,
                        gm_stream stream);
 
-/* Fill count tensors (at most GM_MAX_TENSORS) of n[k] floats with zeros in one launch. */
+/* Fill count tensors (at most GM_MAX_TENSORS) of n[k] floats with zeros in one launch; they may
+ * start at any float. */
 gm_status gm_zero_many(int32_t count, float* const* tensors, const int64_t* n, gm_stream stream);
 
 /* Devoxelization initialisation (Sec. 3.1; Fig. 1b): fill n = g^3 Gaussians (g >= 1) laid on

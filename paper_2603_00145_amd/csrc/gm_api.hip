@@ -1276,7 +1276,8 @@ gm_status gm_zero_many(int32_t count, float* const* tensors, const int64_t* n, g
         if (n[k] < 0) return fail(GM_ERR_INVALID_ARGUMENT, "n[%d] < 0", k);
         t.n[k] = n[k];
         if (n[k] == 0) continue;
-        REQ_PTR(tensors[k], "tensors[k]");
+        // (written float by float: views that start anywhere in a buffer are as good)
+        if (!tensors[k]) return fail(GM_ERR_INVALID_ARGUMENT, "tensors[%d] NULL", k);
         t.p[k] = tensors[k];
     }
     GM_HIP(launch_zero_many(t, reinterpret_cast<hipStream_t>(stream)), "zero tensors");

@@ -35,3 +35,14 @@ def test_many_equal_separate_calls(sizes):
     guard = [torch.cat([t, torch.ones(5, device="cuda")]) for t in p]
     api.zero_many([t[:n] for t, n in zip(guard, sizes)])
     assert all(not t[:n].any() and bool((t[n:] == 1).all()) for t, n in zip(guard, sizes))
+
+
+def test_clears_of_views_at_any_offset():
+    """Gradients that are views into one buffer are cleared wherever they start, and nothing else."""
+    flat = torch.ones(4096, device="cuda")
+    spans = [(1, 5), (7, 1030), (1041, 1042), (2003, 4095)]
+    api.zero_many([flat[a:b] for a, b in spans])
+    ref = torch.ones(4096)
+    for a, b in spans:
+        ref[a:b] = 0
+    assert torch.equal(flat.cpu(), ref)
