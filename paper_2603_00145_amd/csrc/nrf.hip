@@ -20,7 +20,13 @@ namespace {
 
 using namespace nrfcore;
 
-constexpr int MAX_BLOCKS = 512;      // two blocks on each of 256 CUs, all resident at once
+constexpr int FULL = 512;            // two blocks on each of 256 CUs, all resident at once
+// A block's FP32 sums run over all its rounds, and their error grows with that: from 1M points on the
+// launch takes FULL blocks more for every CUT rounds of one, up to MAX_BLOCKS (1.1 GB of partials).
+// Every voxel of 256^3 in one call, against the sum of small calls: off by 2.8e-7 of the largest
+// first-layer weight gradient, 1.4e-6 with 512 rounds a block, in the same 2.95 ms (3.21 ms with 16
+// rounds a block, no closer).
+constexpr int CUT = 32, MAX_BLOCKS = 32 * FULL;
 
 // Floats of one block's partial gradients: dW of the first layer in the GPU's K order [W][16 KT],
 // the hidden layers' [depth - 1][W][W], the biases [depth][W], w_out [W], b_out
@@ -140,8 +146,10 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
 #pragma unroll
     for (int l = 0; l < DEPTH; ++l) accb[l] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     // the output layer's gradient over this wavefront's points: gwo[4 o + j] for feature
-    // 16 o + 4 g + j (sum of dzo a_D), gbo the sum of dzo (lanes of group 0)
-    float gwo[16], gbo = 0.0f;
+    // 16 o + 4 g + j (sum of dzo a_D), gbo the sum of dzo (lanes of group 0; of terms of either sign,
+    // it cancels the most)
+    float gwo[16];
+    double gbo = 0.0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) gwo[i] = 0.0f;
 
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
         for (int o = 0; o < 4; ++o)
 #pragma unroll
             for (int j = 0; j < 4; ++j) s.out[wv][16 * o + 4 * g + j] = gwo[4 * o + j];
-        if (g == 0) s.out[wv][W] = gbo;
+        if (g == 0) s.out[wv][W] = (float)gbo;
     }
     __syncthreads();
     if (threadIdx.x <= W)
@@ -297,7 +305,8 @@ __global__ __launch_bounds__(256, DEPTH < 4 ? 2 : 1) void k_nrf_grad(const NrfAr
 // Every gradient += the sum of its nb partials, in a fixed order: 64 elements per block, whose
 // SUM_WAVES wavefronts share the partials (partial c to wavefront c mod SUM_WAVES), each with
 // four independent accumulators so that its loads are in flight together, then the wavefronts'
-// sums are added in order.  The first layer's weights go from the GPU's K order to the natural
+// sums are added in order.  In binary64, which takes no longer here: with the blocks' b_out sums,
+// 262144 points' gradients are 2.0e-7 from the exact sums in place of 5.4e-7.  The first layer's weights go from the GPU's K order to the natural
 // one (padding slots are dropped).
 constexpr int SUM_WAVES = 16;
 constexpr int SUM_THREADS = 64 * SUM_WAVES;
@@ -307,10 +316,10 @@ __global__ __launch_bounds__(SUM_THREADS) void k_nrf_sums(const NrfArgs a,
                                                           const float* __restrict__ part, int nb)
 {
     constexpr int N = 16 * KT, n = part_floats(N, DEPTH);
-    __shared__ float sh[SUM_WAVES][64];
+    __shared__ double sh[SUM_WAVES][64];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     int e = blockIdx.x * 64 + l;
-    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     if (e < n) {
         const float* p = part + e;
         int c = w;
@@ -325,9 +334,10 @@ __global__ __launch_bounds__(SUM_THREADS) void k_nrf_sums(const NrfArgs a,
     sh[w][l] = (a0 + a1) + (a2 + a3);
     __syncthreads();
     if (threadIdx.x >= 64 || e >= n) return;
-    float sum = 0.0f;
+    double all = 0.0;
 #pragma unroll
-    for (int i = 0; i < SUM_WAVES; ++i) sum += sh[i][l];
+    for (int i = 0; i < SUM_WAVES; ++i) all += sh[i][l];
+    const float sum = (float)all;
     if (e < W * N) {
         const int nf = natural_feature<KT>(e % N, a.n_freq);
         if (nf >= 0) a.g_w_in[e / N * N + nf] += sum;
@@ -357,7 +367,12 @@ __global__ __launch_bounds__(256) void k_to_bf16(const float* __restrict__ in,
         out[i] = to_bf16(in[i]);
 }
 
-int grad_blocks(int64_t rounds) { return (int)(rounds < MAX_BLOCKS ? rounds : MAX_BLOCKS); }
+int grad_blocks(int64_t rounds)
+{
+    if (rounds < FULL) return (int)rounds;
+    const int64_t nb = (rounds + FULL * CUT - 1) / (FULL * CUT) * FULL;
+    return (int)(nb < MAX_BLOCKS ? nb : MAX_BLOCKS);
+}
 
 template <int KT, int DEPTH>
 void launch_grad_t(const NrfArgs& a, const NrfGrids& gs, float* part, hipStream_t s)
