@@ -113,3 +113,44 @@ def test_long_sums_stay_close():
             total[k] += v
     for k, v in total.items():
         assert (one[k] - v).abs().max() <= 2.0 ** -21 * v.abs().max(), k
+
+
+@pytest.mark.parametrize("n_freq", [6, 16])
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+@pytest.mark.parametrize("counts", [(1,), (16,), (64, 0, 17), (65, 63)])
+def test_every_point_counts(n_freq, depth, counts):
+    """One call over short lists against its points one by one at the same scales: the same terms in
+    another order of the FP32 sums, and without a list's last point (left out of the reference) further
+    off than that order can be."""
+    rng = np.random.default_rng(n_freq + 10 * depth + counts[0])
+    net = nrf.NRF(n_freq=n_freq, depth=depth, seed=4, zero_last=False)
+    grids = [inputs.stack_grid(v, 24, 6, 1.0, *inputs.random_rigid(rng, 2, 1, 24))
+             for v in ("axial", "coronal", "sagittal")[:len(counts)]]
+    dls = [torch.from_numpy(rng.uniform(0.5, 1.5, g.shape).astype(np.float32)).cuda() for g in grids]
+    idxs = [torch.from_numpy(rng.choice(g.n_voxels, size=c, replace=False).astype(np.int32)).cuda()
+            for g, c in zip(grids, counts)]
+    net.zero_grad()
+    _, scales = net.backward_grids(grids, dls, idxs=idxs)
+    got = {k: v.double() for k, v in net.g.items()}
+    lib, net_s = _lib.load(), net.struct()
+    ref, mag, last = ({k: torch.zeros_like(v) for k, v in got.items()} for _ in range(3))
+    lists = [i for i, c in enumerate(counts) if c]
+    for i in lists:
+        for p in range(counts[i]):
+            net.zero_grad()
+            one, grads = idxs[i][p:p + 1].clone(), net.grads_struct()
+            _lib.check(lib.gm_nrf_backward(
+                ctypes.byref(net_s), ctypes.byref(_lib.grid_struct(grids[i])),
+                ctypes.c_void_p(one.data_ptr()), 1, ctypes.c_void_p(dls[i].data_ptr()), float(scales[i]),
+                ctypes.byref(grads), ctypes.c_void_p(net._ws.data_ptr()), net._ws.numel() * 4,
+                api._stream()))
+            for k, v in net.g.items():
+                ref[k] += v.double()
+                mag[k] += v.double().abs()
+                if i == lists[-1] and p == counts[i] - 1:
+                    last[k] = v.double()
+    off = {k: float((got[k] - ref[k]).abs().max() / mag[k].max().clamp_min(1e-30)) for k in ref}
+    assert max(off.values()) <= 1e-5, off
+    missing = {k: float((got[k] - (ref[k] - last[k])).abs().max() / mag[k].max().clamp_min(1e-30))
+               for k in ref}
+    assert max(missing.values()) > 1e-3, missing
