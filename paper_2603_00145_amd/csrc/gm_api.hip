@@ -503,6 +503,14 @@ gm_status gm_bin(const gm_gaussians* g, const gm_grid* grids, int32_t n_grids,
     return GM_OK;
 }
 
+// the list length of the bins' tiles on average
+static int32_t mean_list(const gm_bins* bins)
+{
+    int64_t tiles = 0;
+    for (int k = 0; k < bins->n_grids; ++k) tiles += grid_tiles(bins->grids[k]);
+    return tiles > 0 ? (int32_t)(bins->n_pairs / tiles) : 0;
+}
+
 // The loss fields (targets, dl, loss) are NULL for a plain render; with them the render also
 // writes the smooth-L1 gradient and loss, and outs (the array or an entry) may be NULL.
 struct RenderLoss {
@@ -587,6 +595,7 @@ static gm_status render_impl(const gm_bins* bins, const int32_t* ids, int32_t n_
     REQ_PTR(bins->tile_start, "bins->tile_start");
     ra.n_render = n_ids;
     ra.total_blocks = (int32_t)blocks;
+    ra.mean_list = mean_list(bins);
     ra.n_gauss = bins->n_gauss;
     ra.records = bins->records;
     ra.tile_start = bins->tile_start;

@@ -159,6 +159,7 @@ struct RenderArgs {
     int32_t total_blocks;
     int32_t parts_log2;      // every tile's list is cut into 2^this parts (set by the launcher)
     int32_t part0;           // loss_part entry of the launch's first tile (set by the launcher)
+    int32_t mean_list;       // (tile, Gaussian) pairs per tile over the bins' grids
     int64_t n_gauss;
     const float* records;
     const int32_t* tile_start;

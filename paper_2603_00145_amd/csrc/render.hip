@@ -294,14 +294,17 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
     // PARTS: the sum of the finished parts, lane's columns lane + 64 j, and the next part's start
     float4 tot[4] = {};
     int k = k0 + 1, next = PARTS ? L.part_start(k0 + 1) : 0;
-    auto flush = [&]() {
+    // the part that ends before entry b is added; parts without entries would add zeros
+    auto flush = [&](int b) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             tot[j] = add4(tot[j], acc[j * 64 + lane]);     // 0 + v = v: no value is negative
             acc[j * 64 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        ++k;
-        next = L.part_start(k);
+        do {
+            ++k;
+            next = L.part_start(k);
+        } while (k < k0 + np && b >= next);
     };
     const RenderGrid& G = *P.G;
     const int t0x = P.t0x, t0y = P.t0y, t0z = P.t0z;
@@ -352,7 +355,7 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
         id_next = load_id(b0 + 2 * RB);
         wave_sync();
         if (PARTS)
-            while (b0 >= next && k < k0 + np) flush();
+            if (b0 >= next && k < k0 + np) flush(b0);
         // this lane's piece: footprint area with its first and last columns in x and y (4 bits
         // each, from bit 9 on), and its place in the batch
         int myF = 0, pos = lane;
@@ -447,10 +450,9 @@ __device__ __forceinline__ void accumulate_tile(const RenderArgs& a, const TileP
         }
     }
     wave_sync();
-    if (PARTS) {
-        while (k <= k0 + np) flush();
+    if (PARTS && k > k0 + 1) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j * 64 + lane] = tot[j];
+        for (int j = 0; j < 4; ++j) acc[j * 64 + lane] = add4(tot[j], acc[j * 64 + lane]);
         wave_sync();
     }
 }
@@ -541,6 +543,21 @@ __global__ __launch_bounds__(64 * NW) void k_render(const RenderArgs a)
                                   nullptr);
     __syncthreads();
     finish_tile<NW, 64 * NW>(a, P, sh.accs, tv, threadIdx.x, a.part0 + blk, red);
+}
+
+// k_render with one wavefront for all of a tile's parts (up to 8), the same sums: for lists too short
+// to share (one_wavefront), where what counts is how many tiles are in flight (six wavefronts per SIMD;
+// with the targets of the loss held over the walk four, and 320^3 with lists of 83 took 185 us, not 160)
+__global__ __launch_bounds__(64, 6) void k_render_one(const RenderArgs a)
+{
+    __shared__ TileLds<1> sh;
+    const int lane = threadIdx.x;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const TilePos P = tile_pos(a, blk);
+    accumulate_tile<false, true>(a, P, sh.accs, sh.pcs[0], lane, 0, 1 << a.parts_log2, nullptr, nullptr);
+    float tv[cols_per_thread<64>()][GM_TZ];
+    if (a.loss_part) load_targets<64>(P, lane, tv);
+    finish_tile<1, 64>(a, P, sh.accs, tv, lane, a.part0 + blk, nullptr);
 }
 
 // k_render for launches that hold a masked grid (the block query on a rotated grid)
@@ -749,12 +766,29 @@ bool any_masked(const RenderArgs& a)
     return masked;
 }
 
+// Whether the tiles of a launch are better taken by a wavefront each than by one per part: where the
+// parts' wavefronts are more than the chip holds at a time (26 a CU) and the lists are short on average
+// (a list of one batch is one part's whatever their number; the others' wavefronts only keep tiles
+// waiting).  us with the parts' wavefronts and with one, by list length, 1- and 8-voxel Gaussians alike:
+//     128^3 (2048 tiles, 4 parts)     15: 14, 11     32: 31, 27     79: 21, 27     159: 33, 45
+//     three 128x128x32 (1536, 8)      12: 28, 19     48: 55, 50     68: 60, 68     199: 29, 53
+//     256^3 (16384, 4)                16: 64, 33     83: 103, 94    166: 176, 169  416: 374, 400
+//     three 256x256x64 (12288, 4)     17: 109, 57    85: 226, 217   171: 411, 407  419: 310, 326
+//     320^3 (32000, 2)                18: 122, 91    83: 167, 160   167: 295, 297
+bool one_wavefront(const RenderArgs& a, int np)
+{
+    const int64_t waves = (int64_t)a.total_blocks * np;
+    return np <= GROUPS && a.mean_list * waves < 170 * (waves - 26 * 256);
+}
+
 template <int NW>
 void launch_render_t(const RenderArgs& a, hipStream_t s)
 {
     const dim3 grid((unsigned)a.total_blocks), block(64 * NW);
     if (any_masked(a))
         hipLaunchKernelGGL(k_render_block<NW>, grid, block, 0, s, a);
+    else if (one_wavefront(a, NW))
+        hipLaunchKernelGGL(k_render_one, grid, dim3(64), 0, s, a);
     else
         hipLaunchKernelGGL(k_render<NW>, grid, block, 0, s, a);
 }
