@@ -942,10 +942,14 @@ __global__ __launch_bounds__(POSE_BLOCKS) void k_pose_sum(const double* part, in
 // each part pays the sort and the staging again.  Three 64x64x16 stacks (192 tiles): a step of
 // 128 us with four parts, 137 with one, 129 with eight; three 96x96x24 (648 tiles): 196 with two,
 // 191 with one.  The block query's boxes are many times larger than the staging, and a part more
-// even: 192 tiles at radius 3, 271 us with 16 parts, 286 with 8, 550 with one, 277 with 32.
+// even: 192 tiles at radius 3, 271 us with 16 parts, 286 with 8, 550 with one, 277 with 32.  Beyond what
+// fills the chip once its parts only add launches' ends: the partials alone of three rotated stacks
+// at radius 2 with 1, 2, 4 and 8 parts, us: 375 tiles 371, 296, 256, 198; 648: 411, 449, 345, 320; 1029:
+// 486, 593, 527, 511; 1536: 655, 831, 777, 772; 3000: 1709, 2672, 2550, 1941 (axis-aligned 98 to 71, 89
+// to 95, 119 to 176, 141 to 281, 419 to 721).
 static int partial_parts_log2(int64_t tiles, bool block_query)
 {
-    const int64_t blocks = block_query ? 4096 : 1024;
+    const int64_t blocks = !block_query ? 1024 : tiles <= 768 ? 4096 : 0;
     int lg = 0;
     while (lg < 4 && tiles << (lg + 1) <= blocks) ++lg;
     return lg;
