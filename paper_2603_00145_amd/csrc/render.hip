@@ -772,13 +772,16 @@ bool any_masked(const RenderArgs& a)
 // waiting).  us with the parts' wavefronts and with one, by list length, 1- and 8-voxel Gaussians alike:
 //     128^3 (2048 tiles, 4 parts)     15: 14, 11     32: 31, 27     79: 21, 27     159: 33, 45
 //     three 128x128x32 (1536, 8)      12: 28, 19     48: 55, 50     68: 60, 68     199: 29, 53
+//     200^3 (8450, 4)                 77: 56, 54     83: 107, 114   145: 89, 93    155: 92, 97
+//     three 256x256x64 (12288, 4)     17: 109, 57    152: 214, 195  209: 165, 168  249: 196, 202
 //     256^3 (16384, 4)                16: 64, 33     83: 103, 94    166: 176, 169  416: 374, 400
-//     three 256x256x64 (12288, 4)     17: 109, 57    85: 226, 217   171: 411, 407  419: 310, 326
 //     320^3 (32000, 2)                18: 122, 91    83: 167, 160   167: 295, 297
+// The line through where the two meet: lists of 38 where the parts just fill the chip, 25 more for
+// every time they fill it again, up to 200.
 bool one_wavefront(const RenderArgs& a, int np)
 {
-    const int64_t waves = (int64_t)a.total_blocks * np;
-    return np <= GROUPS && a.mean_list * waves < 170 * (waves - 26 * 256);
+    const double fill = (double)a.total_blocks * np / (26 * 256);
+    return np <= GROUPS && fill > 1.0 && a.mean_list < fmin(200.0, 38.0 + 25.0 * (fill - 1.0));
 }
 
 template <int NW>
