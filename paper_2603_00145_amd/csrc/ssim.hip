@@ -98,10 +98,17 @@ __device__ __forceinline__ void cycle(F& row, int& r, std::integer_sequence<int,
     ((row(std::integral_constant<int, P>{}), ++r), ...);
 }
 
-__global__ __launch_bounds__(64, 2) void k_ssim(const SsimArgs a, double* part)
+// Four strips to a block, one on each SIMD of its CU (blocks of one wavefront fall on the SIMDs as the
+// launch before left them: 40 us or 56 for the same 920).  ALONE: a block takes so much LDS that a
+// CU holds no second one while others are empty.
+constexpr int WPB = 4;
+template <bool ALONE>
+__global__ __launch_bounds__(64 * WPB, ALONE ? 1 : 2) void k_ssim(const SsimArgs a, double* part, int nw)
 {
-    __shared__ Lds s;
-    const int lane = threadIdx.x;
+    __shared__ struct { Lds w[WPB]; char room[ALONE ? 72 * 1024 : 1]; } all;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = (int)blockIdx.x * WPB + w;
+    Lds& s = all.w[w];
     const int64_t total = a.tile_begin[a.n_stacks];
     double ssum = 0.0;
     if (lane < R) {            // the columns past the strip's lanes: read, never used
@@ -109,7 +116,7 @@ __global__ __launch_bounds__(64, 2) void k_ssim(const SsimArgs a, double* part)
         for (int q = 0; q < 3; ++q) s.u[q][lane] = s.u[q][64 + R + lane] = 0.0;
     }
 #pragma unroll 1
-    for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
+    for (int64_t t = first; t < total; t += gridDim.x * WPB) {
         const Strip S = strip(a, t);
         const int X = S.x0 - R + lane;                       // the lane's map column
         const bool in_x = X >= 0 && X < S.nx;
@@ -271,7 +278,7 @@ __global__ __launch_bounds__(64, 2) void k_ssim(const SsimArgs a, double* part)
         while (r < r_end) cycle(row, r, std::make_integer_sequence<int, WN>{});
     }
     for (int o = 32; o > 0; o >>= 1) ssum += __shfl_xor(ssum, o, 64);
-    if (lane == 0) part[blockIdx.x] = ssum;
+    if (lane == 0 && first < nw) part[first] = ssum;
 }
 
 __global__ __launch_bounds__(256) void k_ssim_finish(const double* part, int nb, double inv_n,
@@ -294,20 +301,20 @@ __global__ __launch_bounds__(256) void k_ssim_finish(const double* part, int nb,
 // top of the segment's own and one to finish.  Per cycle, with wavefronts for at most 1, 2, 3 or 4
 // times the chip's SIMDs:
 //     wavefronts     up to 1024   2048   3072   4096   6144
-//     us a cycle     9 - 11       15     21     29     42
+//     us a cycle     9 - 12       15     20     28     41
 // A lone wavefront's rows are one dependent chain, so that a second on its SIMD adds half of its time
 // and a short segment still costs three cycles.  The tiles of ssim_tiles.hip take 14, 24.5, 35, 53, 87,
 // 163 and 330 us for up to 1, 2, 3, 5, 9, 18 and 38 times 256 tiles.  So the tiles are faster where
 // they are few, or where the strips' 54 columns are badly filled.  Three stacks of square slices, us in
 // tiles and in strips (the rule takes the smaller but for 72 of 128 x 128, 53.6):
 //     slices      18        36        72       144       288       576
-//     33 x 33               14 26     25 27    36 28     54 30     88 43
-//     54 x 54     14 26     14 26     25 28    35 29     54 38     88 58
-//     55 x 55     14 26     14 27     25 30    36 38     54 58     88 101
-//     64 x 64     14 26     14 28     25 30    35 39     54 61     87 100
-//     80 x 80     14 26     24 28     34 30    61 46     102 72    185 121
-//     128 x 128   24 29     35 39     54 51    88 76     163 122
-//     256 x 256   54 46     88 74     163 106
+//     33 x 33               14 28     25 28    36 28     54 30     88 44
+//     54 x 54     14 27     14 28     25 28    35 29     54 38     88 57
+//     55 x 55     14 27     14 28     25 29    36 39     54 57     88 100
+//     64 x 64     14 27     14 28     25 29    35 39     54 57     87 93
+//     80 x 80     14 27     24 28     34 30    61 46     102 71    185 120
+//     128 x 128   24 28     35 39     54 50    88 76     163 121
+//     256 x 256   54 46     88 75     163 106
 double strip_us(int64_t wavefronts, int64_t rows)
 {
     const int64_t n = (wavefronts + SIMDS - 1) / SIMDS;
@@ -368,8 +375,13 @@ hipError_t launch_ssim(SsimArgs& a, const int32_t* nz, int64_t n_voxels, float* 
     int nb = (int)(total < SLOTS ? total : SLOTS);
     if (!rows)
         nb = launch_ssim_tiles(a, part, s);
-    else if (nb > 0)
-        hipLaunchKernelGGL(k_ssim, dim3((unsigned)nb), dim3(64), 0, s, a, part);
+    else if (nb > 0) {
+        const dim3 grid((unsigned)((nb + WPB - 1) / WPB)), block(64 * WPB);
+        if (nb <= SIMDS)
+            hipLaunchKernelGGL(k_ssim<true>, grid, block, 0, s, a, part, nb);
+        else
+            hipLaunchKernelGGL(k_ssim<false>, grid, block, 0, s, a, part, nb);
+    }
     hipLaunchKernelGGL(k_ssim_finish, dim3(1), dim3(256), 0, s, part, nb,
                        n_voxels > 0 ? 1.0 / (double)n_voxels : 0.0, loss);
     return hipGetLastError();

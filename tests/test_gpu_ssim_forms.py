@@ -74,3 +74,35 @@ def test_small_stacks_take_the_time_of_a_tile(shape):
         b.synchronize()
         best = min(best, a.elapsed_time(b) * 1e3 / 20)
     assert best < 20, best
+
+
+def test_strips_do_not_depend_on_the_launch_before():
+    """920 strips, fewer than the chip's 1024 SIMDs: one to a SIMD whatever ran before.  As blocks of one
+    wavefront they shared SIMDs after a large launch, 56 us in place of 40."""
+    x = [torch.rand((23, 74, 74), device="cuda") for _ in range(5)]
+    y, d = [torch.rand_like(a) for a in x], [torch.zeros_like(a) for a in x]
+    big = torch.zeros(40_000_000, device="cuda")
+
+    def best(*calls):
+        """us of the calls, replayed from a graph of ten times all of them."""
+        for f in calls:
+            f()
+        torch.cuda.synchronize()
+        g, st = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        st.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(g, stream=st):
+            for _ in range(10):
+                for f in calls:
+                    f()
+        t = 1e9
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.replay()
+            b.record()
+            b.synchronize()
+            t = min(t, a.elapsed_time(b) * 1e2)
+        return t
+    ssim, fill = lambda: api.ssim_loss(x, y, d, 0.5), lambda: big.fill_(1.0)
+    alone = best(ssim)
+    assert best(fill, ssim) - best(fill) <= 1.2 * alone, alone
