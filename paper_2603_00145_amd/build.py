@@ -29,8 +29,7 @@ SOURCES = ["gm_api.hip", "preprocess.hip", "binning.hip", "render.hip", "backwar
            "warm_train.hip", "ssim.hip", "ssim_tiles.hip"]
 NO_CONTRACT = {"preprocess.hip"}
 # MFMA results in ordinary VGPRs rather than AGPRs: the field's forward reads every accumulator
-# back for the activation, which AGPRs would cost one v_accvgpr_read each (the field's chain
-# kernel, in nrf.hip, holds more live registers and runs 3% slower so built)
+# back for the activation, which AGPRs would cost one v_accvgpr_read each
 MFMA_VGPR = {"nrf_fwd.hip"}
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

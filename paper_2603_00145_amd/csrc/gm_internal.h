@@ -6,7 +6,7 @@
 
 #include "../../include/gm.h"
 
-// Tile of the forward render: one wavefront owns one tile and accumulates it in LDS.
+// Tile of the forward render, accumulated in LDS by one wavefront or by several that share its list.
 #define GM_TX 16
 #define GM_TY 16
 #define GM_TZ 4

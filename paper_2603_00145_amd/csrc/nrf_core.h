@@ -198,10 +198,6 @@ struct Tile {
     }
 };
 
-// Where tile_forward takes the layers' MFMA A operands from: the LDS stage, read at each use,
-// or the wavefront's registers (each lane its piece of every operand, 2 KT + 8 (DEPTH - 1)
-// pieces, copied once from the stage; the per-tile LDS reads of the weights, 512 bytes per lane,
-// then disappear).
 // the lane's four biases of o-tile o of layer l
 __device__ __forceinline__ v4f global_bias(const NrfArgs& a, int l, int o)
 {
@@ -209,6 +205,10 @@ __device__ __forceinline__ v4f global_bias(const NrfArgs& a, int l, int o)
     const float* b = l == 0 ? a.b_in : a.b_hid + (l - 1) * W;
     return v4f{b[f], b[f + 1], b[f + 2], b[f + 3]};
 }
+// Where tile_forward_w takes the layers' MFMA A operands from: the LDS stage, read at each use,
+// or the wavefront's registers (each lane its piece of every operand, 2 KT + 8 (DEPTH - 1)
+// pieces, copied once from the stage; the per-tile LDS reads of the weights, 512 bytes per lane,
+// then disappear).
 template <int KT, int DEPTH>
 struct WeightsLds {
     const Lds<KT, DEPTH>& s;

@@ -108,9 +108,9 @@ class NRF:
 
     def backward_grids(self, grids, dls, idxs=None, n_sample: Optional[int] = None,
                        generator: Optional[torch.Generator] = None):
-        """backward over several grids in one call (one chain pass per grid, the weight
-        gradients over all the points at once): the gradient of sum over grids k of
-        scale_k * sum_j dls[k][v_kj] r(x_{v_kj}), point lists as for backward."""
+        """backward over several grids in one call (one launch over all their points): the
+        gradient of sum over grids k of scale_k * sum_j dls[k][v_kj] r(x_{v_kj}), point lists as
+        for backward."""
         n = len(grids)
         if n != len(dls) or (idxs is not None and len(idxs) != n):
             raise ValueError("grids, dls and idxs differ in length")
