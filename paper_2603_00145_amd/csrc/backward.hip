@@ -488,7 +488,7 @@ __device__ __forceinline__ void scan_keys(int* hist, int lane)
 // round, so the order the atomics give within a key does not change any result bit.  Gaussians
 // with an empty box are in no list; gm_bin wrote their zeros.
 //
-// Bound by vector issue (169 M VALU instructions at the 256^3 workload, half of them walking
+// Bound by vector issue (173 M VALU instructions at the 256^3 workload, half of them walking
 // boxes) and by latency: list, records, region and sort precede a block's first round, and five
 // blocks a CU (29 KB of LDS, 96 VGPRs) have to cover that.  1M Gaussians on three 256x256x64
 // stacks 378 us, 200k on 128x128x32 90, 20k on 64x64x16 38 (29 with the list in four parts); with

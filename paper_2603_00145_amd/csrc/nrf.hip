@@ -108,7 +108,7 @@ struct Point {
 // also transposed.  Every block leaves one partial of every gradient.
 //
 // Bound by vector issue: per tile some 1000 instructions, most of them the encoding, SiLU and
-// SiLU'.  3 x 262144 points, 16 bands, depth 3: 177 us for all three grids in one launch and 10
+// SiLU'.  3 x 262144 points, 16 bands, depth 3: 162 us for all three grids in one launch and 10
 // for the partials' sums (the biases read from global memory, each read a wait in the middle of
 // a layer: 261).  With dZ and the activations written out in BF16 (700 MB, two bytes
 // a lane at a time), a GEMM pass over them per layer and a chain launch per grid, the chain took

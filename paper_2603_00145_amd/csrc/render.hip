@@ -16,12 +16,16 @@
 // planes, so the in-plane part of the exponent is formed once per column.  The tile keeps a
 // column's four voxels side by side: a lane adds its column with one 16-byte read and one
 // 16-byte write whatever planes the piece reaches (a plane outside the box gets exactly 0).
-// What bounds it at the 256^3 workload is vector issue (89% busy; LDS 72%): about 50
-// instructions per pass, four of them exponentials.  474 us there, 494 for a 320^3 volume of 2M
-// Gaussians; with the pieces in list order and every piece added by itself 505 and 545.  Evaluating only the planes a pass reaches (ten straight-line variants
-// behind one branch) issued fewer but ran 4% slower, fetching the next pass's pieces one pass
-// ahead 2-5% slower, and padding the tile's rows to 17, 20 or 21 columns changed nothing (the
-// 16-byte accesses do not conflict).
+// What bounds it at the 256^3 workload is vector issue (92% busy; LDS 77%, of which 23 of bank
+// conflicts): about 50 instructions per pass, four of them exponentials.  463 us there, 494 for a
+// 320^3 volume of 2M Gaussians; with the pieces in list order and every piece added by itself 505
+// and 545.  Evaluating only the planes a pass reaches (ten straight-line variants behind one
+// branch, two halves of the tile, a path of its own for wide pieces) issued fewer but ran 4 to 13%
+// slower, fetching the next pass's pieces one pass ahead 2-5% slower, and padding the tile's rows
+// to 17, 20 or 21 columns changed no time.  A column is read and written whole, so pieces that
+// reach few of the four planes pay for the others: 256x256x64 stacks of Gaussians 1.5 to 8 voxels
+// wide are rendered 4 to 14% slower than with one add per voxel and reached plane.
+// Short lists are taken by one wavefront a tile (k_render_one), with the same sums.
 // Two consecutive pieces whose footprints sum to at most 64 columns share the wave (the first
 // piece's columns on the low lanes).  Where no column is in both they are added at once, otherwise
 // the first piece's lanes add into the tile before the second's, so every voxel's sum is formed in a fixed order and the result is the same on every

@@ -51,7 +51,7 @@ struct Lds {
     double u[3][ROW];          // an output row's vertical adjoint sums, lane l at l + R
 };
 
-// one wavefront per block: its LDS accesses execute in order, only the compiler has to keep them so
+// a wavefront has an Lds of its own: its LDS accesses execute in order, only the compiler has to keep them so
 __device__ __forceinline__ void lds_order()
 {
     __asm__ __volatile__("" ::: "memory");

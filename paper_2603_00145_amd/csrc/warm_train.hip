@@ -17,8 +17,8 @@
 //     the rows), the operand as it is.
 // Each block keeps its weight-gradient sums in registers over all its samples and writes them
 // once.  A batch of 1024 gives each of 256 blocks four samples; the kernels are bound by the
-// latency of their phases (one wavefront per SIMD), not by throughput (20 GFLOP a step): 50, 50, 85
-// and 17 us, the whole training step 241 us.  One kernel per layer and direction, each storing its
+// latency of their phases (one wavefront per SIMD), not by throughput (20 GFLOP a step): 49, 50, 86
+// and 17 us, the whole training step 205 us.  One kernel per layer and direction, each storing its
 // activations and gathering operands from memory or per output channel tile, took 960 us of a
 // 1118 us step; the same kernels as here with every K step one tap (one 16-byte read per operand)
 // 206 us, but their gradients differ by 1.5e-4 through roundings that fall the other way.
